@@ -524,7 +524,7 @@ typedef struct {
 
 typedef struct {
     int32_t persistent;      /* launch kind: 1 (default) one persistent launch
-                              * pulling tiles from per-XCD queues; 0 one
+                              * whose workgroups walk the tiles in strides; 0 one
                               * workgroup per group of wavefront tiles; other
                               * values are rejected (SPK_ERR_ARG) */
     int32_t use_graph;       /* 1 (default): replay a captured hipGraph */
@@ -566,9 +566,9 @@ spk_status spk_batch_plan(spk_handle h, const spk_batch_desc *desc, const spk_ba
  * then Figure 1's update w = alpha*y + x (w may be NULL for SpMV only), all
  * instances in one launch.  With use_graph the launch is
  * captured once per (stream, x, y, w, alpha) and replayed.  The batch keeps
- * its persistent queue counters and its captured graph per stream, so runs
+ * its captured graph per stream, so runs
  * on different streams (with distinct y / w) may overlap; the first run on a
- * stream allocates that stream's counters and synchronises, so a caller
+ * stream builds that stream's graph and synchronises, so a caller
  * capturing runs into its own graph makes one eager run on the capture
  * stream first.  Calls on one batch from several host threads are
  * serialised by the library only for that per-stream state: runs that share

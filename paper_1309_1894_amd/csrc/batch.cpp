@@ -4,8 +4,8 @@
 // length); each class is served by one tile kernel (LDS row stream, or G
 // lanes per row), taken from the plan DB or from spk_batch_tune.  Instances
 // are cut into tiles of about `tile_nnz` entries; tiles are listed instance
-// by instance and executed by one persistent launch that pulls them from a
-// queue (or one workgroup per tile).  The launch is captured in a hipGraph
+// by instance and executed by one persistent launch that walks them in
+// strides (or one workgroup per tile group).  The launch is captured in a hipGraph
 // once per (x, y, w, alpha) and replayed.
 #include <algorithm>
 #include <cmath>
@@ -17,12 +17,9 @@
 #include "device_common.h"
 #include "internal.h"
 
-// State a batch keeps per stream it runs on: the persistent kind's queue
-// heads and completion count (a run on another stream must not share them:
-// two runs in flight would claim each other's tiles), and the executable
-// graph of the launch, which bakes those counters in.
+// State a batch keeps per stream it runs on: the executable graph of the
+// launch with that stream's operands.
 struct BatchStream {
-    uint32_t *ctr = nullptr;              // 8 per-XCD queue heads (256 B apart), then the done count
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     const void *gx = nullptr;
@@ -54,8 +51,6 @@ struct spk_batch_s {
 };
 
 namespace spk {
-
-constexpr size_t kCounterBytes = 9 * 256;
 
 int batch_class(int64_t m, int64_t nnz)
 {
@@ -145,7 +140,7 @@ void cut_rows(const int32_t *rp, int64_t m, int mode, int entries, int64_t targe
 }
 
 spk_status launch_tiles(const BatchEntry *e, int dtype, const BatchTile *d_tiles, int64_t ntiles, double alpha,
-                        const void *x, void *y, void *w, int kind, uint32_t *ctr, int64_t persistent_grid,
+                        const void *x, void *y, void *w, int kind, int64_t persistent_grid,
                         hipStream_t s, const BatchReq *reqs, const uint16_t *req_of_tile)
 {
     if (ntiles == 0) return SPK_OK;
@@ -167,18 +162,13 @@ spk_status launch_tiles(const BatchEntry *e, int dtype, const BatchTile *d_tiles
         q.y = (T *)y;
         q.w = (T *)w;
         q.alpha = (T)alpha;
-        q.next = ctr;                              // 8 queue heads, 256 bytes apart
-        q.done = ctr ? ctr + 8 * 64 : nullptr;     // then the completion count
         q.reqs = reqs;
         q.req_of_tile = reqs ? req_of_tile : nullptr;
     };
     if (dtype == SPK_F64) fill(a.d); else fill(a.f);
     const int64_t nw = e->block / 64;
     int64_t g = (ntiles + nw - 1) / nw;   // tile groups, one per workgroup
-    // persistent: every XCD queue that holds tiles needs a workgroup of its
-    // own (workgroup b serves queue b % 8), so at least min(8, ntiles)
-    if (kind == kBatchPersistent)
-        g = std::min<int64_t>(persistent_grid, std::max<int64_t>(g, std::min<int64_t>(8, ntiles)));
+    if (kind == kBatchPersistent) g = std::min<int64_t>(persistent_grid, g);
     SPK_HIP(e->fn[dtype][kind](dtype == SPK_F64 ? (const void *)&a.d : (const void *)&a.f, dim3((unsigned)g), s));
     return SPK_OK;
 }
@@ -203,26 +193,11 @@ void invalidate_graph(spk_batch b)
     }
 }
 
-// The state of stream s; on the first use of s, its queue counters are
-// allocated and zeroed (an allocation and a synchronisation: not inside a
-// graph capture, so a captured run needs an eager run on its stream first).
-spk_status stream_state(spk_batch b, hipStream_t s, BatchStream **out)
+// The state of stream s.
+BatchStream *stream_state(spk_batch b, hipStream_t s)
 {
     std::lock_guard<std::mutex> lk(b->mu);
-    BatchStream &st = b->streams[s];
-    if (!st.ctr) {
-        uint32_t *c = nullptr;
-        SPK_HIP(hipMalloc(&c, kCounterBytes));
-        hipError_t e = hipMemsetAsync(c, 0, kCounterBytes, b->h->work);
-        if (e == hipSuccess) e = hipStreamSynchronize(b->h->work);
-        if (e != hipSuccess) {
-            (void)hipFree(c);
-            return hip_fail(e, "batch queue counters");
-        }
-        st.ctr = c;
-    }
-    *out = &st;
-    return SPK_OK;
+    return &b->streams[s];
 }
 
 // Whether the batch's kernel can run mode-3 tiles (compact columns index a
@@ -306,18 +281,25 @@ spk_status replan(spk_batch b)
     return upload_tiles(b, b->tiles);
 }
 
+// Workgroups of the persistent kind: eight times what the GPU holds (or what
+// waves_per_cu asks for).  A wavefront's next tile waits for the last one's
+// stores (loads and stores are counted in order), which a fresh workgroup's
+// does not, so many short walks beat few long ones: 4,096 banded FP64
+// instances take 748 us at one residency, 740 us at eight; 512 take 92.5 and
+// 85.8 us.
+constexpr int64_t kPersistentRounds = 8;
+
+int64_t persistent_cap(const spk_batch b)
+{
+    return b->grid_persistent * (b->opts.waves_per_cu > 0 ? 1 : kPersistentRounds);
+}
+
 // Launches the tile kernel over `ntiles` tiles already on the device, on
-// stream s with s's queue counters.
+// stream s.
 spk_status launch(spk_batch b, int64_t ntiles, double alpha, const void *x, void *y, void *w, hipStream_t s)
 {
-    uint32_t *ctr = nullptr;
-    if (b->opts.persistent == kBatchPersistent) {
-        BatchStream *st = nullptr;
-        SPK_TRY(stream_state(b, s, &st));
-        ctr = st->ctr;
-    }
-    return launch_tiles(b->entry, b->dtype, b->d_tiles, ntiles, alpha, x, y, w, b->opts.persistent, ctr,
-                        b->grid_persistent, s);
+    return launch_tiles(b->entry, b->dtype, b->d_tiles, ntiles, alpha, x, y, w, b->opts.persistent,
+                        persistent_cap(b), s);
 }
 
 spk_status occupancy(spk_batch b)
@@ -452,8 +434,7 @@ spk_status spk_batch_run(spk_handle h, spk_batch b, double alpha, const void *x,
     DeviceGuard g(h);
     hipStream_t s = (hipStream_t)stream;
     if (!b->opts.use_graph) return launch(b, (int64_t)b->tiles.size(), alpha, x, y, w, s);
-    BatchStream *st = nullptr;
-    SPK_TRY(stream_state(b, s, &st));
+    BatchStream *st = stream_state(b, s);
     if (!st->exec || st->gx != x || st->gy != y || st->gw != w || st->galpha != alpha) {
         if (st->exec) {
             // a replay of the old graph may still be queued on s
@@ -463,12 +444,12 @@ spk_status spk_batch_run(spk_handle h, spk_batch b, double alpha, const void *x,
             st->exec = nullptr;
             st->graph = nullptr;
         }
-        // captured on the library's own stream (s may itself be capturing),
-        // with s's counters, for replay on s
+        // captured on the library's own stream (s may itself be capturing)
+        // for replay on s
         SPK_HIP(hipStreamSynchronize(h->work));
         SPK_HIP(hipStreamBeginCapture(h->work, hipStreamCaptureModeThreadLocal));
         spk_status ls = launch_tiles(b->entry, b->dtype, b->d_tiles, (int64_t)b->tiles.size(), alpha, x, y, w,
-                                     b->opts.persistent, st->ctr, b->grid_persistent, h->work);
+                                     b->opts.persistent, persistent_cap(b), h->work);
         hipGraph_t graph = nullptr;
         const hipError_t ce = hipStreamEndCapture(h->work, &graph);
         if (ls != SPK_OK) {
@@ -898,8 +879,6 @@ spk_status spk_batch_free(spk_handle h, spk_batch b)
     if (b->c8) (void)hipFree(b->c8);
     if (b->c16) (void)hipFree(b->c16);
     if (b->d_need16) (void)hipFree(b->d_need16);
-    for (auto &kv : b->streams)
-        if (kv.second.ctr) (void)hipFree(kv.second.ctr);
     delete b;
     return SPK_OK;
 }

@@ -111,13 +111,6 @@ __device__ __forceinline__ double block_sum(double v, double *red)
 // XCD b % 8), each XCD with its own L2.
 constexpr int kXcds = 8;
 
-// XCD k's contiguous eighth of n items starts at xcd_first(k, n).
-__device__ __forceinline__ int xcd_first(int xcd, int n)
-{
-    const int per = n / kXcds, rem = n % kXcds;
-    return xcd * per + min(xcd, rem);
-}
-
 // Chunked dealing: the n items are cut into runs of C, and the runs go to
 // the XCDs in turn (run j to XCD j % 8), in order.  Every XCD meets
 // neighbouring items together (inside a run, so rows that share x entries
@@ -180,8 +173,6 @@ struct BatchArgs {
     T *y;
     T *w;              // may be null (SpMV only)
     T alpha;
-    uint32_t *next;    // tile queue head (persistent launch), zero between launches
-    uint32_t *done;    // finished workgroups (persistent launch), zero between launches
     const BatchReq *reqs;            // serving (grid launch): tiles named per request, or null
     const uint16_t *req_of_tile;     // request of each launch tile (with reqs)
 };

@@ -204,7 +204,7 @@ using BatchFn = hipError_t (*)(const void *args, dim3 grid, hipStream_t);
 // Launch kinds of the batched kernel.  Tiles are wavefront-sized: a
 // workgroup of BS threads runs BS/64 consecutive tiles, one per wavefront.
 constexpr int kBatchGrid = 0;        // one workgroup per group of BS/64 tiles
-constexpr int kBatchPersistent = 1;  // persistent grid pulling tile groups from per-XCD queues
+constexpr int kBatchPersistent = 1;  // persistent grid walking the tile groups in strides
 
 struct BatchEntry {
     int block, tile;     // threads per workgroup, LDS products per workgroup

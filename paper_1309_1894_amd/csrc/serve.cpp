@@ -453,7 +453,7 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
         SPK_TRY(run_spmv(S->h, q, pv, s));
         SPK_TRY(run_waxpy(S->h, M.dtype, M.m, S->opts.alpha, y, x, w, plain_variant(SPK_OP_WAXPY, 0), s));
     } else {
-        SPK_TRY(launch_tiles(S->entry, dtype, nullptr, ntiles, S->opts.alpha, x, y, w, kBatchGrid, nullptr, 0, s,
+        SPK_TRY(launch_tiles(S->entry, dtype, nullptr, ntiles, S->opts.alpha, x, y, w, kBatchGrid, 0, s,
                              (const BatchReq *)dev, (const uint16_t *)(dev + req_b)));
     }
     if (staged == total) {

@@ -474,3 +474,34 @@ def test_batch_compact_columns_width_boundaries(spk, dev, dt):
             b.free()
             h.close()
     assert torch.equal(outs[0][0], outs[3][0]) and torch.equal(outs[0][1], outs[3][1])
+
+
+@pytest.mark.parametrize("dt", [np.float64, np.float32])
+@pytest.mark.parametrize("count", [1, 5, 4099, 80_001])
+def test_batch_persistent_walks_every_tile(spk, dev, count, dt):
+    """One tile per instance: fewer tile groups than the persistent grid's
+    workgroups, and (80,001) more, so that workgroups walk several, the last
+    round ragged.  Every row against the oracle on the block-diagonal matrix
+    (exact: integer data), and the grid kind the same bits."""
+    m, n = 3, 3 * count
+    k = np.arange(7 * count, dtype=np.int64)
+    one = lambda v: np.full(count, v, np.int64)
+    B = I.Batch(one(m), one(7), one(1), (m + 1) * np.arange(count), 7 * np.arange(count), m * np.arange(count),
+                np.tile(np.array([0, 2, 5, 7], np.int32), count),
+                np.tile(np.array([0, 1, 0, 1, 2, 1, 2], np.int32), count), ((k * 7) % 13 - 6).astype(dt))
+    x = ((np.arange(n) * 5) % 11 - 5).astype(dt)
+    ref, _ = O.spmv(I.block_diagonal(B), x)
+    xd = torch.from_numpy(x).to(dev)
+    for persistent in (1, 0):
+        say(f"batch walk count={count} dtype={dt.__name__} persistent={persistent}")
+        y = torch.full((n,), float("nan"), dtype=xd.dtype, device=dev)
+        w = torch.full_like(y, float("nan"))
+        b = spk.Batch(B, _dev_batch(B, dev), persistent=persistent)
+        try:
+            for _ in range(2):
+                b.run(0.5, xd, y, w)
+            torch.cuda.synchronize()
+        finally:
+            b.free()
+        assert np.array_equal(y.cpu().numpy(), ref.astype(dt))
+        assert np.array_equal(w.cpu().numpy(), (0.5 * ref + x).astype(dt))
