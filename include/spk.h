@@ -527,7 +527,10 @@ typedef struct {
                               * whose workgroups walk the tiles in strides; 0 one
                               * workgroup per group of wavefront tiles; other
                               * values are rejected (SPK_ERR_ARG) */
-    int32_t use_graph;       /* 1 (default): replay a captured hipGraph */
+    int32_t use_graph;       /* 1 (default): replay a captured hipGraph (a
+                              * batch of at most 65,536 tiles, whose kernel is
+                              * shorter than a replay costs, is launched
+                              * directly: the same kernel); 0: launch directly */
     int32_t block;           /* threads per workgroup; 0 -> the launch shape
                               * spk_batch_tune recorded for the dtype
                               * (workgroup size, LDS tile and launch kind,
@@ -564,8 +567,8 @@ spk_status spk_batch_plan(spk_handle h, const spk_batch_desc *desc, const spk_ba
 
 /* One step over every instance: Section 3's sparse product y = A_i*x_i,
  * then Figure 1's update w = alpha*y + x (w may be NULL for SpMV only), all
- * instances in one launch.  With use_graph the launch is
- * captured once per (stream, x, y, w, alpha) and replayed.  The batch keeps
+ * instances in one launch.  With use_graph the launch (of more than 65,536
+ * tiles) is captured once per (stream, x, y, w, alpha) and replayed.  The batch keeps
  * its captured graph per stream, so runs
  * on different streams (with distinct y / w) may overlap; the first run on a
  * stream builds that stream's graph and synchronises, so a caller
