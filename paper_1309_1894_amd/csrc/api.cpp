@@ -397,7 +397,7 @@ spk_status run_spmv(spk_handle h, const SpmvProblem &p, const spk_variant &v, hi
     BlockData *bd = nullptr;
     if (v.format == SPK_FMT_SELL) SPK_TRY(get_sell(h, p.mat, v.group, &sd));
     if (v.format == SPK_FMT_ADAPTIVE) {
-        SPK_TRY(get_blocks(h, p.mat, v.lds, &bd));
+        SPK_TRY(get_blocks(h, p.mat, v.lds, v.block, &bd));
         if (v.group > 1) SPK_TRY(get_block_windows(h, p.mat, bd));
         if (e->vec == 2) SPK_TRY(get_block_c16(h, p.mat, bd));
     }
@@ -417,7 +417,9 @@ spk_status run_spmv(spk_handle h, const SpmvProblem &p, const spk_variant &v, hi
     // row over more than 2^24 rows) is run as consecutive launches.
     const int64_t unit = v.format == SPK_FMT_ADAPTIVE ? v.block / 64
                          : v.format == SPK_FMT_VECTOR ? v.block / v.group : v.block;
-    const int64_t span = kMaxLaunchItems / v.block * unit;
+    // (ADAPTIVE launches also hold a workgroup per long row of the range: half
+    // the work-items are kept for those.)
+    const int64_t span = kMaxLaunchItems / v.block / (v.format == SPK_FMT_ADAPTIVE ? 2 : 1) * unit;
 
     auto launch_range = [&](int64_t lo, int64_t hi, hipStream_t st) -> spk_status {
         union {
@@ -426,6 +428,7 @@ spk_status run_spmv(spk_handle h, const SpmvProblem &p, const spk_variant &v, hi
         } args;
         memset(&args, 0, sizeof args);
         dim3 grid;
+        int64_t nlong = 0;
         auto setup = [&](auto &a) {
             using A = std::remove_reference_t<decltype(a)>;
             using T = std::remove_pointer_t<decltype(A::val)>;
@@ -438,6 +441,12 @@ spk_status run_spmv(spk_handle h, const SpmvProblem &p, const spk_variant &v, hi
                 a.block_c16 = e->vec == 2 ? bd->cbase : nullptr;
                 a.blk0 = (int32_t)lo;
                 a.nblk = (int32_t)(hi - lo);   // one wavefront tile per wavefront
+                // the range's long rows
+                const auto l0 = std::lower_bound(bd->longs.begin(), bd->longs.end(), (int32_t)lo);
+                const auto l1 = std::lower_bound(l0, bd->longs.end(), (int32_t)hi);
+                nlong = l1 - l0;
+                a.lrow = nlong ? bd->lrow + (l0 - bd->longs.begin()) : nullptr;
+                a.nlong = (int32_t)nlong;
             } else {
                 a.row0 = (int32_t)lo;
                 a.m = (int32_t)(hi - lo);
@@ -450,7 +459,7 @@ spk_status run_spmv(spk_handle h, const SpmvProblem &p, const spk_variant &v, hi
             }
         };
         if (dtype == SPK_F64) setup(args.d); else setup(args.f);
-        grid = dim3((unsigned)((hi - lo + unit - 1) / unit));
+        grid = dim3((unsigned)(nlong + (hi - lo + unit - 1) / unit));
         SPK_HIP(fn(dtype == SPK_F64 ? (const void *)&args.d : (const void *)&args.f, grid, st));
         return SPK_OK;
     };
@@ -524,25 +533,31 @@ spk_status get_sell(spk_handle h, spk_mat *A, int C, SellData **out)
     return SPK_OK;
 }
 
-spk_status get_blocks(spk_handle h, spk_mat *A, int entries, BlockData **out)
+spk_status get_blocks(spk_handle h, spk_mat *A, int entries, int block, BlockData **out)
 {
     std::lock_guard<std::mutex> lk(h->mu);
-    const auto key = std::make_pair(0, entries);
+    const auto key = std::make_pair((int)long_row_min(block), entries);
     auto it = A->blocks.find(key);
     if (it != A->blocks.end()) {
         *out = &it->second;
         return SPK_OK;
     }
     BlockData d;
-    make_blocks(A->rp_host.data(), A->nrows, entries, d.host, d.host_k);
+    make_row_tiles(A->rp_host.data(), A->nrows, entries, block, d.host, d.host_k, d.longs);
     d.nblk = (int32_t)d.host.size() - 1;
+    std::vector<int32_t> lrow;
+    for (int32_t t : d.longs) lrow.push_back((int32_t)(d.host[t] & kBlkRowMask));
     SPK_HIP(hipMalloc(&d.blk, sizeof(uint32_t) * d.host.size()));
     SPK_HIP(hipMalloc(&d.bk, sizeof(int32_t) * d.host_k.size()));
     SPK_HIP(hipMemcpyAsync(d.blk, d.host.data(), sizeof(uint32_t) * d.host.size(), hipMemcpyHostToDevice, h->work));
     SPK_HIP(hipMemcpyAsync(d.bk, d.host_k.data(), sizeof(int32_t) * d.host_k.size(), hipMemcpyHostToDevice,
                            h->work));
+    if (!lrow.empty()) {
+        SPK_HIP(hipMalloc(&d.lrow, sizeof(int32_t) * lrow.size()));
+        SPK_HIP(hipMemcpyAsync(d.lrow, lrow.data(), sizeof(int32_t) * lrow.size(), hipMemcpyHostToDevice, h->work));
+    }
     SPK_HIP(hipStreamSynchronize(h->work));
-    d.bytes = (int64_t)(sizeof(uint32_t) * d.host.size() + sizeof(int32_t) * d.host_k.size());
+    d.bytes = (int64_t)(sizeof(uint32_t) * d.host.size() + sizeof(int32_t) * (d.host_k.size() + lrow.size()));
     A->bytes += d.bytes;
     auto res = A->blocks.emplace(key, std::move(d));
     *out = &res.first->second;
@@ -610,6 +625,7 @@ static void free_mat(spk_mat *A)
     for (auto &kv : A->blocks) {
         (void)hipFree(kv.second.blk);
         (void)hipFree(kv.second.bk);
+        if (kv.second.lrow) (void)hipFree(kv.second.lrow);
         if (kv.second.bx) (void)hipFree(kv.second.bx);
         if (kv.second.c16) (void)hipFree(kv.second.c16);
         if (kv.second.cbase) (void)hipFree(kv.second.cbase);

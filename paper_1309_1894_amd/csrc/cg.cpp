@@ -137,9 +137,11 @@ spk_status run_cg(spk_handle h, spk_mat *A, const CgEntry *e, const double *b, d
         for (int q = 0; q < 7; ++q) c.st.coef[q] = A->st.coef[q];
     } else {
         BlockData *bd = nullptr;
-        SPK_TRY(get_blocks(h, A, e->entries, &bd));
+        SPK_TRY(get_blocks(h, A, e->entries, e->block, &bd));
         const int nw = e->block / 64;
-        spmv_grid = std::max<int64_t>(1, ((int64_t)bd->nblk + nw - 1) / nw);
+        c.lrow = bd->lrow;
+        c.nlong = (int32_t)bd->longs.size();
+        spmv_grid = c.nlong + std::max<int64_t>(1, ((int64_t)bd->nblk + nw - 1) / nw);
         c.blocks = bd->blk;
         c.block_k = bd->bk;
         c.nblk = bd->nblk;

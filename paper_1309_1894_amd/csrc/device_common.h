@@ -159,6 +159,8 @@ struct SpmvArgs {
     const uint16_t *c16;      // two-byte columns: each row-stream entry's column minus its block's base
     const int32_t *block_c16; // base (first column) of each block with two-byte columns, -1 = none
     int32_t blk0, nblk;
+    const int32_t *lrow;      // rows run by a workgroup each (the launch's first nlong workgroups)
+    int32_t nlong;
 };
 
 // Row blocks of the LDS-staged kernel are wavefront tiles:

@@ -22,6 +22,10 @@ __device__ __forceinline__ void wave_lds_sync()
 }
 
 constexpr int kWaveTileRows = 2 * kWave;   // rows of one wavefront's row stream
+// Entries of a streamed row that its own lane adds; wider rows take 16 lanes.
+// One lane adds four entries per LDS round trip, so a row of 512 took 128 of
+// them with the other lanes idle.
+constexpr int kLaneRowMax = 96;
 
 typedef int int4v __attribute__((ext_vector_type(4)));
 
@@ -56,7 +60,7 @@ __device__ __forceinline__ gptr_mut<T> as_global_mut(T *p) { return (gptr_mut<T>
 // arriving.  Lanes past the tile's end load the tile's last entry or group
 // again (an address in the same page as a valid entry, already cached) and
 // drop it.  Then products to LDS and one lane per row sums them (four
-// interleaved partial sums).
+// interleaved partial sums), or 16 lanes for a row over kLaneRowMax entries.
 // With DOT, also returns the lane's part of sum_i x_i*y_i over the tile's
 // rows (square matrices: x_i is the row's own entry of x).
 // With XW > 0 and xn > 0, the tile's window of x (columns [xlo, xlo + xn),
@@ -177,13 +181,20 @@ __device__ __forceinline__ double wave_stream(const int32_t *rp_, const int32_t 
     for (int q = 0; q < 3; ++q)
         if (l + q * kWave <= nr) srp[l + q * kWave] = rpv[q];
     wave_lds_sync();
-    double dot = 0.0;
+    // one lane per row of up to kLaneRowMax entries: four interleaved partial
+    // sums, four LDS reads in flight
+    double sum[2] = {0.0, 0.0};
+    unsigned long long wide[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const int i = l + q * kWave;
+        int s = 0, e = 0;
         if (i < nr) {
-            // four interleaved partial sums: four LDS reads in flight
-            const int s = srp[i], e = srp[i + 1];
+            s = srp[i];
+            e = srp[i + 1];
+        }
+        wide[q] = __ballot(e - s > kLaneRowMax);
+        if (e - s <= kLaneRowMax) {
             double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
             int k = s;
             for (; k + 3 < e; k += 4) {
@@ -195,7 +206,49 @@ __device__ __forceinline__ double wave_stream(const int32_t *rp_, const int32_t 
             if (k < e) a0 += sp[k];
             if (k + 1 < e) a1 += sp[k + 1];
             if (k + 2 < e) a2 += sp[k + 2];
-            const T yt = (T)((a0 + a1) + (a2 + a3));
+            sum[q] = (a0 + a1) + (a2 + a3);
+        }
+    }
+    // wider rows: 16 lanes each, four rows at a time; a row's own lane takes
+    // the sum
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        unsigned long long left = wide[q];
+        while (left) {
+            int row[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                row[g] = left ? __builtin_ctzll(left) : row[0];
+                left &= left - 1;
+            }
+            const int g = l >> 4;
+            const int i = q * kWave + (g == 0 ? row[0] : g == 1 ? row[1] : g == 2 ? row[2] : row[3]);
+            const int e = srp[i + 1];
+            int k = srp[i] + (l & 15);
+            double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+            for (; k + 48 < e; k += 64) {
+                a0 += sp[k];
+                a1 += sp[k + 16];
+                a2 += sp[k + 32];
+                a3 += sp[k + 48];
+            }
+            if (k < e) a0 += sp[k];
+            if (k + 16 < e) a1 += sp[k + 16];
+            if (k + 32 < e) a2 += sp[k + 32];
+            const double t = group_sum<16>((a0 + a1) + (a2 + a3));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double tu = readlane_f64(t, 16 * u);
+                if (l == row[u]) sum[q] = tu;
+            }
+        }
+    }
+    double dot = 0.0;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int i = l + q * kWave;
+        if (i < nr) {
+            const T yt = (T)sum[q];
             __builtin_nontemporal_store(yt, y + r0 + i);
             if (w) __builtin_nontemporal_store(fma_t(alpha, yt, xo[q]), w + r0 + i);
             if constexpr (DOT) dot = fma_t((double)xo[q], (double)yt, dot);
@@ -280,6 +333,44 @@ __device__ __forceinline__ double wave_rows_mlp(const int32_t *rp, const int32_t
         }
     }
     return dot;
+}
+
+// One row by a whole workgroup: its entries [s, e) in passes of BS*UNR, every
+// lane's value/column loads and then its x gathers in flight together; a
+// fixed order, and the sum returned to every thread.  `red` holds BS/64
+// doubles.
+template <typename T, int BS, int UNR>
+__device__ __forceinline__ double block_row(const int32_t *ci_, const T *val_, const T *x_, int s, int e, double *red)
+{
+    const gptr<int32_t> ci = as_global(ci_);
+    const gptr<T> val = as_global(val_);
+    const gptr<T> x = as_global(x_);
+    double acc[UNR];
+#pragma unroll
+    for (int j = 0; j < UNR; ++j) acc[j] = 0.0;
+    for (int64_t base = s; base < e; base += BS * UNR) {
+        T v[UNR];
+        int c[UNR];
+#pragma unroll
+        for (int j = 0; j < UNR; ++j) {
+            const int64_t k = min(base + (int)threadIdx.x + j * BS, (int64_t)e - 1);
+            c[j] = __builtin_nontemporal_load(ci + k);
+            v[j] = __builtin_nontemporal_load(val + k);
+        }
+        T xv[UNR];
+#pragma unroll
+        for (int j = 0; j < UNR; ++j) xv[j] = x[c[j]];
+#pragma unroll
+        for (int j = 0; j < UNR; ++j) {
+            const double t = fma_t((double)v[j], (double)xv[j], acc[j]);
+            acc[j] = base + (int)threadIdx.x + j * BS < e ? t : acc[j];
+        }
+    }
+#pragma unroll
+    for (int d = 1; d < UNR; d *= 2)
+#pragma unroll
+        for (int j = 0; j + d < UNR; j += 2 * d) acc[j] += acc[j + d];
+    return block_sum<BS>(acc[0], red);
 }
 
 }  // namespace spk

@@ -109,6 +109,8 @@ struct BlockData {
     uint16_t *c16 = nullptr;    // two-byte columns (nnz entries, made when first needed)
     int32_t *cbase = nullptr;   // nblk: base column of each block's two-byte columns, -1 = none
     int32_t nblk = 0;
+    int32_t *lrow = nullptr;    // rows of the kBlkLong tiles (a workgroup each)
+    std::vector<int32_t> longs; // those tiles, ascending
     std::vector<uint32_t> host;
     std::vector<int32_t> host_k;
     int64_t bytes = 0;
@@ -143,7 +145,7 @@ struct spk_mat {
     int64_t max_len = 0;
     int64_t bytes = 0;
     std::map<int, spk::SellData> sell;                       // by slice height
-    std::map<std::pair<int, int>, spk::BlockData> blocks;    // by (0, wavefront entries)
+    std::map<std::pair<int, int>, spk::BlockData> blocks;    // by (long_row_min, wavefront entries)
     spk::StructInfo st;
     spk::DiaData dia;                                        // built on first use
     std::map<int, spk::ColBlockData> colblk;                 // by block count, built on first use
@@ -272,7 +274,7 @@ int64_t format_bytes(const spk_mat *A, int format, bool fused);
 
 // Derived formats of a registered matrix (built on first use; synchronous).
 spk_status get_sell(spk_handle h, spk_mat *A, int C, SellData **out);
-spk_status get_blocks(spk_handle h, spk_mat *A, int entries, BlockData **out);
+spk_status get_blocks(spk_handle h, spk_mat *A, int entries, int block, BlockData **out);
 spk_status get_block_windows(spk_handle h, spk_mat *A, BlockData *bd);
 spk_status get_block_c16(spk_handle h, spk_mat *A, BlockData *bd);
 

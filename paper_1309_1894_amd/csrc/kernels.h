@@ -262,7 +262,9 @@ struct CgLaunch {
     const uint32_t *blocks;    // wavefront tiles: nblk + 1 packed starts
     const int32_t *block_k;    // first entry of each tile
     int32_t nblk;
-    int32_t spmv_grid;         // workgroups of the SpMV kernel = tile groups (slots of part1)
+    const int32_t *lrow;       // rows run by a workgroup each (the first nlong workgroups)
+    int32_t nlong;
+    int32_t spmv_grid;         // workgroups of the SpMV kernel = long rows + tile groups (slots of part1)
     const double *spmv_x;      // operand of the product (p, or x at the start)
     const double *b;
     double *x, *r, *p, *q;     // x, r, p, q 16-byte aligned

@@ -48,7 +48,8 @@ __device__ __forceinline__ double sum_partials(const double *part, int64_t n, do
 // q = A p over wavefront tiles: wavefront w of workgroup b runs tile w of
 // tile group xcd_remap(b) (runs of neighbouring groups per XCD, so groups in
 // flight on an XCD share their x entries in its L2), and the workgroup
-// leaves its part of p.q at that group's index.  With CB = 2 the row-stream
+// leaves its part of p.q at that group's index, after those of the long rows,
+// which the launch's first workgroups run, one each.  With CB = 2 the row-stream
 // tiles that have two-byte columns read those (offsets from the tile's
 // first column) instead of the CSR's.
 template <int BS, int E, int CB>
@@ -58,10 +59,20 @@ __global__ __launch_bounds__(BS) void k_cg_spmv_dot(CgLaunch c)
     __shared__ double sp[NW * E];
     __shared__ int srp[NW * (kWaveTileRows + 1)];
     __shared__ double red[NW];
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int g = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-    const int bl = g * NW + wv;
     const double *p = c.spmv_x;
+    if ((int)blockIdx.x < c.nlong) {
+        // long rows first, a workgroup each
+        const int row = c.lrow[blockIdx.x];
+        const double sum = block_row<double, BS, 8>(c.ci, c.val, p, c.rp[row], c.rp[row + 1], red);
+        if (threadIdx.x == 0) {
+            c.q[row] = sum;
+            if (c.part1) c.part1[blockIdx.x] = p[row] * sum;
+        }
+        return;
+    }
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int g = xcd_remap((int)blockIdx.x - c.nlong, (int)gridDim.x - c.nlong);
+    const int bl = g * NW + wv;
     double d = 0.0;
     if (bl < c.nblk) {
         const uint32_t e0 = c.blocks[bl], e1 = c.blocks[bl + 1];
@@ -76,12 +87,12 @@ __global__ __launch_bounds__(BS) void k_cg_spmv_dot(CgLaunch c)
             d = wave_stream<double, E / kWave, true>(c.rp, c.ci, c.val, p, c.q, nullptr, 0.0, r0, r1,
                                                      c.block_k[bl], c.block_k[bl + 1], sp + wv * E,
                                                      srp + wv * (kWaveTileRows + 1));
-        else
+        else if ((e0 >> 30) == kBlkWave)
             d = wave_rows_mlp<double, 8, true>(c.rp, c.ci, c.val, p, c.q, nullptr, 0.0, r0, r1);
     }
     if (!c.part1) return;   // same for the whole grid
     d = block_sum<BS>(d, red);
-    if (threadIdx.x == 0) c.part1[g] = d;
+    if (threadIdx.x == 0) c.part1[c.nlong + g] = d;
 }
 
 // q = A p for a constant-coefficient grid stencil (no matrix arrays): a

@@ -13,8 +13,8 @@
 //   ADAPTIVE precomputed wavefront tiles: runs of short rows whose entries
 //            fit a wavefront's LDS slice are streamed into LDS with
 //            coalesced loads and summed per row from LDS; runs of medium
-//            rows, and single long rows, get a wavefront (64 lanes per row,
-//            eight loads and gathers in flight per lane).  Streaming short
+//            rows get a wavefront (64 lanes per row, eight loads and gathers
+//            in flight per lane), single long rows a workgroup.  Streaming short
 //            rows through on-chip memory and giving long rows a vector of
 //            their own is the CSR-Stream / CSR-Adaptive scheme published by
 //            Greathouse and Daga (SC 2014); here each wavefront streams its
@@ -183,7 +183,8 @@ __global__ __launch_bounds__(BS) void k_spmv_sell(SpmvArgs<T> a)
 
 // Row blocks are wavefront tiles (precomputed at registration for a
 // wavefront capacity of E entries): each wavefront of a workgroup runs its
-// own block with a private LDS slice, without workgroup barriers.
+// own block with a private LDS slice, without workgroup barriers.  Rows over
+// long_row_min entries get the launch's first workgroups, one each.
 // With XW > 0, row-stream blocks whose x window fits XW entries take x from
 // LDS (the window copied there beside the entry loads).  With CB = 2,
 // row-stream blocks whose columns span at most 65,536 read two-byte column
@@ -197,9 +198,16 @@ __global__ __launch_bounds__(BS) void k_spmv_adaptive(SpmvArgs<T> a)
     __shared__ double sp[NW * E];
     __shared__ int srp[NW * (kWaveTileRows + 1)];
     __shared__ T xs[NW * (XW > 0 ? XW : 1)];
+    if ((int)blockIdx.x < a.nlong) {
+        // long rows first, a workgroup each: they take longest
+        const int row = a.lrow[blockIdx.x];
+        const double sum = block_row<T, BS, 8>(a.ci, a.val, a.x, a.rp[row], a.rp[row + 1], sp);
+        if (threadIdx.x == 0) store_row<T, FUSED>(a, row, sum);
+        return;
+    }
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int ngroups = (a.nblk + NW - 1) / NW;
-    const int g = xcd_remap((int)blockIdx.x, ngroups);
+    const int g = xcd_remap((int)blockIdx.x - a.nlong, ngroups);
     const int bl = g * NW + wv;
     if (bl >= a.nblk) return;
     const int b = a.blk0 + bl;
@@ -227,8 +235,8 @@ __global__ __launch_bounds__(BS) void k_spmv_adaptive(SpmvArgs<T> a)
         wave_stream<T, E / kWave, false, XW>(a.rp, a.ci, a.val, a.x, a.y, w, a.alpha, r0, r1, a.block_k[b],
                                              a.block_k[b + 1], sp + wv * E, srp + wv * (kWaveTileRows + 1), xlo, xn,
                                              xs + wv * (XW > 0 ? XW : 1));
-    } else {
-        // medium rows (kBlkWave) and single long rows (kBlkLong)
+    } else if (mode == kBlkWave) {
+        // medium rows (a kBlkLong tile's row is a workgroup's)
         wave_rows_mlp<T, 8>(a.rp, a.ci, a.val, a.x, a.y, w, a.alpha, r0, r1);
     }
 }

@@ -421,3 +421,38 @@ def test_row_blocks_two_byte_columns_at_the_width_limit(spk, dev, dt):
             assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1]), far
         finally:
             M.release()
+
+
+@pytest.mark.parametrize("dt", [1, 0])
+def test_row_tiles_at_the_length_limits(spk, dev, dt):
+    """Row lengths on both sides of every limit of the row-block tiles (one
+    lane, 16 lanes, a wavefront, a workgroup per row), mixed, every row-block
+    variant, plain and fused, on one, two and four streams.  Integer data:
+    every sum is exact, so the outputs are compared bit for bit."""
+    lens = [0, 1, 95, 96, 97, 3, 128, 255, 256, 257, 0, 511, 512, 513, 5, 600, 1023, 1024, 1025, 2, 2047, 2048, 2049,
+            4096, 4097, 1, 0, 98, 99, 100, 101, 130, 1, 1, 4700, 513, 514] + [97] * 9 + [2] * 150 + [1025]
+    n = 4800
+    rng = np.random.default_rng(5)
+    rp = np.concatenate([[0], np.cumsum(lens + [0] * (n - len(lens)))]).astype(np.int32)
+    A = I.CSR(n, n, rp, rng.integers(0, n, rp[-1]).astype(np.int32), rng.integers(-8, 9, rp[-1]).astype(NP[dt]))
+    x = rng.integers(-8, 9, n).astype(NP[dt])
+    ref, _ = O.spmv(A, x)
+    M = spk.Matrix(A)
+    xd = torch.from_numpy(x).to(dev)
+    y, w = torch.empty_like(xd), torch.empty_like(xd)
+    vs = [v for v in spk.variants(spk.SPK_OP_SPMV, dt) if v.format == spk.SPK_FMT_ADAPTIVE]
+    say(f"row tiles at their limits dtype={dt}: {len(vs)} variants")
+    try:
+        for v in vs:
+            for streams in (1, 2, 4):
+                v.streams = streams
+                y.fill_(float("nan"))
+                spk.spk_run(spk.problem(spk.SPK_OP_SPMV, A=M, x=xd, y=y), v)
+                assert np.array_equal(y.cpu().numpy(), ref.astype(NP[dt])), v
+                y.fill_(float("nan"))
+                w.fill_(float("nan"))
+                spk.spk_run(spk.problem(spk.SPK_OP_SPMV_WAXPY, A=M, x=xd, y=y, w=w, alpha=0.5), v)
+                assert np.array_equal(y.cpu().numpy(), ref.astype(NP[dt])), v
+                assert np.array_equal(w.cpu().numpy(), (0.5 * ref + x).astype(NP[dt])), v
+    finally:
+        M.release()
