@@ -369,7 +369,9 @@ spk_status spk_spmv_waxpy(spk_handle h, spk_matrix A, double alpha, const void *
  * direction updates in one pass over p.  The SpMV+dot kernel is the one
  * spk_cg_tune recorded for A's class (a CSR wavefront-tile shape, or the
  * matrix-free form when A is a constant-coefficient grid stencil), else a
- * default tile shape.
+ * default tile shape.  A small system (up to 4,096 rows of up to 7 entries,
+ * 3,072 of 8, 2,048 of 12 or 1,024 of 24) for whose class nothing is
+ * recorded is solved by one launch of one workgroup.
  *   b        device, n doubles (right-hand side), read only
  *   x        device, n doubles, 8-byte aligned: initial guess on entry, the
  *            iterate after `iters` iterations on return
@@ -487,9 +489,10 @@ spk_status spk_plan_put(spk_handle h, const char *class_key, const spk_variant *
  * of the residual kernel adds, so the solve's best shape can differ from a
  * lone SpMV's; or, when A is a grid stencil (spk_matrix_formats), the
  * matrix-free kernel (SPK_FMT_STENCIL, `block` threads, `unroll` rows per
- * lane, `lds` 1 = p staged through LDS).  opts->formats
- * limits the search (bits 1 << SPK_FMT_ADAPTIVE, 1 << SPK_FMT_STENCIL; 0 =
- * all that apply).  Every candidate runs `iters` iterations
+ * lane, `lds` 1 = p staged through LDS); or, when the system is small enough,
+ * the one-workgroup solve (SPK_FMT_SELL, `block` 1024).  opts->formats
+ * limits the search (bits 1 << SPK_FMT_ADAPTIVE, 1 << SPK_FMT_STENCIL,
+ * 1 << SPK_FMT_SELL; 0 = all that apply).  Every candidate runs `iters` iterations
  * from x = 0 on b (device, n doubles); its r.r history and x must match
  * the default shape's run within tau (relative per entry of the history,
  * relative to max |x| for x; opts->tau, 0 -> 1e-10) or it is discarded

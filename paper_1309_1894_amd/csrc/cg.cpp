@@ -12,7 +12,8 @@
 // count, hence the number of partials every workgroup of the residual
 // kernel adds up, so the best shape for the solve need not be the best for
 // a lone SpMV; or, for a matrix that is a constant-coefficient grid
-// stencil, the matrix-free form.  spk_cg_tune applies Section 2's search to
+// stencil, the matrix-free form; or, for a small system, the whole solve in
+// one workgroup.  spk_cg_tune applies Section 2's search to
 // it and files the winner under "cg:" + the matrix's SpMV class key.
 #include <algorithm>
 #include <cmath>
@@ -51,6 +52,7 @@ const CgEntry *default_cg_entry()
 bool cg_entry_fits(const spk_mat *A, const CgEntry &e)
 {
     if (!format_applies(A, e.format)) return false;
+    if (e.format == SPK_FMT_SELL) return cg_small_fits(A->nrows, A->max_len);
     if (e.format == SPK_FMT_STENCIL && e.lds)
         return stencil_lds_bytes(e.block, e.entries, A->st.dim, A->st.N3, 8) <= kStencilLdsMaxBytes;
     return true;
@@ -65,7 +67,9 @@ std::string cg_key(spk_mat *A)
     return "cg:" + class_key(p, nullptr);
 }
 
-// The SpMV+dot kernel recorded for A's class, else the default tile shape.
+// The kernel recorded for A's class; else, for a system it takes, the
+// one-workgroup solve (kernels_cg.hip: as far as the rows' entries fit one
+// workgroup's registers), else the default tile shape.
 const CgEntry *cg_entry_for(spk_handle h, spk_mat *A)
 {
     if (!h->plain) {
@@ -79,6 +83,8 @@ const CgEntry *cg_entry_for(spk_handle h, spk_mat *A)
             if (e && cg_entry_fits(A, *e)) return e;
         }
     }
+    const CgEntry *small = find_cg_entry(SPK_FMT_SELL, kCgSmallBlock, 0, 0);
+    if (!h->plain && small && cg_entry_fits(A, *small)) return small;
     return default_cg_entry();
 }
 
@@ -116,6 +122,13 @@ spk_status run_cg(spk_handle h, spk_mat *A, const CgEntry *e, const double *b, d
                   double *hist, hipStream_t s)
 {
     const int64_t n = A->nrows;
+    if (e->format == SPK_FMT_SELL) {
+        SellData *sd = nullptr;
+        SPK_TRY(get_sell(h, A, 64, &sd));
+        SPK_HIP(launch_cg_small(n, A->max_len, iters, sd->ptr, sd->len, sd->ci, (const double *)sd->val, b, x, hist,
+                                s));
+        return SPK_OK;
+    }
     // the vector kernels make one pass with at most 8 workgroups per CU
     // (their partials are re-read by every workgroup of the consuming
     // kernel); the tile SpMV runs one workgroup per tile group, the stencil

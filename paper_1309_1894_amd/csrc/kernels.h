@@ -283,13 +283,28 @@ using CgFn = hipError_t (*)(const CgLaunch &, hipStream_t);
 
 // An SpMV+dot kernel of the solve: SPK_FMT_ADAPTIVE (CSR wavefront tiles of
 // `entries` entries, one workgroup per tile group) or SPK_FMT_STENCIL
-// (matrix-free, grid-stride rows, `entries` rows per lane).
+// (matrix-free, grid-stride rows, `entries` rows per lane); or
+// SPK_FMT_SELL, the whole solve of a small system in one workgroup.
 struct CgEntry {
     int format, block, entries;
     int lds;                   // matrix-free: 1 = p staged through LDS
     CgFn spmv_dot;
     int vec = 0;               // tiles: 2 = two-byte columns in the row-stream tiles
 };
+
+// The one-workgroup solve (SPK_FMT_SELL entry): its threads, and whether it
+// takes a system of n rows whose longest has max_len entries (a thread holds
+// at most four rows and 28 entries in registers).
+constexpr int kCgSmallBlock = 1024;
+inline bool cg_small_fits(int64_t n, int64_t max_len)
+{
+    const int64_t rpt = (n + kCgSmallBlock - 1) / kCgSmallBlock;
+    const int64_t w[5] = {0, 24, 12, 8, 7};
+    return rpt >= 1 && rpt <= 4 && max_len <= w[rpt];
+}
+hipError_t launch_cg_small(int64_t n, int64_t max_len, int32_t iters, const int64_t *ptr, const int32_t *len,
+                           const int32_t *ci, const double *val, const double *b, double *x, double *hist,
+                           hipStream_t s);
 
 const CgEntry *cg_table(int *count);
 hipError_t launch_cg_start(const CgLaunch &c, hipStream_t s);

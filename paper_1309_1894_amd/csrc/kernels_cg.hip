@@ -368,6 +368,120 @@ __global__ __launch_bounds__(BS) void k_cg_record(CgLaunch c)
     }
 }
 
+// The whole solve of a small system in one workgroup: row i belongs to
+// thread i % BS, which keeps its rows' x and r in registers; p lives in LDS,
+// where the products gather it; a reduction is one wavefront sum and one
+// barrier.  The rows' entries (at most W each) are read once, from the
+// sliced-ELL copy, and stay in registers too, so an iteration touches no
+// memory but LDS: it is bound by its dependent steps (product, two
+// reductions, three barriers).  Same recurrence and step-size rule as the
+// three-kernel form.  50 iterations on lap2d(48) (2,304 rows): 593 us with
+// three launches an iteration, 93 us here; the entries of 5,184 rows no
+// longer fit the registers, and streaming them from L2 through one compute
+// unit took 14 us an iteration against 13 us of the three launches.
+struct CgSmall {
+    int32_t n, iters;
+    const int64_t *ptr;        // sliced ELL, slices of 64 rows
+    const int32_t *len, *ci;
+    const double *val;
+    const double *b;
+    double *x, *hist;
+};
+
+template <int BS>
+__device__ __forceinline__ double small_sum(double v, double *red)
+{
+    v = group_sum<kWave>(v);
+    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = v;
+    __syncthreads();
+    double t = red[0];
+#pragma unroll
+    for (int i = 1; i < BS / kWave; ++i) t += red[i];
+    return t;
+}
+
+template <int BS, int RPT, int W>
+__global__ __launch_bounds__(BS) void k_cg_small(CgSmall c)
+{
+    __shared__ double ps[BS * RPT + 1];     // p, then a zero that absent entries gather
+    __shared__ double red[2][BS / kWave];   // two, so that one barrier per reduction is enough
+    const int t = (int)threadIdx.x;
+    const int l = t & (kWave - 1);
+    double v[RPT][W];
+    uint32_t cc[RPT][(W + 1) / 2];   // two columns (n <= 65,536) to a register
+    double x[RPT], r[RPT], q[RPT];
+    if (t == 0) ps[BS * RPT] = 0.0;
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+        const int i = t + j * BS;
+        const bool in = i < c.n;
+        const int len = in ? c.len[i] : 0;
+        x[j] = in ? c.x[i] : 0.0;
+        ps[i] = x[j];
+        const int64_t base = len > 0 ? c.ptr[i / kWave] + l : 0;
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            const int64_t at = base + (int64_t)min(k, max(len - 1, 0)) * kWave;
+            const double vk = c.val[at];
+            const uint32_t ck = (uint32_t)c.ci[at];
+            v[j][k] = k < len ? vk : 0.0;
+            const uint32_t col = k < len ? ck : (uint32_t)(BS * RPT);
+            if (k & 1) cc[j][k / 2] |= col << 16;
+            else cc[j][k / 2] = col;
+        }
+    }
+    // q = A ps
+    auto product = [&]() {
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            q[j] = 0.0;
+#pragma unroll
+            for (int k = 0; k < W; ++k) q[j] = fma_t(v[j][k], ps[(cc[j][k / 2] >> (16 * (k & 1))) & 0xffffu], q[j]);
+        }
+    };
+    __syncthreads();
+    product();
+    double rr = 0.0;
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+        const int i = t + j * BS;
+        r[j] = i < c.n ? fma_t(-1.0, q[j], c.b[i]) : 0.0;
+        rr = fma_t(r[j], r[j], rr);
+    }
+    rr = small_sum<BS>(rr, red[0]);   // its barrier: every read of ps is done
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) ps[t + j * BS] = r[j];
+    if (t == 0) c.hist[0] = rr;
+    for (int it = 0; it < c.iters; ++it) {
+        __syncthreads();
+        product();
+        double d = 0.0;
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) d = fma_t(ps[t + j * BS], q[j], d);
+        const double pq = small_sum<BS>(d, red[1]);
+        const double alpha = pq != 0.0 ? rr / pq : 0.0;
+        d = 0.0;
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            r[j] = fma_t(-alpha, q[j], r[j]);
+            d = fma_t(r[j], r[j], d);
+        }
+        const double rn = small_sum<BS>(d, red[0]);
+        const double beta = rr != 0.0 ? rn / rr : 0.0;
+        rr = rn;
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            const double p = ps[t + j * BS];
+            x[j] = fma_t(alpha, p, x[j]);
+            ps[t + j * BS] = fma_t(beta, p, r[j]);
+        }
+        if (t == 0) c.hist[it + 1] = rn;
+    }
+#pragma unroll
+    for (int j = 0; j < RPT; ++j)
+        if (t + j * BS < c.n) c.x[t + j * BS] = x[j];
+}
+
 // hist[0, count) = 0 (the solve of an empty system).
 __global__ __launch_bounds__(256) void k_cg_zero(double *hist, int64_t count)
 {
@@ -426,6 +540,8 @@ const CgEntry kCg[] = {
     {6, 512, 2, 0, L_stencil_dot<512, 2>}, {6, 512, 4, 0, L_stencil_dot<512, 4>},
     {6, 256, 2, 1, L_stencil_lds<256, 2>}, {6, 256, 4, 1, L_stencil_lds<256, 4>},
     {6, 512, 2, 1, L_stencil_lds<512, 2>}, {6, 512, 4, 1, L_stencil_lds<512, 4>},
+    // the whole solve in one workgroup (no SpMV kernel of its own)
+    {3, kCgSmallBlock, 0, 0, nullptr},
 };
 #undef TILES
 #undef TILES16
@@ -461,6 +577,27 @@ hipError_t launch_cg_direction(const CgLaunch &c, hipStream_t s)
 hipError_t launch_cg_record(const CgLaunch &c, hipStream_t s)
 {
     hipLaunchKernelGGL((k_cg_record<kCgVecBlock>), dim3(1), dim3(kCgVecBlock), 0, s, c);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_small(int64_t n, int64_t max_len, int32_t iters, const int64_t *ptr, const int32_t *len,
+                           const int32_t *ci, const double *val, const double *b, double *x, double *hist,
+                           hipStream_t s)
+{
+    constexpr int BS = kCgSmallBlock;
+    const CgSmall c{(int32_t)n, iters, ptr, len, ci, val, b, x, hist};
+    const int rpt = (int)((n + BS - 1) / BS);
+#define SMALL(RPT, W) hipLaunchKernelGGL((k_cg_small<BS, RPT, W>), dim3(1), dim3(BS), 0, s, c)
+    if (rpt == 1 && max_len <= 8) SMALL(1, 8);
+    else if (rpt == 1 && max_len <= 24) SMALL(1, 24);
+    else if (rpt == 2 && max_len <= 6) SMALL(2, 6);
+    else if (rpt == 2 && max_len <= 12) SMALL(2, 12);
+    else if (rpt == 3 && max_len <= 6) SMALL(3, 6);
+    else if (rpt == 3 && max_len <= 8) SMALL(3, 8);
+    else if (rpt == 4 && max_len <= 6) SMALL(4, 6);
+    else if (rpt == 4 && max_len <= 7) SMALL(4, 7);
+    else return hipErrorInvalidValue;
+#undef SMALL
     return hipGetLastError();
 }
 

@@ -328,3 +328,54 @@ def test_cg_irregular_spd_long_run(spk, dev):
     assert np.abs(x - xo).max() <= 1e-12 * scale
     assert np.linalg.norm(b - S @ x) <= 1e-12 * np.linalg.norm(b)
     assert hist[-1] <= 1e-30 * hist[0] and ho[-1] <= 1e-30 * ho[0]
+
+
+def _band_spd(n, half, seed):
+    """Symmetric band of half-width ``half`` with distinct values, diagonally
+    dominant; the longest row has 2*half + 1 entries."""
+    r = np.arange(n)
+    rows, cols, vals = [r], [r], [2.0 * half + 1.0 + (r % 5)]
+    for d in range(1, min(half, n - 1) + 1):
+        v = I.uniform(seed, d, n - d)
+        rows += [r[:-d], r[d:]]
+        cols += [r[d:], r[:-d]]
+        vals += [v, v]
+    rows, cols, vals = np.concatenate(rows), np.concatenate(cols), np.concatenate(vals)
+    o = np.lexsort((cols, rows))
+    rp = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))]).astype(np.int32)
+    return I.CSR(n, n, rp, cols[o].astype(np.int32), vals[o])
+
+
+@pytest.mark.parametrize("n,half", [(1, 1), (2, 1), (63, 3), (1023, 3), (1024, 11), (1024, 12), (1025, 2), (2048, 5),
+                                    (2048, 6), (2049, 2), (3071, 3), (3072, 3), (3073, 2), (4095, 3), (4096, 2),
+                                    (4096, 3), (4097, 2)])
+def test_cg_one_workgroup_solve_at_its_limits(spk, dev, n, half):
+    """Rows per thread and entries per row on both sides of what the
+    one-workgroup solve takes, against the oracle; an x that is 8-byte but not
+    16-byte aligned and repeated solves give the same bits; the recorded
+    default tile shape (three kernels an iteration) agrees too."""
+    A = _band_spd(n, half, 41)
+    b, x0 = _vecs(A, 42)
+    iters = 12
+    xo, ho = O.cg(A, b, iters, x0)
+    say("cg one workgroup", n, half)
+    H = spk.Handle()
+    try:
+        M = spk.Matrix(A, handle=H)
+        x, hist = _run(spk, M, b, x0, iters, dev)
+        live = ho > 1e-24 * ho[0]      # past that r.r is rounding of an exactly solved system
+        assert np.all(np.abs(hist - ho)[live] <= RTOL * ho[live])
+        assert np.all(np.abs(x - xo) <= RTOL * np.abs(xo).max())
+        pad = torch.zeros(n + 1, dtype=torch.float64, device=dev)
+        pad[1:] = torch.from_numpy(x0).to(dev)
+        h2 = spk.spk_cg(M, torch.from_numpy(b).to(dev), pad[1:], iters)
+        assert np.array_equal(pad[1:].cpu().numpy(), x) and np.array_equal(h2.cpu().numpy(), hist)
+        key = "cg:" + spk.spk_class_key(spk.problem(spk.SPK_OP_SPMV, A=M), handle=H)
+        spk.spk_plan_put(key, spk.make_variant(format=spk.SPK_FMT_ADAPTIVE, block=512, group=1, unroll=1, lds=512,
+                                               streams=1), handle=H)
+        xt, ht = _run(spk, M, b, x0, iters, dev)
+        assert np.all(np.abs(ht - ho)[live] <= RTOL * ho[live])
+        assert np.all(np.abs(xt - xo) <= RTOL * np.abs(xo).max())
+        M.release()
+    finally:
+        H.close()
