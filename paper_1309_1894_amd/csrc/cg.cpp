@@ -134,9 +134,17 @@ spk_status run_cg(spk_handle h, spk_mat *A, const CgEntry *e, const double *b, d
     // kernel); the tile SpMV runs one workgroup per tile group, the stencil
     // SpMV a grid-stride loop on the same cap
     const int64_t cap = 8ll * h->num_cu;
-    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>((n + kCgVecPer - 1) / kCgVecPer, cap));
     CgLaunch c;
     memset(&c, 0, sizeof c);
+    // One access per lane while that gives at most one workgroup per CU: up
+    // to there a workgroup more costs less than a longer one (and every
+    // chunk, the ragged one too, is one round of loads).  An iteration on
+    // lap2d(90) (8,100 rows) takes 12.2 us so, 15.8 us with four accesses;
+    // lap2d(250) 12.5 and 14.2; from lap2d(360) to lap3d(100) both take the
+    // same, and on lap3d(128) one access is 7% slower.
+    c.unroll = n <= cg_vec_per(1) * h->num_cu ? 1 : kCgVecUnroll;
+    const int64_t per_wg = cg_vec_per(c.unroll);
+    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>((n + per_wg - 1) / per_wg, cap));
     int64_t spmv_grid = 1;
     if (e->format == SPK_FMT_STENCIL) {
         if (!cg_entry_fits(A, *e)) return fail(SPK_ERR_ARG, "A is not a grid stencil this kernel can run");

@@ -253,7 +253,7 @@ hipError_t launch_block_c16(const uint32_t *blocks, const int32_t *block_k, cons
 // carries alpha from the residual kernel to the direction kernel.
 constexpr int kCgAlpha = 2, kCgScalars = 3;
 constexpr int kCgVecBlock = 256, kCgVecUnroll = 4;
-constexpr int64_t kCgVecPer = (int64_t)kCgVecBlock * 2 * kCgVecUnroll;   // elements per workgroup pass
+inline int64_t cg_vec_per(int unroll) { return (int64_t)kCgVecBlock * 2 * unroll; }   // elements per workgroup pass
 
 struct CgLaunch {
     int64_t n;                 // rows (= columns)
@@ -275,6 +275,7 @@ struct CgLaunch {
     const uint16_t *c16;       // two-byte columns of the tiles (entries with vec 2), else null
     const int32_t *block_c16;  // base column of each tile's two-byte columns, -1 = none
     int32_t slot;              // iteration parity
+    int32_t unroll;            // accesses in flight per lane of the vector kernels (1 or kCgVecUnroll)
     int64_t grid;              // workgroups of the vector kernels (slots of part2)
     StencilArgs st;            // stencil form of the matrix (SpMV+dot of a STENCIL entry)
 };

@@ -60,10 +60,10 @@ __global__ __launch_bounds__(BS) void k_cg_spmv_dot(CgLaunch c)
     __shared__ int srp[NW * (kWaveTileRows + 1)];
     __shared__ double red[NW];
     const double *p = c.spmv_x;
-    if ((int)blockIdx.x < c.nlong) {
+    if (__builtin_expect((int)blockIdx.x < c.nlong, 0)) {
         // long rows first, a workgroup each
         const int row = c.lrow[blockIdx.x];
-        const double sum = block_row<double, BS, 8>(c.ci, c.val, p, c.rp[row], c.rp[row + 1], red);
+        const double sum = block_row<double, BS, 4>(c.ci, c.val, p, c.rp[row], c.rp[row + 1], red);
         if (threadIdx.x == 0) {
             c.q[row] = sum;
             if (c.part1) c.part1[blockIdx.x] = p[row] * sum;
@@ -219,7 +219,9 @@ __global__ __launch_bounds__(BS) void k_cg_stencil_lds(CgLaunch c)
 // alpha = rr / p.q, r -= alpha q, part2 = this workgroup's r.r; the first
 // workgroup stores alpha for the direction kernel.  Two doubles per lane
 // access, UNR accesses in flight; the first chunk's loads are issued before
-// p.q is assembled.
+// p.q is assembled.  With UNR = 1 every workgroup has one chunk, and a ragged
+// one is loaded up front too; with more (whose registers a second set of
+// loads would cost occupancy) a ragged chunk is walked in dependent steps.
 template <int BS, int UNR>
 __global__ __launch_bounds__(BS) void k_cg_residual(CgLaunch c)
 {
@@ -240,6 +242,14 @@ __global__ __launch_bounds__(BS) void k_cg_residual(CgLaunch c)
     };
     bool full = base + PER <= n;
     if (full) load(base);
+    else if constexpr (UNR == 1) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int64_t i = min(base + 2 * t + k, n - 1);
+            rv[0][k] = c.r[i];
+            qv[0][k] = c.q[i];
+        }
+    }
     const double pq = sum_partials<BS>(c.part1, c.spmv_grid, red);
     const double rr = c.sc[c.slot];
     const double alpha = pq != 0.0 ? rr / pq : 0.0;
@@ -258,6 +268,16 @@ __global__ __launch_bounds__(BS) void k_cg_residual(CgLaunch c)
                 acc[u] = fma_t(rn[0], rn[0], acc[u]);
                 acc[u] = fma_t(rn[1], rn[1], acc[u]);
                 *(f64x2_t *)(c.r + i) = rn;
+            }
+        } else if constexpr (UNR == 1) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int64_t i = base + 2 * t + k;
+                const double rn = fma_t(-alpha, qv[0][k], rv[0][k]);
+                if (i < n) {
+                    c.r[i] = rn;
+                    acc[0] = fma_t(rn, rn, acc[0]);
+                }
             }
         } else {
             for (int64_t i = base + t; i < n && i < base + PER; i += BS) {
@@ -300,6 +320,15 @@ __global__ __launch_bounds__(BS) void k_cg_direction(CgLaunch c)
     };
     bool full = base + PER <= n;
     if (full) load(base);
+    else if constexpr (UNR == 1) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int64_t i = min(base + 2 * t + k, n - 1);
+            xv[0][k] = c.x[i];
+            rv[0][k] = c.r[i];
+            pv[0][k] = c.p[i];
+        }
+    }
     const double rr_new = sum_partials<BS>(c.part2, c.grid, red);
     const double rr = c.sc[c.slot];
     const double beta = rr != 0.0 ? rr_new / rr : 0.0;
@@ -320,6 +349,15 @@ __global__ __launch_bounds__(BS) void k_cg_direction(CgLaunch c)
                 pn[1] = fma_t(beta, pv[u][1], rv[u][1]);
                 __builtin_nontemporal_store(xn, (f64x2_t *)(c.x + i));
                 *(f64x2_t *)(c.p + i) = pn;
+            }
+        } else if constexpr (UNR == 1) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int64_t i = base + 2 * t + k;
+                if (i < n) {
+                    c.x[i] = fma_t(alpha, pv[0][k], xv[0][k]);
+                    c.p[i] = fma_t(beta, pv[0][k], rv[0][k]);
+                }
             }
         } else {
             for (int64_t i = base + t; i < n && i < base + PER; i += BS) {
@@ -554,25 +592,19 @@ const CgEntry *cg_table(int *count)
     return kCg;
 }
 
-hipError_t launch_cg_start(const CgLaunch &c, hipStream_t s)
-{
-    hipLaunchKernelGGL((k_cg_start<kCgVecBlock, kCgVecUnroll>), dim3((unsigned)c.grid), dim3(kCgVecBlock), 0, s, c);
-    return hipGetLastError();
-}
+// The vector kernels with the launch's accesses per lane.
+#define VEC_LAUNCH(K)                                                                                            \
+    if (c.unroll == 1)                                                                                           \
+        hipLaunchKernelGGL((K<kCgVecBlock, 1>), dim3((unsigned)c.grid), dim3(kCgVecBlock), 0, s, c);              \
+    else                                                                                                         \
+        hipLaunchKernelGGL((K<kCgVecBlock, kCgVecUnroll>), dim3((unsigned)c.grid), dim3(kCgVecBlock), 0, s, c);   \
+    return hipGetLastError()
 
-hipError_t launch_cg_residual(const CgLaunch &c, hipStream_t s)
-{
-    hipLaunchKernelGGL((k_cg_residual<kCgVecBlock, kCgVecUnroll>), dim3((unsigned)c.grid), dim3(kCgVecBlock), 0, s,
-                       c);
-    return hipGetLastError();
-}
+hipError_t launch_cg_start(const CgLaunch &c, hipStream_t s) { VEC_LAUNCH(k_cg_start); }
+hipError_t launch_cg_residual(const CgLaunch &c, hipStream_t s) { VEC_LAUNCH(k_cg_residual); }
+hipError_t launch_cg_direction(const CgLaunch &c, hipStream_t s) { VEC_LAUNCH(k_cg_direction); }
 
-hipError_t launch_cg_direction(const CgLaunch &c, hipStream_t s)
-{
-    hipLaunchKernelGGL((k_cg_direction<kCgVecBlock, kCgVecUnroll>), dim3((unsigned)c.grid), dim3(kCgVecBlock), 0, s,
-                       c);
-    return hipGetLastError();
-}
+#undef VEC_LAUNCH
 
 hipError_t launch_cg_record(const CgLaunch &c, hipStream_t s)
 {

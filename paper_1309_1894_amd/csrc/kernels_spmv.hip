@@ -198,10 +198,10 @@ __global__ __launch_bounds__(BS) void k_spmv_adaptive(SpmvArgs<T> a)
     __shared__ double sp[NW * E];
     __shared__ int srp[NW * (kWaveTileRows + 1)];
     __shared__ T xs[NW * (XW > 0 ? XW : 1)];
-    if ((int)blockIdx.x < a.nlong) {
+    if (__builtin_expect((int)blockIdx.x < a.nlong, 0)) {
         // long rows first, a workgroup each: they take longest
         const int row = a.lrow[blockIdx.x];
-        const double sum = block_row<T, BS, 8>(a.ci, a.val, a.x, a.rp[row], a.rp[row + 1], sp);
+        const double sum = block_row<T, BS, 4>(a.ci, a.val, a.x, a.rp[row], a.rp[row + 1], sp);
         if (threadIdx.x == 0) store_row<T, FUSED>(a, row, sum);
         return;
     }

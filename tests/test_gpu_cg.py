@@ -379,3 +379,18 @@ def test_cg_one_workgroup_solve_at_its_limits(spk, dev, n, half):
         M.release()
     finally:
         H.close()
+
+
+@pytest.mark.parametrize("n", [4353, 131071, 131072, 131073])
+def test_cg_vector_kernels_at_the_chunk_limits(spk, dev, n):
+    """Rows on both sides of the line between one and four accesses per lane
+    of the vector kernels (131,072 on 256 compute units), ragged chunks and
+    the smallest system the three-kernel form takes by itself."""
+    A = _band_spd(n, 2, 43)
+    b, x0 = _vecs(A, 44)
+    xo, ho = O.cg(A, b, 10, x0)
+    say("cg vector kernels", n)
+    M = spk.Matrix(A)
+    x, hist = _run(spk, M, b, x0, 10, dev)
+    _compare(x, hist, xo, ho)
+    M.release()
