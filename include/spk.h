@@ -153,7 +153,8 @@ typedef struct {
  * apply to an operation must be 0.
  *   format  spk_format (SpMV only)
  *   block   threads per workgroup (64..1024, power of two)
- *   group   SpMV VECTOR: lanes per row (2..64); SELL: rows per slice
+ *   group   SpMV VECTOR: lanes per row (2..64), or rows per wavefront (8..64)
+ *           of the row stream (lds > 1); SELL: rows per slice
  *   unroll  independent loads in flight per lane (1, 2, 4 or 8)
  *   vec     vector ops: elements per lane load (1, 2 or 4; at most 16 bytes);
  *           SpMV SCALAR/VECTOR: entries per value/index access (0 = one);
@@ -165,7 +166,8 @@ typedef struct {
  *           grid-stride launch (either way at most 2^30 work-items: past
  *           that the kernels loop over the grid, so any n is covered)
  *   streams SpMV: split rows over this many streams (1, 2 or 4)
- *   lds     SpMV VECTOR: 1 = stage row_ptr in LDS; ADAPTIVE: LDS row-stream
+ *   lds     SpMV VECTOR: 1 = stage row_ptr in LDS, more = stream runs of rows
+ *           through LDS in chunks of that many entries per wavefront; ADAPTIVE: LDS row-stream
  *           capacity in entries per wavefront (the "L1 size" knob; gfx950
  *           has no L1/LDS split, so the staged tile size takes its place);
  *           STENCIL: 1 = stage each workgroup's x values and one grid line

@@ -160,7 +160,6 @@ static int pow2_ceil(double x)
 
 spk_variant default_variant(spk_handle h, const spk_problem &p, const spk_csr *csr)
 {
-    (void)h;
     spk_variant v{};
     switch (p.op) {
     case SPK_OP_WAXPY:
@@ -191,6 +190,21 @@ spk_variant default_variant(spk_handle h, const spk_problem &p, const spk_csr *c
     const double mean = csr && csr->nrows > 0 ? (double)csr->nnz / (double)csr->nrows : 1.0;
     v.format = SPK_FMT_VECTOR;
     v.block = 256;
+    // A borrowed CSR matrix (only its sizes are known): the row stream, with
+    // as many rows per wavefront as make about one 512-entry chunk, but at
+    // least eight wavefronts per compute unit.  64 rows of 7.8 entries take
+    // 14.0 us where 32 take 14.4 (500,000 rows), 32 rows of 19.8 14.1 us where
+    // 64 take 20.1; of 40,000 such rows 32 per wavefront take 9.5 us, 16 take
+    // 7.8.  From about 80 entries a row on, G lanes per row read long runs
+    // anyway (145 entries: 15.1 us against 18.5 with 8 rows a wavefront, 73
+    // entries: 20.0 against 14.4); and below 8,192 rows they give the GPU more
+    // wavefronts.
+    if (mean <= 80.0 && csr && csr->nrows >= 8192) {
+        v.group = 64;
+        while (v.group > 8 && (v.group * mean > 640.0 || csr->nrows < v.group * 8ll * h->num_cu)) v.group /= 2;
+        v.lds = 512;
+        return v;
+    }
     v.group = std::min(64, std::max(2, pow2_ceil(mean)));
     return v;
 }
@@ -416,7 +430,8 @@ spk_status run_spmv(spk_handle h, const SpmvProblem &p, const spk_variant &v, hi
     // launch would exceed kMaxLaunchItems work-items (e.g. a wavefront per
     // row over more than 2^24 rows) is run as consecutive launches.
     const int64_t unit = v.format == SPK_FMT_ADAPTIVE ? v.block / 64
-                         : v.format == SPK_FMT_VECTOR ? v.block / v.group : v.block;
+                         : v.format != SPK_FMT_VECTOR ? v.block
+                         : v.lds > 1 ? v.block / 64 * v.group : v.block / v.group;
     // (ADAPTIVE launches also hold a workgroup per long row of the range: half
     // the work-items are kept for those.)
     const int64_t span = kMaxLaunchItems / v.block / (v.format == SPK_FMT_ADAPTIVE ? 2 : 1) * unit;

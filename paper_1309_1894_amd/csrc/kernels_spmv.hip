@@ -6,7 +6,9 @@
 //   VECTOR   G lanes per row (G = 2..64; 64 is one wavefront per row): the
 //            lanes of a group stride the row with coalesced loads and meet
 //            in a DPP/ds_swizzle group reduction.  Optionally stages the
-//            workgroup's row_ptr slice in LDS.
+//            workgroup's row_ptr slice in LDS; or streams runs of rows
+//            through LDS (`lds` > 1: chunks of `lds` entries, `group` rows
+//            per wavefront).
 //   SELL     sliced ELL: slices of C rows stored column-major, one lane per
 //            row, fully coalesced, no reduction; rows keep their own length
 //            so padding is never read.
@@ -146,6 +148,83 @@ __global__ __launch_bounds__(BS) void k_spmv_vector(SpmvArgs<T> a)
     for (int u = 1; u < UNR; ++u) sum += acc[u];
     sum = group_sum<G>(sum);  // every lane of the wavefront takes part
     if (lane == 0 && row < rend) store_row<T, FUSED>(a, row, sum);
+}
+
+// --------------------------------------------------- VECTOR, row stream --
+
+// R consecutive rows per wavefront on the plain CSR arrays (no tiles made
+// beforehand): their entries are streamed in chunks of E with coalesced loads,
+// the products go to the wavefront's LDS slice, and G = 64/R lanes add each
+// row's part of the chunk; a row with more than 32*G entries in a chunk is
+// added by all 64 lanes.  ROWSNUM
+template <typename T, int BS, int R, int E, bool FUSED>
+__global__ __launch_bounds__(BS) void k_spmv_rows(SpmvArgs<T> a)
+{
+    constexpr int NW = BS / kWave;
+    constexpr int G = kWave / R;
+    constexpr int ITEMS = E / kWave;
+    __shared__ double stage[NW * E];
+    const int l = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int rend = a.row0 + a.m;
+    const int r0 = a.row0 + (xcd_remap((int)blockIdx.x, (int)gridDim.x) * NW + wv) * R;
+    if (r0 >= rend) return;
+    const int nr = min(R, rend - r0);
+    const gptr<int32_t> rp = as_global(a.rp), ci = as_global(a.ci);
+    const gptr<T> val = as_global(a.val), x = as_global(a.x);
+    double *sp = stage + wv * E;
+    const int row = l / G, sub = l & (G - 1);
+    int s = rp[r0 + min(row, nr)], e = rp[r0 + min(row + 1, nr)];   // empty past the last row
+    T xo = T(0);
+    if constexpr (FUSED) xo = x[r0 + min(row, nr - 1)];
+    const int k0 = __builtin_amdgcn_readlane(s, 0);
+    const int k1 = __builtin_amdgcn_readlane(e, kWave - 1);
+    double acc = 0.0;
+    for (int64_t kb64 = k0; kb64 < k1; kb64 += E) {
+        const int kb = (int)kb64;
+        const int last = k1 - 1 - kb;      // last entry of the rows, from the chunk's first
+        int c[ITEMS];
+        T v[ITEMS];
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j)
+            if (j * kWave <= last) {
+                const int k = min(l + j * kWave, last);
+                c[j] = __builtin_nontemporal_load(ci + kb + k);
+                v[j] = __builtin_nontemporal_load(val + kb + k);
+            }
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j)
+            if (j * kWave <= last) sp[l + j * kWave] = (double)v[j] * (double)x[c[j]];
+        wave_lds_sync();
+        const int lo = max(s - kb, 0), hi = min(e - kb, E);
+        unsigned long long wide = __ballot(hi - lo > 32 * G && sub == 0);
+        if (hi - lo <= 32 * G) {
+            double a0 = 0.0, a1 = 0.0;
+            int k = lo + sub;
+            for (; k + G < hi; k += 2 * G) {
+                a0 += sp[k];
+                a1 += sp[k + G];
+            }
+            if (k < hi) a0 += sp[k];
+            acc += a0 + a1;
+        }
+        while (wide) {
+            const int src = __builtin_ctzll(wide);
+            wide &= wide - 1;
+            const int wlo = __builtin_amdgcn_readlane(lo, src), whi = __builtin_amdgcn_readlane(hi, src);
+            double t = 0.0;
+            for (int k = wlo + l; k < whi; k += kWave) t += sp[k];
+            t = group_sum<kWave>(t);
+            if (l == src) acc += t;
+        }
+        wave_lds_sync();
+    }
+    acc = group_sum<G>(acc);
+    if (sub == 0 && row < nr) {
+        const T yt = (T)acc;
+        __builtin_nontemporal_store(yt, as_global_mut(a.y) + r0 + row);
+        if constexpr (FUSED) __builtin_nontemporal_store(fma_t(a.alpha, yt, xo), as_global_mut(a.w) + r0 + row);
+    }
 }
 
 // ----------------------------------------------------------------- SELL --
@@ -335,6 +414,13 @@ hipError_t L_vector(const void *p, dim3 g, hipStream_t s)
     return hipGetLastError();
 }
 
+template <typename T, int BS, int R, int E, bool F>
+hipError_t L_rows(const void *p, dim3 g, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_spmv_rows<T, BS, R, E, F>), g, dim3(BS), 0, s, *(const SpmvArgs<T> *)p);
+    return hipGetLastError();
+}
+
 template <typename T, int BS, int C, int UNR, bool F>
 hipError_t L_sell(const void *p, dim3 g, hipStream_t s)
 {
@@ -358,6 +444,8 @@ hipError_t L_adaptive(const void *p, dim3 g, hipStream_t s)
 #define VECTOR(BS, G, U) {2, BS, G, U, 0, FN4(L_vector, BS, G, U, false, 1)}
 #define VECTOR_V(BS, G, U, V) {2, BS, G, U, 0, FN4(L_vector, BS, G, U, false, V), V}
 #define VECTOR_LDS(BS, G) {2, BS, G, 1, 1, FN4(L_vector, BS, G, 1, true, 1)}
+// row stream: `group` rows per wavefront, chunks of `lds` entries
+#define ROWS(BS, R, E) {2, BS, R, 1, E, FN4(L_rows, BS, R, E)}
 #define SELL(C, U) {3, 256, C, U, 0, FN4(L_sell, 256, C, U)}
 // lds = row-stream entries per wavefront tile; group = LDS room for x per
 // wavefront (1 = none)
@@ -397,6 +485,8 @@ const SpmvEntry kSpmv[] = {
     SCALAR_V(256, 2), SCALAR_V(256, 4),
     VECTOR_V(256, 4, 2, 2), VECTOR_V(256, 8, 2, 2), VECTOR_V(256, 16, 2, 2), VECTOR_V(256, 32, 2, 2),
     VECTOR_V(256, 64, 2, 2), VECTOR_V(256, 8, 4, 4), VECTOR_V(256, 16, 4, 4), VECTOR_V(256, 64, 4, 4),
+    // row stream on the plain arrays
+    ROWS(256, 8, 512), ROWS(256, 16, 512), ROWS(256, 32, 512), ROWS(256, 64, 512),
     // row blocks with two-byte columns
     ADAPT_C16(64, 256), ADAPT_C16(64, 512), ADAPT_C16(64, 1024), ADAPT_C16(128, 256), ADAPT_C16(128, 512),
     ADAPT_C16(256, 256), ADAPT_C16(256, 512), ADAPT_C16(512, 256),

@@ -130,7 +130,7 @@ void candidate_space(const Ctx &c, uint32_t formats, std::vector<spk_variant> &o
                 continue;
             }
             // lane groups far wider than the longest row only idle
-            if (v.format == SPK_FMT_VECTOR && v.group > 2 && (int64_t)v.group > 8 * std::max<int64_t>(1, A->max_len)) {
+            if (v.format == SPK_FMT_VECTOR && v.lds <= 1 && v.group > 2 && (int64_t)v.group > 8 * std::max<int64_t>(1, A->max_len)) {
                 ++*pruned;
                 continue;
             }

@@ -456,3 +456,31 @@ def test_row_tiles_at_the_length_limits(spk, dev, dt):
                 assert np.array_equal(w.cpu().numpy(), (0.5 * ref + x).astype(NP[dt])), v
     finally:
         M.release()
+
+
+@pytest.mark.parametrize("dt", [1, 0])
+@pytest.mark.parametrize("m,mean", [(8191, 20), (8192, 20), (8193, 79), (8200, 82), (20001, 5), (70001, 9), (70001, 11),
+                                    (140001, 9), (140001, 0)])
+def test_borrowed_csr_default_on_both_sides_of_its_rules(spk, dev, m, mean, dt):
+    """spk_spmv_csr's default kernel around its limits (rows, mean length),
+    ragged last wavefronts, empty rows, rows longer than a chunk and rows that
+    end exactly at one.  Integer data: exact, compared bit for bit."""
+    rng = np.random.default_rng(m + mean)
+    lens = rng.integers(0, 2 * mean + 1, m)
+    lens[[0, m // 2, m - 1]] = [2000, 512, 1500]
+    lens[1:4] = 0
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    A = I.CSR(m, 4099, rp, rng.integers(0, 4099, rp[-1]).astype(np.int32), rng.integers(-8, 9, rp[-1]).astype(NP[dt]))
+    x = rng.integers(-8, 9, 4099).astype(NP[dt])
+    ref, _ = O.spmv(A, x)
+    say(f"borrowed csr m={m} mean={mean} dtype={dt}")
+    d = [torch.from_numpy(v).to(dev) for v in (A.row_ptr, A.col_idx, A.val, x)]
+    y = torch.full((m + 64,), float("nan"), dtype=d[3].dtype, device=dev)
+    spk.spk_spmv_csr(*d, y[:m])
+    got = y.cpu().numpy()
+    assert np.array_equal(got[:m], ref.astype(NP[dt])) and np.all(np.isnan(got[m:]))
+    # arrays that are only element-aligned
+    o = [torch.cat([t[:1], t])[1:] for t in d[1:3]]
+    y.fill_(float("nan"))
+    spk.spk_spmv_csr(d[0], o[0], o[1], d[3], y[:m])
+    assert np.array_equal(y.cpu().numpy()[:m], ref.astype(NP[dt]))
