@@ -210,11 +210,12 @@ namespace spk {
 
 // Makes the handle's device current for the scope.
 struct DeviceGuard {
-    int prev = -1;
+    int prev = -1;   // device to return to, -1 = none
     explicit DeviceGuard(spk_handle h)
     {
         if (hipGetDevice(&prev) != hipSuccess) prev = -1;
-        if (prev != h->device) (void)hipSetDevice(h->device);
+        if (prev == h->device) prev = -1;
+        else (void)hipSetDevice(h->device);
     }
     ~DeviceGuard()
     {

@@ -213,9 +213,17 @@ def _need(t, n: int, name: str):
 
 
 def _stream(stream=None):
+    """hipStream_t of ``stream``, or of torch's current stream on the current
+    device.  The latter is asked of torch's C layer where it offers the raw
+    handle: torch.cuda.current_stream() builds a Stream object for it, 2.9 us
+    of a call that takes 7.2 us in all (the launch itself 3.2)."""
     if stream is not None:
         return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
-    return _torch().cuda.current_stream().cuda_stream
+    torch = _torch()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch._C._cuda_getDevice())
 
 
 class Handle:
