@@ -252,11 +252,11 @@ spk_status spk_dot(spk_handle h, int32_t dtype, int64_t n, const void *x, const 
 /* spk_dot for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same arguments, kernels, variant and result bits as spk_dot, but the
- * partial sums and the ticket live in a fixed per-GPU array of the library
- * (65,536 partials, 512 KiB plus one 256-byte line, held by each GPU the
+ * partial sums and the tickets live in a fixed per-GPU array of the library
+ * (65,536 partials, 512 KiB, plus 6 KiB of tickets, held by each GPU the
  * library runs on until the process ends) instead of scratch the handle
  * allocates; the call allocates nothing, launches a small kernel that zeroes
- * the ticket, then the dot.  A dot whose variant needs more than 65,536
+ * the tickets, then the dot.  A dot whose variant needs more than 65,536
  * workgroups (only the one-pass plain variant, above 16.7M elements) is
  * rejected with SPK_ERR_SHAPE.  Every call on a GPU, from any handle or
  * stream, shares that GPU's array: calls that overlap on one GPU race and

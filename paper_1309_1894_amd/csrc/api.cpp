@@ -286,8 +286,8 @@ static spk_status dot_scratch(spk_handle h, hipStream_t s, int64_t need, DotScra
         }
         const int64_t cap = std::max<int64_t>(need, 4096);
         SPK_HIP(hipMalloc(&d.partial, (size_t)cap * sizeof(double)));
-        SPK_HIP(hipMalloc(&d.ticket, 256));
-        SPK_HIP(hipMemsetAsync(d.ticket, 0, 256, s));
+        SPK_HIP(hipMalloc(&d.ticket, sizeof(uint32_t) * kDotTicketWords));
+        SPK_HIP(hipMemsetAsync(d.ticket, 0, sizeof(uint32_t) * kDotTicketWords, s));
         d.cap = cap;
     }
     *out = &d;
@@ -339,12 +339,12 @@ spk_status run_dot(spk_handle h, int dtype, int64_t n, const void *x, const void
 }
 
 // Scratch of spk_dot_noalloc, one copy per GPU for the life of the process:
-// kNoAllocPartials workgroup partials, then one 256-byte line whose first
-// word is the dot's ticket.  Host code reaches it only through the address
-// spk_create stores in the handle (hipGetSymbolAddress on the handle's
-// device); the array's name in host code is not a device address.
+// kNoAllocPartials workgroup partials, then the dot's tickets.  Host code
+// reaches it only through the address spk_create stores in the handle
+// (hipGetSymbolAddress on the handle's device); the array's name in host code
+// is not a device address.
 constexpr int64_t kNoAllocPartials = 65536;
-static __device__ __align__(256) double scratch[kNoAllocPartials + 32];
+static __device__ __align__(256) double scratch[kNoAllocPartials + kDotTicketWords / 2];
 
 // ----------------------------------------------------------------- SpMV --
 
@@ -1093,10 +1093,10 @@ spk_status spk_dot_noalloc(spk_handle h, int32_t dtype, int64_t n, const void *x
     hipStream_t s = (hipStream_t)stream;
     uint32_t *ticket = nullptr;
     if (g <= kDotTicketMaxGrid) {
-        // the array keeps the last call's contents: the ticket starts at zero
+        // the array keeps the last call's contents: the tickets start at zero
         // (a kernel, not a memset node, so the call can be captured)
         ticket = (uint32_t *)(h->noalloc_scratch + kNoAllocPartials);
-        SPK_HIP(launch_zero_u32(ticket, 1, s));
+        SPK_HIP(launch_zero_u32(ticket, kDotTicketWords, s));
     }
     return dot_launch(e, dtype, n, x, y, d_result, g, h->noalloc_scratch, ticket, s);
 }

@@ -22,7 +22,7 @@ struct VecLaunch {
     const void *y;
     void *w;             // WAXPY/AXPY output
     double *partial;     // DOT: one double per workgroup
-    uint32_t *ticket;    // DOT: zero on entry, left zero on exit; null = partials
+    uint32_t *ticket;    // DOT: kDotTicketWords words, zero on entry, left zero on exit; null = partials
                          // only (finished by launch_dot_final)
     double *out;         // DOT: result
     int64_t grid;        // workgroups to launch
@@ -47,10 +47,15 @@ hipError_t launch_dot_final(const double *partial, int64_t count, double *out, h
 hipError_t launch_colblock_sum(int nblk, int64_t m, const double *part, double *y, double *w, const double *x,
                                double alpha, hipStream_t s);
 
-// Largest dot grid finished by the ticket (each workgroup then publishes
-// its partial with a device-scope release, which writes back the XCD's L2
-// and serialises there); larger grids use launch_dot_final.
-constexpr int64_t kDotTicketMaxGrid = 16;
+// Largest dot grid finished by the tickets (489 workgroups, n = 1,000,003
+// FP64: 7.5-7.8 us a call against 9.0-10.5 with the second launch; 1,465,
+// n = 3e6: 10.7 and 11.2; 2,048, n = 5e7 FP32: 64.0 and 61.5, so there the
+// launch is the cheaper end).  One ticket per kDotGroup workgroups and one for
+// the groups (the first), kDotTicketStride words apart.
+constexpr int kDotGroup = 32;
+constexpr int kDotTicketStride = 32;
+constexpr int64_t kDotTicketMaxGrid = 1536;
+constexpr int64_t kDotTicketWords = (1 + kDotTicketMaxGrid / kDotGroup) * kDotTicketStride;
 
 // Elements covered by one workgroup in one pass.
 inline int64_t vec_per_block(const VecEntry &e) { return (int64_t)e.block * e.vec * e.unroll; }
