@@ -72,24 +72,23 @@ struct ColBlockData {
 };
 
 // SPK_FMT_XWIN (see kernels.h, XwinArgs): the entries regrouped by column
-// window, built on first use for one window size; the wavefront tiles and
-// chunks of each (entries per wavefront, chunks per compute unit); the FP64
-// partials, one per (row, window) pair, per stream.
+// window, built on first use for one window size; the chunks and wavefront
+// ranges of each (threads, chunks per compute unit); the FP64 partials, one
+// per (row, window) pair, per stream.
 struct XwinPlan {
-    uint32_t *tiles = nullptr;      // ntiles + 1
-    int32_t *tile_k = nullptr;      // ntiles + 1
-    int32_t *chunk_t = nullptr;     // nchunk + 1
+    int32_t *wave_p = nullptr;      // nchunk * wavefronts + 1: first pair of each wavefront's range
+    int32_t *wave_k = nullptr;      // the same: its first entry
+    int32_t *wave_c = nullptr;      // nchunk * wavefronts: pairs starting before the range's first tile
     int32_t *chunk_w = nullptr;     // nchunk
-    int32_t ntiles = 0, nchunk = 0;
+    int32_t nchunk = 0;
     int64_t bytes = 0;
 };
 
 struct XwinData {
     int64_t wc = 0;                 // window columns
     int64_t nwin = 0, npairs = 0;
-    uint16_t *ci = nullptr;         // nnz, column inside the window
-    void *val = nullptr;            // nnz, window-major
-    int32_t *ent = nullptr;         // npairs + 1
+    uint16_t *ci = nullptr;         // nnz (and slack), column inside the window | pair start << 15
+    void *val = nullptr;            // nnz (and slack), window-major
     int32_t *pos_ptr = nullptr;     // nrows + 1: row i's pairs are [pos_ptr[i], pos_ptr[i+1]) in window order
     uint16_t *rowpos = nullptr;     // npairs: each staged partial's place in its row block's row order
     int32_t *first = nullptr;       // nblk * nwin: first pair of each window's run in each row block
@@ -97,7 +96,7 @@ struct XwinData {
     int64_t rb = 0, nblk = 0;       // rows per block of the second pass, blocks
     std::vector<int32_t> ent_host;
     std::vector<int64_t> pair_off;  // nwin + 1: first pair of each window
-    std::map<std::pair<int, int>, XwinPlan> plans;
+    std::map<std::pair<int, int>, XwinPlan> plans;   // by (threads, chunks per compute unit)
     std::map<hipStream_t, double *> part;
     int64_t bytes = 0;
 };

@@ -106,18 +106,21 @@ const SpmvEntry *spmv_table(int *count);
 // blocks of the LDS-staged kernel, and their first entries); chunk c is the
 // tiles [chunk_t[c], chunk_t[c+1]) of window chunk_w[c], one workgroup each.
 struct XwinArgs {
-    const uint32_t *tiles;     // ntiles + 1
-    const int32_t *tile_k;     // ntiles + 1
-    const int32_t *chunk_t;    // nchunk + 1
+    const int32_t *wave_p;     // nchunk * wavefronts + 1: first pair of each wavefront's range
+    const int32_t *wave_k;     // the same: its first entry
+    const int32_t *wave_c;     // nchunk * wavefronts: pairs that start before the range's first tile
     const int32_t *chunk_w;    // nchunk
-    const int32_t *ent;        // npairs + 1
-    const uint16_t *ci;        // nnz
-    const void *val;           // T[nnz]
+    const uint16_t *ci;        // nnz + kXwinSlack: column in the window | pair start << 15
+    const void *val;           // T[nnz + kXwinSlack]
     const void *x;             // T[n]
     int64_t n;
     double *part;              // npairs FP64 partial sums
     int32_t nchunk;
 };
+
+// Entries after the last that a wavefront's last tile may read (marked, of
+// value zero): tiles hold at most 256.
+constexpr int64_t kXwinSlack = 512;
 
 using XwinFn = hipError_t (*)(const XwinArgs &a, hipStream_t s);
 

@@ -8,13 +8,14 @@
 // live in a compute unit's LDS.  At conversion the entries are regrouped
 // window by window: a (row, window) pair holds the row's entries whose
 // columns fall in the window, in their original order, with 16-bit column
-// indices inside the window.  The first pass runs one workgroup per chunk of
-// one window's pairs: it copies that window of x into LDS once, then its
-// wavefronts stream the pairs' values and indices with coalesced loads,
-// take x from LDS and write one FP64 partial per pair.  A second pass adds
-// each row's partials in window order (and forms w = alpha*y + x when
-// fused).  Every byte of the first pass is a coalesced stream; the gathers
-// never leave the compute unit.
+// words: 15 bits of column inside the window and the top bit on a pair's
+// first entry.  The first pass runs one workgroup per chunk of one window's
+// pairs: it copies that window of x into LDS once, then its wavefronts
+// stream the chunk's values and column words with coalesced loads, take x
+// from LDS, sum between the marks and write one FP64 partial per pair.  A
+// second pass adds each row's partials in window order (and forms
+// w = alpha*y + x when fused).  Every byte of the first pass is a coalesced
+// stream; the gathers never leave the compute unit.
 #include "device_common.h"
 #include "device_rows.h"
 #include "kernels.h"
@@ -24,143 +25,191 @@ namespace spk {
 
 namespace {
 
-// One wavefront tile: pairs [p0, p1) with entries [k0, k1); a row-stream
-// tile (k1 - k0 <= 64*ITEMS, p1 - p0 <= 128) carries its lanes' indices,
-// values and pair starts, loaded ahead of its processing.
+// A tile is 64*ITEMS consecutive entries of a wavefront's range, lane l
+// holding ITEMS consecutive ones: its values in 16-byte loads, its column
+// words in one load.
 template <typename T, int ITEMS>
 struct WinTile {
-    int p0, p1, k0, k1;
-    bool stream;
-    uint16_t c[ITEMS];
     T v[ITEMS];
-    int rpv[3];
+    uint32_t c[ITEMS / 2];   // two column words each
 };
 
-// Takes a tile's record (start pair | mode << 30, first entry, and the
-// next tile's) and issues the loads of its first 64*ITEMS entries and of
-// its pair starts, whatever the tile's mode (a tile holds at least one pair
-// and every pair at least one entry, so these stay inside the tile; lanes
-// past its end load its last entry again and drop it).  Loading
-// unconditionally keeps the pipeline's load counts fixed.
 template <typename T, int ITEMS>
-__device__ __forceinline__ void window_load(const XwinArgs &a, uint32_t e0, uint32_t e1, int k0, int k1,
-                                            WinTile<T, ITEMS> &tl)
+__device__ __forceinline__ void window_load(const XwinArgs &a, int64_t k, WinTile<T, ITEMS> &tl)
 {
-    tl.p0 = (int)(e0 & kBlkRowMask);
-    tl.p1 = (int)(e1 & kBlkRowMask);
-    tl.k0 = k0;
-    tl.k1 = k1;
-    tl.stream = (e0 >> 30) == kBlkStream;
-    const gptr<int32_t> ent = as_global(a.ent);
-    const gptr<uint16_t> ci = as_global(a.ci);
-    const gptr<T> val = as_global((const T *)a.val);
-    const int l = threadIdx.x & (kWave - 1);
-    const int np = tl.p1 - tl.p0, klast = tl.k1 - tl.k0 - 1;
+    constexpr int VN = 16 / (int)sizeof(T) < ITEMS ? 16 / (int)sizeof(T) : ITEMS;   // values per load
+    typedef T vv __attribute__((ext_vector_type(VN)));
+    typedef uint32_t vc __attribute__((ext_vector_type(ITEMS / 2)));
+    const vc c = __builtin_nontemporal_load((gptr<vc>)(as_global(a.ci) + k));
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) tl.c[j] = __builtin_nontemporal_load(ci + tl.k0 + min(l + j * kWave, klast));
+    for (int j = 0; j < ITEMS; j += VN) {
+        const vv t = *(gptr<vv>)(as_global((const T *)a.val) + k + j);
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) tl.v[j] = __builtin_nontemporal_load(val + tl.k0 + min(l + j * kWave, klast));
-    // raw pair starts: k0 is taken off where they are used, so that no
-    // arithmetic here has to wait for the loads
+        for (int u = 0; u < VN; ++u) tl.v[j + u] = t[u];
+    }
+    if constexpr (ITEMS == 2) {
+        tl.c[0] = *(const uint32_t *)&c;
+    } else {
 #pragma unroll
-    for (int q = 0; q < 3; ++q) tl.rpv[q] = ent[tl.p0 + min(l + q * kWave, np)];
+        for (int j = 0; j < ITEMS / 2; ++j) tl.c[j] = c[j];
+    }
 }
 
-// Row-stream tile: products (x from the window in LDS) to the wavefront's
-// LDS slice sp, then one lane per pair adds that pair's products (four
-// interleaved partial sums) and writes its partial.
-template <typename T, int ITEMS>
-__device__ __forceinline__ void window_stream(const XwinArgs &a, const T *win, const WinTile<T, ITEMS> &tl,
-                                              double *sp, int *srp)
+// Inclusive sums over lanes back to the nearest marked lane: lane l gets
+// v(m) + ... + v(l), m the last lane <= l with a mark, dist = l - m (or
+// anything over l if there is none, for the sum from lane 0).  Shifts inside
+// rows of 16 lanes, then the rows' last lanes to the rows above.
+constexpr int kDppRowShr = 0x110;       // + distance: lane l reads lane l - distance of its row
+constexpr int kDppRowBcast15 = 0x142;   // the last lane of each row to the next row
+constexpr int kDppRowBcast31 = 0x143;   // lane 31 to the rows above
+constexpr int kDppWaveShr1 = 0x138;     // lane l reads lane l - 1
+
+__device__ __forceinline__ double marked_scan(double v, int dist, int l)
 {
-    const gptr_mut<double> part = as_global_mut(a.part);
+    double t;
+    t = dpp_f64<kDppRowShr + 1>(v);
+    v += dist >= 1 ? t : 0.0;
+    t = dpp_f64<kDppRowShr + 2>(v);
+    v += dist >= 2 ? t : 0.0;
+    t = dpp_f64<kDppRowShr + 4>(v);
+    v += dist >= 4 ? t : 0.0;
+    t = dpp_f64<kDppRowShr + 8>(v);
+    v += dist >= 8 ? t : 0.0;
+    t = dpp_f64<kDppRowBcast15>(v);
+    v += (l & 16) && dist > (l & 15) ? t : 0.0;
+    t = dpp_f64<kDppRowBcast31>(v);
+    v += (l & 32) && dist > (l & 31) ? t : 0.0;
+    return v;
+}
+
+// One wavefront's walk over its entries: the pair open where the next tile
+// begins has the sum `carry` so far; the slice holds `held` closed sums, of the
+// pairs from `from` on; the next tile first closes `skip` pairs that are not
+// the wavefront's (only a range's first tile does).
+struct WinWalk {
+    double carry;
+    int held, from, skip;
+};
+
+// Writes the held sums of the pairs before `end` and moves the rest to the
+// slice's front.
+template <int ITEMS>
+__device__ __forceinline__ void window_flush(const XwinArgs &a, double *sp, int end, WinWalk &wk)
+{
     const int l = threadIdx.x & (kWave - 1);
-    const int np = tl.p1 - tl.p0;
-    // stores without branches where the slice has room: products of lanes
-    // past the tile's end (loaded from the clamped last entry) and pair
-    // starts past np land in slots no pair sum reads
+    const int count = end - wk.from;
+    if (count <= 0) return;
+    const gptr_mut<double> part = as_global_mut(a.part) + wk.from;
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) sp[l + j * kWave] = (double)tl.v[j] * (double)win[tl.c[j]];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) srp[l + q * kWave] = tl.rpv[q] - tl.k0;
-    if (l + 2 * kWave <= np) srp[l + 2 * kWave] = tl.rpv[2] - tl.k0;
+    for (int q = 0; q <= ITEMS; ++q)
+        if (q * kWave < count && l + q * kWave < count) part[l + q * kWave] = sp[l + q * kWave];
+    const double rest = sp[min(count + l, kWave * (ITEMS + 1) - 1)];
     wave_lds_sync();
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int i = l + q * kWave;
-        if (i < np) {
-            const int s = srp[i], e = srp[i + 1];
-            double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-            int k = s;
-            for (; k + 3 < e; k += 4) {
-                a0 += sp[k];
-                a1 += sp[k + 1];
-                a2 += sp[k + 2];
-                a3 += sp[k + 3];
-            }
-            if (k < e) a0 += sp[k];
-            if (k + 1 < e) a1 += sp[k + 1];
-            if (k + 2 < e) a2 += sp[k + 2];
-            __builtin_nontemporal_store((a0 + a1) + (a2 + a3), part + tl.p0 + i);
-        }
-    }
-    wave_lds_sync();   // the slice is free again for the next tile
+    sp[l] = rest;
+    wave_lds_sync();
+    wk.held -= count;
+    wk.from = end;
 }
 
-// Pairs [p0, p1) one after another, all 64 lanes on each: UNR loads per lane
-// in flight, UNR partial sums combined in a fixed order, then the wavefront
-// sum.
-template <typename T, int UNR>
-__device__ __forceinline__ void window_pairs(const XwinArgs &a, const T *win, int p0, int p1)
+// Sums one tile between its marks.  A pair that ends in the tile is closed by
+// the lane that holds the next mark: its own entries before the mark plus
+// what the lanes below hold of the pair (one scan over the lanes), so pairs
+// may be of any length and start anywhere.  The closed sums collect in the
+// wavefront's LDS slice sp and leave in whole aligned groups of 64, so that
+// every line of partials is written once; those of pairs past p1 (entries of
+// the next range in the last tile) are dropped.
+template <typename T, int ITEMS>
+__device__ __forceinline__ void window_tile(const XwinArgs &a, const T *win, const WinTile<T, ITEMS> &tl, double *sp,
+                                            int p1, WinWalk &wk)
 {
-    const gptr<int32_t> ent = as_global(a.ent);
-    const gptr<uint16_t> ci = as_global(a.ci);
-    const gptr<T> val = as_global((const T *)a.val);
     const int l = threadIdx.x & (kWave - 1);
-    for (int p = p0; p < p1; ++p) {
-        const int s = ent[p], e = ent[p + 1];
-        double acc[UNR];
+    double run[ITEMS];      // sums since the last mark inside the lane
+    bool mark[ITEMS];
+    unsigned long long any = 0;
+    int below = 0, total = 0;   // marks in lower lanes, in the tile
 #pragma unroll
-        for (int j = 0; j < UNR; ++j) acc[j] = 0.0;
-        for (int base = s; base < e; base += kWave * UNR) {
-            uint16_t c[UNR];
-            T v[UNR];
-#pragma unroll
-            for (int j = 0; j < UNR; ++j) {
-                const int k = min(base + l + j * kWave, e - 1);
-                c[j] = __builtin_nontemporal_load(ci + k);
-                v[j] = __builtin_nontemporal_load(val + k);
-            }
-#pragma unroll
-            for (int j = 0; j < UNR; ++j)
-                if (base + l + j * kWave < e) acc[j] = fma_t((double)v[j], (double)win[c[j]], acc[j]);
-        }
-#pragma unroll
-        for (int d = 1; d < UNR; d *= 2)
-#pragma unroll
-            for (int j = 0; j + d < UNR; j += 2 * d) acc[j] += acc[j + d];
-        const double sum = group_sum<kWave>(acc[0]);
-        if (l == 0) a.part[p] = sum;
+    for (int j = 0; j < ITEMS; ++j) {
+        const uint32_t c = tl.c[j / 2] >> (16 * (j & 1));
+        mark[j] = (c & 0x8000u) != 0;
+        const double x = (double)win[c & 0x7fffu];
+        run[j] = fma_t((double)tl.v[j], x, mark[j] || j == 0 ? 0.0 : run[j > 0 ? j - 1 : 0]);
+        const unsigned long long m = __ballot(mark[j]);
+        any |= m;
+        total += __builtin_popcountll(m);
+        below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, below));
     }
+    // the nearest lane at or below this one that holds a mark
+    const unsigned long long upto = any & (~0ull >> (kWave - 1 - l));
+    const int dist = upto ? l - (kWave - 1 - __builtin_clzll(upto)) : kWave;
+    const double s = marked_scan(run[ITEMS - 1], dist, l);
+    double open = dpp_f64<kDppWaveShr1>(s);   // of the pair open where the lane begins
+    if (below == 0) open += wk.carry;
+    const double end = readlane_f64(s, kWave - 1);
+    wk.carry = any ? end : wk.carry + end;
+    int at = wk.held + below - wk.skip;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        if (mark[j]) {
+            if (at >= 0) sp[at] = open + (j > 0 ? run[j > 0 ? j - 1 : 0] : 0.0);
+            open = 0.0;
+            ++at;
+        }
+    }
+    wave_lds_sync();
+    wk.held = min(wk.held + total - wk.skip, p1 - wk.from);
+    wk.skip = 0;
+    window_flush<ITEMS>(a, sp, (wk.from + wk.held) & ~(kWave - 1), wk);
 }
 
 }  // namespace
 
-// First pass: workgroup c runs chunk c, tiles [chunk_t[c], chunk_t[c+1]) of
-// window chunk_w[c]; wavefront v takes tiles v, v + NW, ...  The window's
-// x values (WB bytes at most) are copied to LDS once, eight loads in flight
-// per lane.
-constexpr int kRing = 4;   // tiles in the window pass's software pipeline
+// First pass: workgroup c runs chunk c, pairs of window chunk_w[c]; its
+// wavefront v runs pairs [wave_p[i], wave_p[i+1]), i = c*NW + v, whose entries
+// start at wave_k[i] (the next wavefront's start ends them).  Tiles lie on
+// multiples of ITEMS entries from the range's start rounded down, so a range's
+// first tile may begin with up to three entries before it: wave_c[i] counts
+// the pairs that start before the tile.  The window's x values (WB bytes at
+// most) are copied to LDS once, eight loads in flight per lane, while the
+// first tiles are on their way.
+// What bounds it is the memory system, not the sums: without its stores it
+// takes 39 us, without the gathers or the scan the same as with them.  On the
+// 1,000,000-row Zipf matrix (16.2 M entries, 5.4 M pairs, 768 threads) it takes
+// 46 us where one lane per pair, walking products staged in LDS between pair
+// starts read from memory, took 63 us: 16.2 us of the difference are the
+// partials (written as each tile's run they cost 16 us, in whole aligned
+// groups 7) and the pair starts no longer read; values loaded without the
+// non-temporal hint (a lane's 32 bytes are two loads of the same lines) give
+// 3 us, two tiles in flight rather than four 4 us, and an XCD taking
+// neighbouring chunks 2 us.
+constexpr int kRing = 2;   // tiles in flight per wavefront
 
 template <typename T, int BS, int WB, int E>
 __global__ __launch_bounds__(BS) void k_xwin(XwinArgs a)
 {
     constexpr int NW = BS / kWave;
     constexpr int WC = WB / (int)sizeof(T);
+    constexpr int ITEMS = E / kWave;
     __shared__ T win[WC];
-    __shared__ double sp[NW * E];
-    __shared__ int srp[NW * (kWaveTileRows + 1)];
-    const int c = (int)blockIdx.x;
+    __shared__ double sp[NW * (E + kWave)];
+    // XCD k runs the k-th eighth of the chunks, so that a window's chunks, which
+    // copy the same x, share an L2
+    const int b = (int)blockIdx.x, xcd = b % kXcds, each = a.nchunk / kXcds, rest = a.nchunk % kXcds;
+    const int c = xcd * each + min(xcd, rest) + b / kXcds;
+    const int l = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int i = c * NW + wv;
+    const int p0 = a.wave_p[i], p1 = a.wave_p[i + 1];
+    const int64_t k0 = a.wave_k[i] & ~3, k1 = a.wave_k[i + 1];
+    const int nt = p0 < p1 ? (int)((k1 - k0 + E - 1) / E) : 0;
+    using Tile = WinTile<T, ITEMS>;
+    // tile t of the range (clamped to the last: the ring's loads are issued
+    // unconditionally)
+    auto load = [&](int t, Tile &tl) {
+        window_load<T, ITEMS>(a, k0 + (int64_t)max(min(t, nt - 1), 0) * E + l * ITEMS, tl);
+    };
+    Tile ring[kRing];
+#pragma unroll
+    for (int r = 0; r < kRing - 1; ++r) load(r, ring[r]);
     const int wnd = a.chunk_w[c];
     const int64_t col0 = (int64_t)wnd * WC;
     const int ncw = (int)min<int64_t>((int64_t)WC, a.n - col0);
@@ -174,70 +223,30 @@ __global__ __launch_bounds__(BS) void k_xwin(XwinArgs a)
         for (int j = 0; j < BATCH; ++j) t[j] = xs[min(i0 + j * BS + (int)threadIdx.x, ncw - 1)];
 #pragma unroll
         for (int j = 0; j < BATCH; ++j) {
-            const int i = i0 + j * BS + (int)threadIdx.x;
-            if (i < ncw) win[i] = t[j];
+            const int at = i0 + j * BS + (int)threadIdx.x;
+            if (at < ncw) win[at] = t[j];
         }
     }
     __syncthreads();
-    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-    const int t1 = a.chunk_t[c + 1];
-    double *my_sp = sp + wv * E;
-    int *my_srp = srp + wv * (kWaveTileRows + 1);
-    // The wavefront's tiles are t0, t0 + NW, ...; their records are read 64
-    // at a time with one vector load per lane (kept in registers and taken
-    // out with readlane, so no scalar load stands between a tile and its
-    // data), then the tiles run as a software pipeline over a ring of
-    // kRing: the loads of the next kRing - 1 tiles are in flight while one
-    // is summed (seven loads per tile: within the 63 a wavefront may have
-    // outstanding; a ring of eight ran slower).
-    using Tile = WinTile<T, E / kWave>;
-    const int l = threadIdx.x & (kWave - 1);
-    const int tw0 = a.chunk_t[c] + wv;
-    const int ntw = tw0 < t1 ? (t1 - tw0 + NW - 1) / NW : 0;
-    for (int bt = 0; bt < ntw; bt += kWave) {
-        const int nb = min(kWave, ntw - bt);
-        uint32_t r0 = 0, r1 = 0;
-        int q0 = 0, q1 = 0;
-        if (l < nb) {
-            const int ti = tw0 + (bt + l) * NW;
-            r0 = a.tiles[ti];
-            r1 = a.tiles[ti + 1];
-            q0 = a.tile_k[ti];
-            q1 = a.tile_k[ti + 1];
-        }
-        // tile i of the batch (clamped to the last: the pipeline's loads
-        // are issued unconditionally)
-        auto load = [&](int i, Tile &tl) {
-            i = min(i, nb - 1);
-            window_load(a, (uint32_t)__builtin_amdgcn_readlane((int)r0, i), (uint32_t)__builtin_amdgcn_readlane((int)r1, i),
-                        __builtin_amdgcn_readlane(q0, i), __builtin_amdgcn_readlane(q1, i), tl);
-        };
-        // row-stream tiles through the pipeline (their processing issues
-        // no loads, so the pipeline's waits stay exact) ...
-        auto run = [&](const Tile &tl) {
-            if (tl.stream) window_stream(a, win, tl, my_sp, my_srp);
-        };
-        // ring slots are indexed by constants once the inner loop is
-        // unrolled, so the ring stays in registers
-        Tile ring[kRing];
+    double *my_sp = sp + wv * (E + kWave);
+    WinWalk wk{0.0, 0, p0, p0 - a.wave_c[i] + 1};
+    // ring slots are indexed by constants once the inner loop is unrolled, so
+    // the ring stays in registers
+    for (int t = 0; t < nt; t += kRing) {
 #pragma unroll
-        for (int r = 0; r < kRing - 1; ++r) load(r, ring[r]);
-        for (int i = 0; i < nb; i += kRing) {
-#pragma unroll
-            for (int r = 0; r < kRing; ++r) {
-                load(i + r + kRing - 1, ring[(r + kRing - 1) % kRing]);
-                if (r == 0 || i + r < nb) run(ring[r]);
-            }
-        }
-        // ... then the tiles of pairs too long for the row stream, one
-        // wavefront per pair
-        for (int i = 0; i < nb; ++i) {
-            const uint32_t e0 = (uint32_t)__builtin_amdgcn_readlane((int)r0, i);
-            if ((e0 >> 30) == kBlkStream) continue;
-            const uint32_t e1 = (uint32_t)__builtin_amdgcn_readlane((int)r1, i);
-            window_pairs<T, 8>(a, win, (int)(e0 & kBlkRowMask), (int)(e1 & kBlkRowMask));
+        for (int r = 0; r < kRing; ++r) {
+            load(t + r + kRing - 1, ring[(r + kRing - 1) % kRing]);
+            if (r == 0 || t + r < nt) window_tile<T, ITEMS>(a, win, ring[r], my_sp, p1, wk);
         }
     }
+    if (nt == 0) return;
+    // the last pair, when no mark followed it in the last tile
+    if (wk.from + wk.held < p1) {
+        if (l == 0) my_sp[wk.held] = wk.carry;
+        ++wk.held;
+        wave_lds_sync();
+    }
+    window_flush<ITEMS>(a, my_sp, p1, wk);
 }
 
 // Second pass: workgroup b reads block b's partials run by run (window w's

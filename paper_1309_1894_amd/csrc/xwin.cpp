@@ -1,6 +1,6 @@
 // xwin.cpp -- host side of SPK_FMT_XWIN (x staged in LDS by column
 // window): the regrouping of a registered matrix's entries into (row,
-// window) pairs, the wavefront tiles and workgroup chunks over them, and
+// window) pairs, the workgroup chunks and wavefront ranges over them, and
 // the two launches of one product.
 #include <algorithm>
 #include <cmath>
@@ -22,20 +22,24 @@ const XwinEntry *find_xwin_entry(int block, int window_kib, int entries)
     return nullptr;
 }
 
+static void free_plan(XwinPlan &pl)
+{
+    (void)hipFree(pl.wave_p);
+    (void)hipFree(pl.wave_k);
+    (void)hipFree(pl.wave_c);
+    (void)hipFree(pl.chunk_w);
+}
+
 void free_xwin(XwinData &d)
 {
     (void)hipFree(d.ci);
     (void)hipFree(d.val);
-    (void)hipFree(d.ent);
     (void)hipFree(d.pos_ptr);
     (void)hipFree(d.rowpos);
     (void)hipFree(d.first);
     (void)hipFree(d.pre);
     for (auto &kv : d.plans) {
-        (void)hipFree(kv.second.tiles);
-        (void)hipFree(kv.second.tile_k);
-        (void)hipFree(kv.second.chunk_t);
-        (void)hipFree(kv.second.chunk_w);
+        free_plan(kv.second);
     }
     for (auto &kv : d.part) (void)hipFree(kv.second);
     d = XwinData();
@@ -75,9 +79,13 @@ spk_status build_xwin(spk_handle h, spk_mat *A, int64_t wc, XwinData &d)
         if (e == hipSuccess && bytes) e = hipMemcpyAsync(*dst, src, bytes, hipMemcpyHostToDevice, h->work);
         return e;
     };
-    hipError_t e = up((void **)&d.ci, hx.ci.data(), sizeof(uint16_t) * nnz);
-    if (e == hipSuccess) e = up(&d.val, hx.val.data(), vs * nnz);
-    if (e == hipSuccess) e = up((void **)&d.ent, hx.ent.data(), sizeof(int32_t) * (d.npairs + 1));
+    // the pairs' starts are marked in the column words; after the last entry,
+    // slack that a tile may read
+    for (int64_t p = 0; p < d.npairs; ++p) hx.ci[hx.ent[p]] |= kXwinMark;
+    hx.ci.resize((size_t)(nnz + kXwinSlack), kXwinMark);
+    hx.val.resize((size_t)(nnz + kXwinSlack) * vs, 0);
+    hipError_t e = up((void **)&d.ci, hx.ci.data(), sizeof(uint16_t) * hx.ci.size());
+    if (e == hipSuccess) e = up(&d.val, hx.val.data(), hx.val.size());
     if (e == hipSuccess) e = up((void **)&d.pos_ptr, hx.pos_ptr.data(), sizeof(int32_t) * (m + 1));
     if (e == hipSuccess) e = up((void **)&d.rowpos, hx.rowpos.data(), sizeof(uint16_t) * d.npairs);
     if (e == hipSuccess) e = up((void **)&d.first, hx.first.data(), sizeof(int32_t) * hx.first.size());
@@ -89,13 +97,14 @@ spk_status build_xwin(spk_handle h, spk_mat *A, int64_t wc, XwinData &d)
     }
     d.ent_host = std::move(hx.ent);
     d.pair_off = std::move(hx.pair_off);
-    d.bytes = (int64_t)((2 + vs) * nnz + 4 * (d.npairs + 1) + 4 * (m + 1) + 2 * d.npairs +
+    d.bytes = (int64_t)((2 + vs) * (nnz + kXwinSlack) + 4 * (m + 1) + 2 * d.npairs +
                         4 * (hx.first.size() + hx.pre.size()));
     return SPK_OK;
 }
 
-// Tiles and chunks of one (entries per wavefront, chunk target), uploaded.
-spk_status build_plan(spk_handle h, const XwinData &d, int E, int64_t target, XwinPlan &pl)
+// Chunks and wavefront ranges of one (wavefronts per workgroup, chunk
+// target), uploaded.
+spk_status build_plan(spk_handle h, const XwinData &d, int E, int nw, int64_t target, XwinPlan &pl)
 {
     XwinHost view;   // the planner reads the pair layout only
     view.nwin = d.nwin;
@@ -103,26 +112,27 @@ spk_status build_plan(spk_handle h, const XwinData &d, int E, int64_t target, Xw
     view.ent = d.ent_host;
     view.pair_off = d.pair_off;
     std::vector<uint32_t> tiles;
-    std::vector<int32_t> tile_k, chunk_t, chunk_w;
+    std::vector<int32_t> tile_k, chunk_t, chunk_w, wave_p, wave_k, wave_c;
     xwin_plan(view, E, target, tiles, tile_k, chunk_t, chunk_w);
-    pl.ntiles = (int32_t)tiles.size() - 1;
+    xwin_waves(view, nw, tiles, chunk_t, wave_p, wave_k, wave_c);
     pl.nchunk = (int32_t)chunk_w.size();
-    auto up = [&](void **dst, const void *src, size_t bytes) -> hipError_t {
+    auto up = [&](void **dst, const std::vector<int32_t> &src) -> hipError_t {
+        const size_t bytes = sizeof(int32_t) * src.size();
         hipError_t e = hipMalloc(dst, std::max<size_t>(bytes, 16));
-        if (e == hipSuccess && bytes) e = hipMemcpyAsync(*dst, src, bytes, hipMemcpyHostToDevice, h->work);
+        if (e == hipSuccess && bytes) e = hipMemcpyAsync(*dst, src.data(), bytes, hipMemcpyHostToDevice, h->work);
         return e;
     };
-    hipError_t e = up((void **)&pl.tiles, tiles.data(), sizeof(uint32_t) * tiles.size());
-    if (e == hipSuccess) e = up((void **)&pl.tile_k, tile_k.data(), sizeof(int32_t) * tile_k.size());
-    if (e == hipSuccess) e = up((void **)&pl.chunk_t, chunk_t.data(), sizeof(int32_t) * chunk_t.size());
-    if (e == hipSuccess) e = up((void **)&pl.chunk_w, chunk_w.data(), sizeof(int32_t) * chunk_w.size());
+    hipError_t e = up((void **)&pl.wave_p, wave_p);
+    if (e == hipSuccess) e = up((void **)&pl.wave_k, wave_k);
+    if (e == hipSuccess) e = up((void **)&pl.wave_c, wave_c);
+    if (e == hipSuccess) e = up((void **)&pl.chunk_w, chunk_w);
     if (e == hipSuccess) e = hipStreamSynchronize(h->work);
     if (e != hipSuccess) return hip_fail(e, "x-window plan upload");
-    pl.bytes = (int64_t)(8 * tiles.size() + 4 * chunk_t.size() + 4 * chunk_w.size());
+    pl.bytes = (int64_t)(4 * (wave_p.size() + wave_k.size() + wave_c.size() + chunk_w.size()));
     return SPK_OK;
 }
 
-spk_status get_xwin(spk_handle h, spk_mat *A, int kib, int E, int grid, XwinData **dout, XwinPlan **pout)
+spk_status get_xwin(spk_handle h, spk_mat *A, int kib, int block, int E, int grid, XwinData **dout, XwinPlan **pout)
 {
     XwinData *d = nullptr;
     {
@@ -143,7 +153,7 @@ spk_status get_xwin(spk_handle h, spk_mat *A, int kib, int E, int grid, XwinData
             d = &A->xwin.emplace(kib, std::move(nd)).first->second;
         }
     }
-    const auto key = std::make_pair(E, grid);
+    const auto key = std::make_pair(block, grid);
     XwinPlan *pl = nullptr;
     {
         std::lock_guard<std::mutex> lk(h->mu);
@@ -152,21 +162,15 @@ spk_status get_xwin(spk_handle h, spk_mat *A, int kib, int E, int grid, XwinData
     }
     if (!pl) {
         XwinPlan np;
-        const spk_status st = build_plan(h, *d, E, (int64_t)grid * h->num_cu, np);
+        const spk_status st = build_plan(h, *d, E, block / 64, (int64_t)grid * h->num_cu, np);
         if (st != SPK_OK) {
-            (void)hipFree(np.tiles);
-            (void)hipFree(np.tile_k);
-            (void)hipFree(np.chunk_t);
-            (void)hipFree(np.chunk_w);
+            free_plan(np);
             return st;
         }
         std::lock_guard<std::mutex> lk(h->mu);
         auto it = d->plans.find(key);
         if (it != d->plans.end()) {
-            (void)hipFree(np.tiles);
-            (void)hipFree(np.tile_k);
-            (void)hipFree(np.chunk_t);
-            (void)hipFree(np.chunk_w);
+            free_plan(np);
             pl = &it->second;
         } else {
             A->bytes += np.bytes;
@@ -188,7 +192,7 @@ spk_status run_xwin(spk_handle h, const SpmvProblem &p, const spk_variant &v, hi
     if (!e) return fail(SPK_ERR_NOT_FOUND, "x-window kernel not compiled");
     XwinData *d = nullptr;
     XwinPlan *pl = nullptr;
-    SPK_TRY(get_xwin(h, A, v.group, v.lds, std::max(1, v.grid), &d, &pl));
+    SPK_TRY(get_xwin(h, A, v.group, v.block, v.lds, std::max(1, v.grid), &d, &pl));
     double *part = nullptr;
     if (d->npairs > 0) {
         {
@@ -209,11 +213,10 @@ spk_status run_xwin(spk_handle h, const SpmvProblem &p, const spk_variant &v, hi
             }
         }
         XwinArgs a{};
-        a.tiles = pl->tiles;
-        a.tile_k = pl->tile_k;
-        a.chunk_t = pl->chunk_t;
+        a.wave_p = pl->wave_p;
+        a.wave_k = pl->wave_k;
+        a.wave_c = pl->wave_c;
         a.chunk_w = pl->chunk_w;
-        a.ent = d->ent;
         a.ci = d->ci;
         a.val = d->val;
         a.x = p.x;

@@ -230,4 +230,40 @@ inline void xwin_plan(const XwinHost &d, int E, int64_t target, std::vector<uint
     chunk_t.push_back((int32_t)ntiles);
 }
 
+// The top bit of a column word marks a pair's first entry (columns inside a
+// window take 15 bits).
+constexpr uint16_t kXwinMark = 0x8000;
+
+// The wavefront ranges of a plan's chunks: nw per chunk, whole pairs, of equal
+// entries as far as pairs allow (a pair longer than a share leaves the
+// wavefronts it covers without any).  wave_p and wave_k (nchunk*nw + 1) hold
+// each range's first pair and entry; wave_c (nchunk*nw) the number of pairs
+// that start before its first tile, which begins at the entry rounded down to
+// a multiple of four.
+inline void xwin_waves(const XwinHost &d, int nw, const std::vector<uint32_t> &tiles,
+                       const std::vector<int32_t> &chunk_t, std::vector<int32_t> &wave_p,
+                       std::vector<int32_t> &wave_k, std::vector<int32_t> &wave_c)
+{
+    wave_p.clear();
+    wave_k.clear();
+    wave_c.clear();
+    const auto ent = d.ent.begin();
+    for (size_t c = 0; c + 1 < chunk_t.size(); ++c) {
+        const int64_t p0 = tiles[chunk_t[c]] & kBlkRowMask, p1 = tiles[chunk_t[c + 1]] & kBlkRowMask;
+        const int64_t k0 = d.ent[p0], k1 = d.ent[p1];
+        for (int v = 0; v < nw; ++v) {
+            const int64_t want = k0 + (k1 - k0) * v / nw;
+            const int64_t p = std::lower_bound(ent + p0, ent + p1, (int32_t)want) - ent;
+            const int32_t k = d.ent[p];
+            wave_p.push_back((int32_t)p);
+            wave_k.push_back(k);
+            int64_t before = p;
+            while (before > 0 && d.ent[before - 1] >= (k & ~3)) --before;
+            wave_c.push_back((int32_t)before);
+        }
+    }
+    wave_p.push_back((int32_t)d.npairs);
+    wave_k.push_back(d.ent.empty() ? 0 : d.ent[d.npairs]);
+}
+
 }  // namespace spk
