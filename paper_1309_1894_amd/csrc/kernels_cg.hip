@@ -34,12 +34,25 @@ typedef double f64x2_t __attribute__((ext_vector_type(2)));
 namespace {
 
 // Sum of part[0, n) in a fixed order (lane-strided, then the block tree),
-// returned to every thread.
-template <int BS>
+// returned to every thread; U loads in flight per lane (the residual kernel
+// adds one partial per tile group, thousands on a large matrix: 12.4 us with
+// one load in flight on lap3d(128), 11.1 with four; the direction kernel's few
+// are better left to the plain loop, 10.9 us against 11.9).
+template <int BS, int U = 1>
 __device__ __forceinline__ double sum_partials(const double *part, int64_t n, double *red)
 {
     double a = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += BS) a += part[i];
+    if constexpr (U == 1) {
+        for (int64_t i = threadIdx.x; i < n; i += BS) a += part[i];
+    } else {
+        for (int64_t i0 = threadIdx.x; i0 < n; i0 += U * BS) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = part[min(i0 + u * BS, n - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u) a += i0 + u * BS < n ? v[u] : 0.0;
+        }
+    }
     return block_sum<BS>(a, red);
 }
 
@@ -250,7 +263,7 @@ __global__ __launch_bounds__(BS) void k_cg_residual(CgLaunch c)
             qv[0][k] = c.q[i];
         }
     }
-    const double pq = sum_partials<BS>(c.part1, c.spmv_grid, red);
+    const double pq = sum_partials<BS, UNR>(c.part1, c.spmv_grid, red);
     const double rr = c.sc[c.slot];
     const double alpha = pq != 0.0 ? rr / pq : 0.0;
     if (blockIdx.x == 0 && t == 0) c.sc[kCgAlpha] = alpha;
