@@ -172,12 +172,13 @@ def test_vector_ops_at_2_pow_27_as_benched(spk, dev, dt):
 @pytest.mark.parametrize("dt", [np.float64, np.float32])
 @pytest.mark.parametrize("groups", [1, 31, 32, 33, 64, 65, 1535, 1536, 1537])
 def test_dot_at_the_ticket_limits(spk, dev, groups, dt):
-    """The default dot with as many workgroups as fill its tickets, one more
-    and one fewer (32 workgroups to a ticket, 1,536 in one launch), the last
-    workgroup ragged.  Integer data: exact; repeated calls on one stream find
-    the tickets as the call before left them."""
-    per = 256 * (2 if dt == np.float64 else 4) * 4     # elements per workgroup of the default variant
-    n = per * groups - 3
+    """A dot with as many workgroups as fill its tickets, one more and one
+    fewer (32 workgroups to a ticket, 1,536 in one launch), the last workgroup
+    ragged.  Integer data: exact; repeated calls on one stream find the tickets
+    as the call before left them."""
+    vec = 2 if dt == np.float64 else 4
+    n = 256 * vec * 4 * groups - 3
+    v = spk.make_variant(block=256, vec=vec, unroll=4, grid=8)
     h = spk.Handle(0)
     try:
         x = ((np.arange(n) * 7) % 17 - 8).astype(dt)
@@ -187,7 +188,8 @@ def test_dot_at_the_ticket_limits(spk, dev, groups, dt):
         xd, yd = torch.from_numpy(x).to(dev), torch.from_numpy(y).to(dev)
         out = torch.full((20,), float("nan"), dtype=torch.float64, device=dev)
         for i in range(20):
-            spk.spk_dot(xd, yd, out[i:i + 1], handle=h)
+            spk.spk_run(spk.problem(spk.SPK_OP_DOT, x=xd, y=yd, d_result=out[i:i + 1]), v, handle=h)
         assert out.cpu().tolist() == [ref] * 20
+        assert float(spk.spk_dot(xd, yd, handle=h)) == ref      # and the default variant
     finally:
         h.close()
