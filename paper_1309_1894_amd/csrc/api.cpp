@@ -158,20 +158,37 @@ static int pow2_ceil(double x)
     return p;
 }
 
+// Bytes of one operand from which WAXPY and AXPY run in narrow workgroups.
+constexpr int64_t kWaxpyNarrowBytes = int64_t(1) << 26;
+
 spk_variant default_variant(spk_handle h, const spk_problem &p, const spk_csr *csr)
 {
     spk_variant v{};
     switch (p.op) {
     case SPK_OP_WAXPY:
     case SPK_OP_AXPY:
-        v.block = 256;
-        v.vec = p.dtype == SPK_F64 ? 2 : 4;
-        v.unroll = 2;
+        // Out of the caches (operands of 64 MB and more): one-wavefront
+        // workgroups that each take 512 bytes of every operand, a line per
+        // request.  Back to back over three sets of operands: 71.2 us at n =
+        // 20,000,003 FP64 (6.74 TB/s), 36.9 in FP32 (6.5), 461 and 232 at 2^27,
+        // where 256 threads with two 16-byte accesses each take 75.6, 38.0, 525
+        // and 264 (wavefronts that wait for more reads before they write hold
+        // their slots longer).  Below 40 MB the two agree within 2%, and at n =
+        // 1e6 the wide form is the faster (6.3 us against 7.0).
+        if (p.n >= kWaxpyNarrowBytes / (int64_t)dtype_size(p.dtype)) {
+            v.block = 64;
+            v.vec = 1;
+            v.unroll = p.dtype == SPK_F64 ? 1 : 2;
+        } else {
+            v.block = 256;
+            v.vec = p.dtype == SPK_F64 ? 2 : 4;
+            v.unroll = 2;
+        }
         v.grid = 0;
         return v;
     case SPK_OP_DOT:
         // A workgroup per compute unit: few enough partials that every n ends
-        // in one launch.  Over the same sizes within 2% of each one's best:
+        // in one launch.  Over n = 1e6 to 2^27 within 2% of each one's best:
         // 16.2 us at n = 5e6 FP64 and 48.7 at 2e7 against 17.0 and 51.2 with
         // eight workgroups of 256 per compute unit.
         v.block = 512;

@@ -193,3 +193,30 @@ def test_dot_at_the_ticket_limits(spk, dev, groups, dt):
         assert float(spk.spk_dot(xd, yd, handle=h)) == ref      # and the default variant
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("dt", [np.float64, np.float32])
+@pytest.mark.parametrize("extra", [-1, 0, 1, 127])
+def test_waxpy_default_on_both_sides_of_the_narrow_rule(spk, dev, extra, dt):
+    """WAXPY and AXPY by the default around the size where it changes from wide
+    to one-wavefront workgroups, against the plain variant (the same
+    multiply-add per element: equal bits), also on operands off their 16-byte
+    alignment."""
+    n = (1 << 26) // np.dtype(dt).itemsize + extra
+    h = spk.Handle(0)
+    try:
+        tdt = torch.float64 if dt == np.float64 else torch.float32
+        x = torch.rand(n + 1, dtype=tdt, device=dev)
+        y = torch.rand(n + 1, dtype=tdt, device=dev)
+        plain = spk.spk_plain_variant(spk.SPK_OP_WAXPY, 0)
+        for o in (0, 1):
+            xs, ys = x[o:n + o], y[o:n + o]
+            ref, got = torch.zeros_like(xs), torch.zeros_like(xs)
+            spk.spk_run(spk.problem(spk.SPK_OP_WAXPY, x=xs, y=ys, w=ref, alpha=1.5), plain, handle=h)
+            spk.spk_waxpy(1.5, xs, ys, got, handle=h)
+            assert torch.equal(got, ref)
+            got.copy_(ys)
+            spk.spk_axpy(1.5, xs, got, handle=h)
+            assert torch.equal(got, ref)
+    finally:
+        h.close()
