@@ -340,7 +340,8 @@ spk_status spk_matrix_format_bytes(spk_handle h, spk_matrix A, int32_t format, i
 
 /* y = A*x on a registered matrix (the sparse product of Section 3's prior
  * GPU work), with the variant Section 2's search recorded for its shape
- * class, or the built-in default when none is recorded.  x: device,
+ * class, or the built-in default when none is recorded (the matrix-free
+ * form of a grid stencil, row blocks of any other matrix).  x: device,
  * A.ncols elements; y: device, A.nrows elements; both of A's dtype; y must
  * not overlap x (SPK_ERR_ALIAS).  Asynchronous on `stream`; a format built
  * on first use (sliced ELL, DIA, column blocks) is built then, on the same
@@ -373,7 +374,8 @@ spk_status spk_spmv_waxpy(spk_handle h, spk_matrix A, double alpha, const void *
  * matrix-free form when A is a constant-coefficient grid stencil), else a
  * default tile shape.  A small system (up to 4,096 rows of up to 7 entries,
  * 3,072 of 8, 2,048 of 12 or 1,024 of 24) for whose class nothing is
- * recorded is solved by one launch of one workgroup.
+ * recorded is solved by one launch of one workgroup, a larger grid stencil
+ * with the matrix-free form.
  *   b        device, n doubles (right-hand side), read only
  *   x        device, n doubles, 8-byte aligned: initial guess on entry, the
  *            iterate after `iters` iterations on return

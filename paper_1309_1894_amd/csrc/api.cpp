@@ -201,6 +201,24 @@ spk_variant default_variant(spk_handle h, const spk_problem &p, const spk_csr *c
     }
     v.streams = 1;
     v.unroll = 1;
+    if (p.A && p.A->st.stencil) {
+        // Registration found A to be a constant-coefficient grid stencil,
+        // entry by entry and bit by bit: its product needs none of A's arrays
+        // (the kernel adds the same products, in column order).  Against the
+        // row blocks, back to back over three sets: lap3d(128) 11.1 us and 43.4
+        // in FP64, 7.9 and 35.3 in FP32; lap2d(1400) 9.3 and 28.7; lap3d(70) 5.6
+        // and 10.5; no size slower (lap3d(40), lap2d(256): launch-bound, 5.6
+        // and 5.6).  Several rows per lane keep more loads in flight, which
+        // pays once there are workgroups enough: from 2^20 rows on (FP32
+        // lap3d(128) 7.9 us, with one row per lane 8.6 to 9.1), below it a row
+        // each is as fast (lap2d(500) 5.5 and 5.7).
+        const bool many = p.A->nrows >= (int64_t(1) << 20);
+        v.format = SPK_FMT_STENCIL;
+        v.block = many ? 512 : 256;
+        v.group = 1;
+        v.unroll = many ? 4 : 1;
+        return v;
+    }
     if (p.A) {
         v.format = SPK_FMT_ADAPTIVE;
         v.block = 256;

@@ -47,6 +47,16 @@ const CgEntry *default_cg_entry()
     return find_cg_entry(SPK_FMT_ADAPTIVE, kCgDefaultBlock, kCgDefaultEntries, 0);
 }
 
+// The matrix-free kernel's shape when nothing is recorded: a row per lane on
+// systems of few workgroups, two once there are enough (30 iterations on
+// lap3d(100): 660 us with two, 687 with one, 1,208 with the tile kernel;
+// lap3d(64) 421, 424 and 544 with one, two and the tiles; lap2d(512) 410, 411
+// and 536; lap3d(30) 340, 355 and 410).
+const CgEntry *default_stencil_entry(int64_t n)
+{
+    return find_cg_entry(SPK_FMT_STENCIL, 512, n >= (int64_t(1) << 19) ? 2 : 1, 0);
+}
+
 // Whether entry e can run on A: its format applies, and an LDS-staged
 // stencil's halo fits the budget.
 bool cg_entry_fits(const spk_mat *A, const CgEntry &e)
@@ -69,7 +79,8 @@ std::string cg_key(spk_mat *A)
 
 // The kernel recorded for A's class; else, for a system it takes, the
 // one-workgroup solve (kernels_cg.hip: as far as the rows' entries fit one
-// workgroup's registers), else the default tile shape.
+// workgroup's registers), else the matrix-free kernel of a grid stencil, else
+// the default tile shape.
 const CgEntry *cg_entry_for(spk_handle h, spk_mat *A)
 {
     if (!h->plain) {
@@ -85,6 +96,7 @@ const CgEntry *cg_entry_for(spk_handle h, spk_mat *A)
     }
     const CgEntry *small = find_cg_entry(SPK_FMT_SELL, kCgSmallBlock, 0, 0);
     if (!h->plain && small && cg_entry_fits(A, *small)) return small;
+    if (!h->plain && format_applies(A, SPK_FMT_STENCIL)) return default_stencil_entry(A->nrows);
     return default_cg_entry();
 }
 

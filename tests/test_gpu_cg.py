@@ -394,3 +394,34 @@ def test_cg_vector_kernels_at_the_chunk_limits(spk, dev, n):
     x, hist = _run(spk, M, b, x0, 10, dev)
     _compare(x, hist, xo, ho)
     M.release()
+
+
+@pytest.mark.parametrize("name", ["lap2d_65", "lap3d_80", "lap3d_81"])
+def test_cg_default_of_a_grid_stencil(spk, dev, name):
+    """A stencil just past the one-workgroup solve, and on both sides of the
+    2^19 rows where the matrix-free kernel takes two rows a lane, with nothing
+    recorded: the bits of that shape recorded, and the oracle's history."""
+    A = {"lap2d_65": lambda: I.lap2d(65), "lap3d_80": lambda: I.lap3d(80), "lap3d_81": lambda: I.lap3d(81)}[name]()
+    iters = 6
+    b, x0 = _vecs(A, 23)
+    xo, ho = O.cg(A, b, iters, x0)
+    H = spk.Handle()
+    try:
+        M = spk.Matrix(A, handle=H)
+        bd = torch.from_numpy(b).to(dev)
+        xs, hs = [], []
+        for rec in (False, True):
+            if rec:
+                key = "cg:" + spk.spk_class_key(spk.problem(spk.SPK_OP_SPMV, A=M), handle=H)
+                spk.spk_plan_put(key, spk.make_variant(format=spk.SPK_FMT_STENCIL, block=512, group=1,
+                                                       unroll=2 if A.nrows >= 1 << 19 else 1, streams=1), handle=H)
+            xd = torch.from_numpy(x0).to(dev)
+            hist = spk.spk_cg(M, bd, xd, iters)
+            torch.cuda.synchronize()
+            xs.append(xd.cpu().numpy())
+            hs.append(hist.cpu().numpy())
+        assert np.array_equal(xs[0], xs[1]) and np.array_equal(hs[0], hs[1])
+        _compare(xs[0], hs[0], xo, ho)
+        M.release()
+    finally:
+        H.close()

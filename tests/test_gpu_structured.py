@@ -216,3 +216,92 @@ def test_full_size_lap3d_128(spk, dev):
                 assert np.array_equal(y.cpu().numpy(), ref), (fmt, v.block, v.unroll, v.lds)
     finally:
         M.release()
+
+
+def grid_stencil(dims, coef):
+    """The constant-coefficient stencil on a grid of `dims` lines (slowest
+    first), `coef` per offset in ascending column order, columns of each row
+    in descending order (storage order is the caller's)."""
+    n = int(np.prod(dims))
+    strides = [int(np.prod(dims[d + 1:])) for d in range(len(dims))]
+    r = np.arange(n)
+    rows, cols, vals = [], [], []
+    steps = [(-s, (r // s) % d > 0) for s, d in zip(strides, dims)] + [(0, np.ones(n, bool))]
+    steps += [(s, (r // s) % d < d - 1) for s, d in list(zip(strides, dims))[::-1]]
+    for (off, ok), v in zip(steps, coef):
+        rows.append(r[ok])
+        cols.append(r[ok] + off)
+        vals.append(np.full(int(ok.sum()), v))
+    rows, cols, vals = map(np.concatenate, (rows, cols, vals))
+    order = np.lexsort((-cols, rows))
+    rp = np.zeros(n + 1, np.int64)
+    np.add.at(rp, rows + 1, 1)
+    return I.CSR(n, n, np.cumsum(rp).astype(np.int32), cols[order].astype(np.int32), vals[order])
+
+
+COEF = (-0.75, 0.3125, -1.1, 4.7, 0.9, -2.3, 0.55)
+GRIDS = {1: (4099,), 2: (61, 67), 3: (17, 5, 23)}
+BIG = {1: ((1 << 20) - 1, 1 << 20), 2: (1023, 1024), 3: (127, 128)}
+
+
+@pytest.mark.parametrize("dt", [1, 0])
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("dims", list(GRIDS.values()) + [(b,) for b in BIG[1]] + [(b, 1024) for b in BIG[2]]
+                         + [(b, 128, 64) for b in BIG[3]], ids=str)
+def test_default_of_grid_stencils_is_the_matrix_free_form(spk, dev, dims, fused, dt):
+    """The default product of grid stencils in one, two and three dimensions,
+    on both sides of the 2^20 rows where its shape changes: the bits of the
+    matrix-free form, within rounding of the row blocks' (at most 7 products
+    and 6 additions in FP64 each way, one rounding to the result's type), with
+    Inf and NaN in x reaching the same rows, and x and y off 16-byte alignment.
+    With one value changed in its last bit, A is no stencil and takes the row
+    blocks."""
+    say("default stencil", dims, fused, dt)
+    npt = NP[dt]
+    A = grid_stencil(dims, COEF[3 - len(dims):4 + len(dims)]).astype(npt)
+    n = A.nrows
+    h = spk.Handle(0)
+    try:
+        op = spk.SPK_OP_SPMV_WAXPY if fused else spk.SPK_OP_SPMV
+        alpha = 0.625
+        tiles = spk.make_variant(format=spk.SPK_FMT_ADAPTIVE, block=256, group=1, unroll=1, streams=1, lds=512)
+        free = spk.make_variant(format=STENCIL, block=256, group=1, unroll=1, streams=1)
+
+        def product(M, x, v):
+            y = torch.full((n + 1,), 7.0, dtype=M.torch_dtype, device=dev)[1:]
+            w = torch.full((n + 1,), 7.0, dtype=M.torch_dtype, device=dev)[1:]
+            spk.spk_run(spk.problem(op, A=M, x=x, y=y, alpha=alpha, **({"w": w} if fused else {})), v, handle=h)
+            return [t.double().cpu().numpy() for t in ((y, w) if fused else (y,))]
+
+        x = torch.from_numpy(I.uniform(77, 0, n + 1, npt)).to(dev)[1:]
+        M = spk.Matrix(A, handle=h)
+        assert M.formats() & (1 << STENCIL)
+        absx = np.abs(x.double().cpu().numpy())
+        bound = 26 * 2.0 ** -53 * sum(abs(c) for c in COEF) * absx.max()
+        eps = 2.0 ** -52 if dt == 1 else 2.0 ** -23
+        for special in (False, True):
+            if special:
+                x[n // 3] = float("inf")
+                x[n // 2] = float("nan")
+            got, same, ref = (product(M, x, v) for v in (None, free, tiles))
+            for g, s, r in zip(got, same, ref):
+                assert np.array_equal(g, s, equal_nan=True)
+                fin = np.isfinite(r)
+                assert np.array_equal(np.isnan(g), np.isnan(r))
+                assert np.array_equal(g[~fin], r[~fin], equal_nan=True)
+                # w = alpha*y + x: one more rounding of each, of at most |w|
+                lim = bound + eps * np.abs(r[fin]) + (eps * np.abs(r[fin]) + eps * bound * 4 if fused else 0.0)
+                if fused and dt == 0:
+                    lim = lim + 2 * eps * alpha * sum(abs(c) for c in COEF) * absx.max()
+                assert np.all(np.abs(g[fin] - r[fin]) <= lim)
+        M.release()
+        x = torch.from_numpy(I.uniform(78, 0, n, npt)).to(dev)
+        val = A.val.copy()
+        val[A.nnz // 2] = np.nextafter(val[A.nnz // 2], npt(np.inf))
+        M = spk.Matrix(I.CSR(n, n, A.row_ptr, A.col_idx, val), handle=h)
+        assert not M.formats() & (1 << STENCIL)
+        for g, r in zip(product(M, x, None), product(M, x, tiles)):
+            assert np.array_equal(g, r)
+        M.release()
+    finally:
+        h.close()
