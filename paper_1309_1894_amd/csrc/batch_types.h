@@ -35,13 +35,16 @@ static_assert(sizeof(BatchTile) == 64, "tile descriptor is one 64-byte line");
 // Serving launches: each request's matrix keeps its tiles on the device
 // (vector offsets 0), and a launch over several requests names them through
 // this table instead of copying tiles: launch tile t is tile
-// t - first of request req_of_tile[t], its vectors at vec_off in x / y / w.
+// t - first of request req_of_tile[t], its x at vec_off in the launch's x, its
+// y and w where they are wanted (device memory, or pinned host memory that
+// the kernel writes itself; a null w is not formed).
 struct BatchReq {
     const BatchTile *tiles;
     int64_t vec_off;
+    void *y, *w;
     int32_t first, pad;
 };
 
-static_assert(sizeof(BatchReq) == 24, "request record");
+static_assert(sizeof(BatchReq) == 40, "request record");
 
 }  // namespace spk

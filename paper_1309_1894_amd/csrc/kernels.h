@@ -337,6 +337,21 @@ hipError_t launch_widen(int dtype, int64_t n, const void *in, double *out, hipSt
 hipError_t launch_row_absum(int dtype, int32_t m, const int32_t *rp, const int32_t *ci,
                             const void *val, const void *x, double *scale, hipStream_t s);
 
+// Segments a copy kernel moves in one launch, each a multiple of 4 bytes
+// between addresses aligned to 4.
+constexpr int kCopySegs = 64;
+
+struct CopySegs {
+    const void *src[kCopySegs];
+    void *dst[kCopySegs];
+    int32_t bytes[kCopySegs];
+    int32_t first[kCopySegs];   // first workgroup of each (filled in at the launch)
+    int32_t n = 0;
+};
+
+// Copies the segments from pinned host memory to the device (in) or back.
+hipError_t launch_copy_segs(const CopySegs &c, bool in, hipStream_t s);
+
 // scale[vec_off + r] = sum_k |a_rk * x_k| for every row of every tile
 hipError_t launch_tiles_absum(int dtype, const BatchTile *tiles, int64_t ntiles, const void *x, double *scale,
                               hipStream_t s);

@@ -33,15 +33,60 @@ struct WaveTiles {
     static_assert(ITEMS * kWave * NW == TILE, "tile must split evenly over the wavefronts");
 };
 
-template <typename T, int BS, int TILE, int XW>
-__device__ __forceinline__ void run_wave_tile(const BatchArgs<T> &a, const BatchTile &td, double *sp, int *srp, T *xs)
+// An address every lane holds, as a scalar.
+__device__ __forceinline__ uint64_t uniform_addr(const void *p)
 {
+    const uint64_t a = (uint64_t)p;
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+}
+
+// Reads the record of launch tile `tile`, and where its y and w go.  The
+// record stays wavefront-uniform: with a request table the 16-bit map entry
+// arrives through a vector load and is made uniform again, and the record is
+// read through the constant address space (scalar loads).
+template <typename T>
+__device__ __forceinline__ BatchTile load_tile(const BatchArgs<T> &a, int tile, T **y, T **w)
+{
+    const BatchTile *tp = a.tiles + tile;
+    int64_t voff = -1;
+    uint64_t yq = 0, wq = 0;
+    if (a.req_of_tile) {
+        const int r = __builtin_amdgcn_readfirstlane((int)a.req_of_tile[tile]);
+        const BatchReq *q = a.reqs + r;
+        tp = q->tiles + (tile - q->first);
+        voff = q->vec_off;
+        yq = uniform_addr(q->y);
+        wq = uniform_addr(q->w);
+    }
+    const uint64_t tu = uniform_addr(tp);
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    const __attribute__((address_space(4))) u32x4 *src = (const __attribute__((address_space(4))) u32x4 *)tu;
+    u32x4 parts[sizeof(BatchTile) / sizeof(u32x4)];
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(BatchTile) / sizeof(u32x4)); ++i) parts[i] = src[i];
+    BatchTile td;
+    __builtin_memcpy(&td, parts, sizeof td);
+    if (voff >= 0) {
+        td.vec_off = voff;
+        *y = (T *)yq;
+        *w = (T *)wq;
+    } else {
+        *y = a.y + td.vec_off;
+        *w = a.w ? a.w + td.vec_off : nullptr;
+    }
+    return td;
+}
+
+template <typename T, int BS, int TILE, int XW>
+__device__ __forceinline__ void run_wave_tile(const BatchArgs<T> &a, int tile, double *sp, int *srp, T *xs)
+{
+    T *y, *w;
+    const BatchTile td = load_tile(a, tile, &y, &w);
     const int32_t *rp = td.rp;
     const int32_t *ci = td.ci;
     const T *val = (const T *)td.val;
     const T *x = a.x + td.vec_off;
-    T *y = a.y + td.vec_off;
-    T *w = a.w ? a.w + td.vec_off : nullptr;
     switch (td.mode) {
     case 0:  // entries and rows fit the wavefront's LDS slice (guaranteed by the planner)
         wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1, td.k0, td.k1,
@@ -71,35 +116,6 @@ __device__ __forceinline__ void run_wave_tile(const BatchArgs<T> &a, const Batch
     }
 }
 
-// Reads the record of launch tile `tile`.  The record stays
-// wavefront-uniform: with a request table the 16-bit map entry arrives
-// through a vector load and is made uniform again, and the record is read
-// through the constant address space (scalar loads).
-template <typename T>
-__device__ __forceinline__ BatchTile load_tile(const BatchArgs<T> &a, int tile)
-{
-    const BatchTile *tp = a.tiles + tile;
-    int64_t voff = -1;
-    if (a.req_of_tile) {
-        const int r = __builtin_amdgcn_readfirstlane((int)a.req_of_tile[tile]);
-        const BatchReq *q = a.reqs + r;
-        tp = q->tiles + (tile - q->first);
-        voff = q->vec_off;
-    }
-    const uint64_t ta = (uint64_t)tp;
-    const uint64_t tu = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(ta >> 32)) << 32) |
-                        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)ta);
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    const __attribute__((address_space(4))) u32x4 *src = (const __attribute__((address_space(4))) u32x4 *)tu;
-    u32x4 parts[sizeof(BatchTile) / sizeof(u32x4)];
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(BatchTile) / sizeof(u32x4)); ++i) parts[i] = src[i];
-    BatchTile td;
-    __builtin_memcpy(&td, parts, sizeof td);
-    if (voff >= 0) td.vec_off = voff;
-    return td;
-}
-
 template <typename T, int BS, int TILE, int XW>
 __global__ __launch_bounds__(BS) void k_batch_grid(BatchArgs<T> a)
 {
@@ -112,7 +128,7 @@ __global__ __launch_bounds__(BS) void k_batch_grid(BatchArgs<T> a)
     // runs of kXcdRunTiles tiles dealt to the XCDs in turn
     const int tile = xcd_chunk((int)blockIdx.x, ngroups, kXcdRunTiles / WT::NW) * WT::NW + wv;
     if (tile >= a.ntiles) return;
-    run_wave_tile<T, BS, TILE, XW>(a, load_tile(a, tile), sp + wv * WT::ENTRIES, srp + wv * (kWaveTileRows + 1),
+    run_wave_tile<T, BS, TILE, XW>(a, tile, sp + wv * WT::ENTRIES, srp + wv * (kWaveTileRows + 1),
                                    xs + wv * (XW > 0 ? XW : 1));
 }
 
@@ -137,8 +153,8 @@ __global__ __launch_bounds__(BS) void k_batch_persistent(BatchArgs<T> a)
     for (int g = (int)blockIdx.x; g < ngroups; g += (int)gridDim.x) {
         const int tile = xcd_chunk(g, ngroups, kXcdRunTiles / WT::NW) * WT::NW + wv;
         if (tile < a.ntiles)
-            run_wave_tile<T, BS, TILE, XW>(a, load_tile(a, tile), sp + wv * WT::ENTRIES,
-                                           srp + wv * (kWaveTileRows + 1), xs + wv * (XW > 0 ? XW : 1));
+            run_wave_tile<T, BS, TILE, XW>(a, tile, sp + wv * WT::ENTRIES, srp + wv * (kWaveTileRows + 1),
+                                           xs + wv * (XW > 0 ? XW : 1));
     }
 }
 

@@ -13,9 +13,10 @@
 //      used first to make room; a matrix in use is never evicted);
 //   3. launches the admitted group as one batched tile kernel on the next of
 //      its streams, so groups admitted while others run overlap on the GPU:
-//      the requests' x are copied into one pinned staging block, moved to
-//      the device by one copy, and the results come back the same way
-//      (large vectors in pinned caller buffers skip the staging block).
+//      the requests' x are copied into one pinned staging block, a copy
+//      kernel moves it to the device, and the tile kernel writes the results
+//      back into it (large vectors in pinned caller buffers skip the staging
+//      block).
 // The tile kernel is the batched one, with each matrix cut into tiles by the
 // kernel of its shape class (the tiles live on the device with the matrix;
 // a launch names them through a small request table), so a request's
@@ -310,22 +311,38 @@ void set_error(Server *S, spk_status st)
 }
 
 // Vectors of at least this many bytes skip the staging copies when the
-// caller's buffers are pinned host memory: the copy engines move them
-// between those buffers and the device directly.  Below it one memcpy into
-// the staging block costs less than a copy command of its own.
+// caller's buffers are pinned host memory: the launch's copy kernels (or, for
+// long vectors, the copy engines) move them between those buffers and the
+// device directly.  Below it one memcpy into the staging block costs less than
+// asking the runtime about three pointers.
 constexpr size_t kDirectMin = 128 << 10;
 
+// Vectors of at least this many bytes are left to the copy engines.  Shorter
+// ones and the staging block go to the device as segments of one copy kernel
+// (a copy command takes the device 10 us whatever its size, all of a launch's
+// segments in one kernel 4.4 us and their time on the link), and their
+// results come back from the tile kernel, which writes host memory itself.
+// The engines move both directions at once (8 MiB each way: 181 us, the
+// kernels 310), so the long vectors are theirs.  A closed round of 64 requests
+// over 16 matrices of 1,000 to 100,000 rows: 1,300 us with engines for
+// everything, 870 with the line at 2 MiB, 775 at 512 KiB, 864 at 256 KiB; 32
+// requests of up to 30,000 rows 500 to 580 us and 400; 8 of up to 8,000 110
+// and 85.
+constexpr size_t kEngineMin = 512 << 10;
+
 // Whether [p, p + n) lies inside one pinned host allocation of the HIP
-// runtime (hipHostMalloc).  Pageable memory, or a pointer the runtime does
-// not know, is not.
-bool pinned_range(const void *p, size_t n)
+// runtime (hipHostMalloc), at that address for the device too, and aligned to
+// the vector's type (`align` bytes).  Pageable memory, or a pointer the
+// runtime does not know, is not.
+bool pinned_range(const void *p, size_t n, size_t align)
 {
+    if ((uintptr_t)p % align != 0) return false;
     hipPointerAttribute_t a{};
     if (hipPointerGetAttributes(&a, p) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    if (a.type != hipMemoryTypeHost) return false;
+    if (a.type != hipMemoryTypeHost || a.devicePointer != p) return false;
     hipDeviceptr_t base = nullptr;
     size_t size = 0;
     if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)const_cast<void *>(p)) != hipSuccess) {
@@ -336,9 +353,38 @@ bool pinned_range(const void *p, size_t n)
     return q >= b && q + n <= b + size;
 }
 
+// One direction of a launch's copies: segments gathered into copy kernels,
+// long ones handed to the copy engines as they come.
+struct SegmentCopy {
+    bool in;             // host to device
+    hipStream_t s;
+    CopySegs c{};
+
+    spk_status add(void *dst, const void *src, size_t bytes)
+    {
+        if (bytes == 0) return SPK_OK;
+        if (bytes >= kEngineMin) {
+            SPK_HIP(hipMemcpyAsync(dst, src, bytes, in ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost, s));
+            return SPK_OK;
+        }
+        if (c.n == kCopySegs) SPK_TRY(flush());
+        c.src[c.n] = src;
+        c.dst[c.n] = dst;
+        c.bytes[c.n] = (int32_t)bytes;
+        ++c.n;
+        return SPK_OK;
+    }
+    spk_status flush()
+    {
+        if (c.n > 0) SPK_HIP(launch_copy_segs(c, in, s));
+        c.n = 0;
+        return SPK_OK;
+    }
+};
+
 // Launches a group of admitted requests (all of one dtype).  Requests whose
-// vectors are staged come first in the launch's vectors, then those copied
-// directly from and to the callers' pinned buffers.
+// vectors are staged come first in the launch's vectors, then those moved
+// straight between the callers' pinned buffers and the device.
 spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &group)
 {
     const int dtype = S->mats[group[0].second.mat].dtype;
@@ -356,8 +402,8 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
         const Request &R = group[k].second;
         const PoolMat &M = S->mats[R.mat];
         const size_t nb = vs * (size_t)M.m;
-        F.direct[k] = nb >= kDirectMin && pinned_range(R.x, nb) && pinned_range(R.y, nb) &&
-                      (!R.w || pinned_range(R.w, nb));
+        F.direct[k] = nb >= kDirectMin && pinned_range(R.x, nb, vs) && pinned_range(R.y, nb, vs) &&
+                      (!R.w || pinned_range(R.w, nb, vs));
         if (!F.direct[k]) staged += M.m;
     }
     F.off.assign(group.size(), 0);
@@ -369,7 +415,7 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
             }
     for (size_t k = 0; k < group.size(); ++k) {
         const PoolMat &M = S->mats[group[k].second.mat];
-        if (batched) rq.push_back({M.d_tiles, F.off[k], (int32_t)ntiles, 0});
+        if (batched) rq.push_back({M.d_tiles, F.off[k], nullptr, nullptr, (int32_t)ntiles, 0});
         ntiles += (int64_t)M.tiles.size();
     }
     // one staging block: [requests | tile map | x | y | w], 256-byte aligned parts
@@ -385,6 +431,19 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
     SPK_HIP(S->dpool.get(all_b, &F.dev));
     SPK_HIP(S->hpool.get(all_b, &F.pin));
     char *pin = (char *)F.pin;
+    char *dev = (char *)F.dev;
+    // where each request's results go: host memory, or device memory for what
+    // the copy engines bring back
+    std::vector<char> engine_out(group.size(), batched ? 0 : 1);
+    for (size_t k = 0; batched && k < group.size(); ++k) {
+        const Request &R = group[k].second;
+        const size_t at = vs * (size_t)F.off[k];
+        engine_out[k] = vs * (size_t)S->mats[R.mat].m >= kEngineMin;
+        char *to_y = F.direct[k] ? (char *)R.y : pin + F.y_off + at;
+        char *to_w = F.direct[k] ? (char *)R.w : pin + F.w_off + at;
+        rq[k].y = engine_out[k] ? dev + F.y_off + at : to_y;
+        rq[k].w = !R.w ? nullptr : engine_out[k] ? dev + F.w_off + at : to_w;
+    }
     if (batched) {
         memcpy(pin, rq.data(), sizeof(BatchReq) * rq.size());
         uint16_t *map = (uint16_t *)(pin + req_b);
@@ -425,13 +484,13 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
         }
         SPK_HIP(hipStreamWaitEvent(s, M.uploaded, 0));
     }
-    char *dev = (char *)F.dev;
-    if (head_b + vs * (size_t)staged > 0)
-        SPK_HIP(hipMemcpyAsync(dev, pin, head_b + vs * (size_t)staged, hipMemcpyHostToDevice, s));
+    SegmentCopy to_dev{true, s};
+    SPK_TRY(to_dev.add(dev, pin, head_b + vs * (size_t)staged));
     for (size_t k = 0; k < group.size(); ++k)
         if (F.direct[k])
-            SPK_HIP(hipMemcpyAsync(dev + head_b + vs * F.off[k], group[k].second.x,
-                                   vs * (size_t)S->mats[group[k].second.mat].n, hipMemcpyHostToDevice, s));
+            SPK_TRY(to_dev.add(dev + head_b + vs * F.off[k], group[k].second.x,
+                               vs * (size_t)S->mats[group[k].second.mat].n));
+    SPK_TRY(to_dev.flush());
     F.t_enqueued = now_seconds();
     {
         std::lock_guard<std::mutex> lk(S->mu);
@@ -456,21 +515,15 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
         SPK_TRY(launch_tiles(S->entry, dtype, nullptr, ntiles, S->opts.alpha, x, y, w, kBatchGrid, 0, s,
                              (const BatchReq *)dev, (const uint16_t *)(dev + req_b)));
     }
-    if (staged == total) {
-        SPK_HIP(hipMemcpyAsync(pin + F.y_off, y, 2 * vec_b, hipMemcpyDeviceToHost, s));
-    } else {
-        if (staged > 0) {
-            SPK_HIP(hipMemcpyAsync(pin + F.y_off, y, vs * (size_t)staged, hipMemcpyDeviceToHost, s));
-            SPK_HIP(hipMemcpyAsync(pin + F.w_off, w, vs * (size_t)staged, hipMemcpyDeviceToHost, s));
-        }
-        for (size_t k = 0; k < group.size(); ++k) {
-            if (!F.direct[k]) continue;
-            const Request &R = group[k].second;
-            const size_t nb = vs * (size_t)S->mats[R.mat].m;
-            SPK_HIP(hipMemcpyAsync(R.y, dev + F.y_off + vs * F.off[k], nb, hipMemcpyDeviceToHost, s));
-            if (R.w) SPK_HIP(hipMemcpyAsync(R.w, dev + F.w_off + vs * F.off[k], nb, hipMemcpyDeviceToHost, s));
-        }
+    SegmentCopy to_host{false, s};
+    for (size_t k = 0; k < group.size(); ++k) {
+        if (!engine_out[k]) continue;
+        const Request &R = group[k].second;
+        const size_t nb = vs * (size_t)S->mats[R.mat].m, at = vs * (size_t)F.off[k];
+        SPK_TRY(to_host.add(F.direct[k] ? (char *)R.y : pin + F.y_off + at, dev + F.y_off + at, nb));
+        if (R.w) SPK_TRY(to_host.add(F.direct[k] ? (char *)R.w : pin + F.w_off + at, dev + F.w_off + at, nb));
     }
+    SPK_TRY(to_host.flush());
     F.done = take_event(S);
     SPK_HIP(hipEventRecord(F.done, s));
     F.vec_bytes = 0;

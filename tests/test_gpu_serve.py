@@ -267,3 +267,53 @@ def test_serve_classes_planned_to_compact_columns(spk, dev):
     for i in range(nreq):
         _check(pool[mats[i]], xs[i], outs[3][0][i], outs[3][1][i])
         assert np.array_equal(outs[3][0][i], outs[1][0][i]) and np.array_equal(outs[3][1][i], outs[1][1][i]), i
+
+
+@pytest.mark.parametrize("dt", [np.float64, np.float32])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_serve_copies_at_their_size_limits(spk, dev, dt, mode):
+    """Vectors at the sizes where the way of their copies changes (128 KiB:
+    straight from and to pinned buffers; 512 KiB: copy engines instead of
+    kernels; lengths that end inside an 8-byte word), each in pinned,
+    pageable and unaligned buffers, with and without w, in launches of more
+    segments than one copy kernel takes: every result matches the oracle."""
+    import torch
+    item = np.dtype(dt).itemsize
+    lim = [(128 << 10) // item, (512 << 10) // item]
+    sizes = [1, 3, lim[0] - 1, lim[0], lim[0] + 1, lim[1] - 1, lim[1], lim[1] + 3]
+    pool = [I.banded(m, 1, 1.0, seed_struct=120, seed_val=121 + i, dtype=dt) for i, m in enumerate(sizes)]
+
+    def pinned(n):
+        return torch.full((n * item,), 255, dtype=torch.uint8).pin_memory().numpy().view(dt)
+
+    def pageable(n):
+        return np.full(n, np.nan, dt)
+
+    def unaligned(n):
+        return torch.full((n * item + 2,), 255, dtype=torch.uint8).pin_memory().numpy()[2:].view(dt)
+
+    nreq = 3 * 8 * len(sizes) if mode == 0 else 3 * len(sizes)
+    mats = [i % len(sizes) for i in range(nreq)]
+    xs, ys, ws = [], [], []
+    for i, m in enumerate(mats):
+        make = (pinned, pageable, unaligned)[i // len(sizes) % 3]
+        x, y, w = (make(pool[m].nrows) for _ in range(3))
+        x[:] = I.uniform(140, i, x.size, dt)
+        xs.append(x), ys.append(y), ws.append(w)
+    say(f"serve copy limits {np.dtype(dt).name} mode={mode}: {nreq} requests")
+    srv = spk.Server(streams=2, max_inflight=nreq, max_batch=nreq, mode=mode, max_launches=2, alpha=0.5)
+    try:
+        ids = [srv.add_matrix(A) for A in pool]
+        for i, m in enumerate(mats):
+            if i % 5 == 4:
+                srv.submit(ids[m], xs[i], ys[i])
+            else:
+                srv.submit(ids[m], xs[i], ys[i], ws[i])
+        srv.drain()
+        assert srv.stats()["completed"] == nreq and srv.stats()["rejected"] == 0
+    finally:
+        srv.close()
+    for i, m in enumerate(mats):
+        if i % 5 == 4:
+            ws[i] = O.waxpy(0.5, np.array(ys[i]), np.array(xs[i]))
+        _check(pool[m], np.array(xs[i]), np.array(ys[i]), np.array(ws[i]))
