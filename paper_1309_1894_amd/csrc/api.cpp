@@ -410,6 +410,7 @@ template <typename T>
 static void fill_args(SpmvArgs<T> &a, const SpmvProblem &p, const int32_t *rp, const int32_t *ci, const void *val)
 {
     a.rp = rp;
+    a.keep = keep_matrix(p.mat ? p.mat->nnz : p.csr->nnz, p.mat ? p.mat->dtype : p.csr->dtype);
     a.ci = ci;
     a.val = (const T *)val;
     a.x = (const T *)p.x;

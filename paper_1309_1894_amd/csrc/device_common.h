@@ -161,6 +161,7 @@ struct SpmvArgs {
     int32_t blk0, nblk;
     const int32_t *lrow;      // rows run by a workgroup each (the launch's first nlong workgroups)
     int32_t nlong;
+    int32_t keep;             // 1 = the matrix may stay in the last-level cache between products
 };
 
 // Row blocks of the LDS-staged kernel are wavefront tiles:

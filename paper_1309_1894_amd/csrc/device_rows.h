@@ -77,10 +77,20 @@ __device__ __forceinline__ gptr_mut<T> as_global_mut(T *p) { return (gptr_mut<T>
 // staging, so an entry costs CB bytes of index traffic instead of 4;
 // everything else, the order of the arithmetic included, is as with
 // 4-byte columns.
-template <typename T, int ITEMS, bool DOT = false, int XW = 0, int CB = 4>
+// A matrix entry is read once a product, so the values are loaded
+// non-temporal: the caches keep the x entries that neighbouring rows share.
+// With `keep` (a matrix small enough to stay in the last-level cache from one
+// product to the next: keep_matrix) they are ordinary loads.  The columns are ordinary
+// loads too: a tile's first and last lines are its neighbours' as well, and
+// read non-temporal they came from memory twice (lap3d(128) FP64 42.3 us and
+// 39.6, a band of 600,000 rows of 20 entries 32.9 and 29.5, in FP32 24.1 and
+// 21.2).  NTC reads them non-temporal all the same, for the batched kernels:
+// 512 instances take 80.6 us so, 82.2 with ordinary loads, 96 in FP32 12.6 and
+// 12.8.
+template <typename T, int ITEMS, bool DOT = false, int XW = 0, int CB = 4, bool NTC = false>
 __device__ __forceinline__ double wave_stream(const int32_t *rp_, const int32_t *ci_, const T *val_, const T *x_,
                                               T *y_, T *w_, T alpha, int r0, int r1, int k0, int k1, double *sp,
-                                              int *srp, int xlo = 0, int xn = 0, T *xs = nullptr)
+                                              int *srp, int xlo = 0, int xn = 0, T *xs = nullptr, bool keep = false)
 {
     static_assert(CB == 4 || CB == 2 || CB == 1, "columns of 4, 2 or 1 bytes");
     static_assert(CB != 1 || (XW > 0 && XW <= 256), "one-byte columns index a window of at most 256 entries");
@@ -108,12 +118,17 @@ __device__ __forceinline__ double wave_stream(const int32_t *rp_, const int32_t 
         const gptr<uint8_t> cg = cb + ((int64_t)k0 - off) * IB;
         const int glast = (off + klast) & ~(GE - 1);   // start of the last group holding an entry
 #pragma unroll
-        for (int s = 0; s < STEPS; ++s)
-            g[s] = __builtin_nontemporal_load((gptr<int4v>)(cg + IB * min(GE * (l + kWave * s), glast)));
-        // matrix entries are read exactly once: non-temporal, so the cache
-        // keeps the x entries that neighbouring rows share
+        for (int s = 0; s < STEPS; ++s) {
+            const gptr<int4v> at = (gptr<int4v>)(cg + IB * min(GE * (l + kWave * s), glast));
+            g[s] = NTC ? __builtin_nontemporal_load(at) : *at;
+        }
+        if (keep) {
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j) v[j] = __builtin_nontemporal_load(val + k0 + min(l + j * kWave, klast));
+            for (int j = 0; j < ITEMS; ++j) v[j] = val[k0 + min(l + j * kWave, klast)];
+        } else {
+#pragma unroll
+            for (int j = 0; j < ITEMS; ++j) v[j] = __builtin_nontemporal_load(val + k0 + min(l + j * kWave, klast));
+        }
     }
     constexpr int XQ = XW > 0 ? XW / kWave : 1;
     T xwv[XQ];

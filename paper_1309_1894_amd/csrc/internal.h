@@ -277,6 +277,13 @@ spk_status get_sell(spk_handle h, spk_mat *A, int C, SellData **out);
 spk_status get_blocks(spk_handle h, spk_mat *A, int entries, int block, BlockData **out);
 spk_status get_block_windows(spk_handle h, spk_mat *A, BlockData *bd);
 spk_status get_block_c16(spk_handle h, spk_mat *A, BlockData *bd);
+// Whether a matrix of nnz entries is read so that it may stay in the
+// last-level cache (256 MB) from one product to the next: up to 80 MB of
+// values and columns.  Products of three such matrices in turn, with ordinary
+// and with non-temporal loads of the values: 39 MB (300,001 Zipf rows, FP32)
+// 34.4 us and 36.0, 47 MB (200,003 rows of 20 entries, FP64) 13.0 and 13.5, 73
+// MB 20.0 and 20.9, 95 MB 26.3 and 25.5, 143 MB 34.2 and 30.7.
+inline bool keep_matrix(int64_t nnz, int dtype) { return nnz * (int64_t)(dtype_size(dtype) + 4) <= (int64_t(80) << 20); }
 
 // SPK_FMT_XWIN: kernel entry, validity, run and release.
 const XwinEntry *find_xwin_entry(int block, int window_kib, int entries);

@@ -89,22 +89,22 @@ __device__ __forceinline__ void run_wave_tile(const BatchArgs<T> &a, int tile, d
     const T *x = a.x + td.vec_off;
     switch (td.mode) {
     case 0:  // entries and rows fit the wavefront's LDS slice (guaranteed by the planner)
-        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1, td.k0, td.k1,
+        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, 0, 4, true>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1, td.k0, td.k1,
                                                       sp, srp);
         break;
     case 1:  // the same, x from the tile's window in LDS when it fits the kernel's room
-        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1,
+        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 4, true>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1,
                                                                  td.k0, td.k1, sp, srp, td.xlo,
                                                                  XW > 0 && td.xn <= XW ? td.xn : 0, xs);
         break;
     case 3:  // mode 1 with compact columns: ci holds each entry's byte offset in the window (which fits)
         if constexpr (XW > 0 && XW <= 256)
-            wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 1>(rp, ci, val, x, y, w, a.alpha, td.r0,
+            wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 1, true>(rp, ci, val, x, y, w, a.alpha, td.r0,
                                                                            td.r1, td.k0, td.k1, sp, srp, td.xlo,
                                                                            td.xn, xs);
         break;
     case 5:  // compact columns of a wider tile: two-byte offsets from xlo, x gathered from memory
-        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 2>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1,
+        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 2, true>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1,
                                                                        td.k0, td.k1, sp, srp, td.xlo, 0, xs);
         break;
     case 2: wave_group_rows<T, 2>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1); break;

@@ -307,13 +307,13 @@ __global__ __launch_bounds__(BS) void k_spmv_adaptive(SpmvArgs<T> a)
                 wave_stream<T, E / kWave, false, XW, 2>(a.rp, reinterpret_cast<const int32_t *>(a.c16), a.val, a.x,
                                                         a.y, w, a.alpha, r0, r1, a.block_k[b], a.block_k[b + 1],
                                                         sp + wv * E, srp + wv * (kWaveTileRows + 1), base, xn,
-                                                        xs + wv * (XW > 0 ? XW : 1));
+                                                        xs + wv * (XW > 0 ? XW : 1), a.keep != 0);
                 return;
             }
         }
         wave_stream<T, E / kWave, false, XW>(a.rp, a.ci, a.val, a.x, a.y, w, a.alpha, r0, r1, a.block_k[b],
                                              a.block_k[b + 1], sp + wv * E, srp + wv * (kWaveTileRows + 1), xlo, xn,
-                                             xs + wv * (XW > 0 ? XW : 1));
+                                             xs + wv * (XW > 0 ? XW : 1), a.keep != 0);
     } else if (mode == kBlkWave) {
         // medium rows (a kBlkLong tile's row is a workgroup's)
         wave_rows_mlp<T, 8>(a.rp, a.ci, a.val, a.x, a.y, w, a.alpha, r0, r1);

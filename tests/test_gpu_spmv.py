@@ -484,3 +484,35 @@ def test_borrowed_csr_default_on_both_sides_of_its_rules(spk, dev, m, mean, dt):
     y.fill_(float("nan"))
     spk.spk_spmv_csr(d[0], o[0], o[1], d[3], y[:m])
     assert np.array_equal(y.cpu().numpy()[:m], ref.astype(NP[dt]))
+
+
+@pytest.mark.parametrize("dt", [1, 0])
+@pytest.mark.parametrize("extra", [0, 1])
+def test_matrices_on_both_sides_of_the_cache_rule(spk, dev, extra, dt):
+    """A matrix of exactly 80 MB of values and columns and one of an entry
+    more (where the values' loads change), by row blocks and by the row stream.
+    Integer data: exact."""
+    nnz = (80 << 20) // (np.dtype(NP[dt]).itemsize + 4) + extra
+    m = nnz // 21
+    lens = np.full(m, nnz // m)
+    lens[:nnz - int(lens.sum())] += 1
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    assert rp[-1] == nnz
+    n = 4096
+    k = np.arange(nnz, dtype=np.int64)
+    A = I.CSR(m, n, rp, ((k * 2654435761) % n).astype(np.int32), ((k % 17) - 8).astype(NP[dt]))
+    x = (np.arange(n) % 13 - 6).astype(NP[dt])
+    ref = np.add.reduceat((A.val.astype(np.float64) * x[A.col_idx]), rp[:-1])
+    say(f"cache rule nnz={nnz} dtype={dt}")
+    M = spk.Matrix(A)
+    try:
+        xd = torch.from_numpy(x).to(dev)
+        y = torch.empty(m, dtype=xd.dtype, device=dev)
+        spk.spk_spmv_mat(M, xd, y)
+        assert np.array_equal(y.cpu().numpy(), ref.astype(NP[dt]))
+        d = [torch.from_numpy(t).to(dev) for t in (A.row_ptr, A.col_idx, A.val)]
+        y.fill_(float("nan"))
+        spk.spk_spmv_csr(*d, xd, y)
+        assert np.array_equal(y.cpu().numpy(), ref.astype(NP[dt]))
+    finally:
+        M.release()
