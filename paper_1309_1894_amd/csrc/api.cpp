@@ -230,17 +230,21 @@ spk_variant default_variant(spk_handle h, const spk_problem &p, const spk_csr *c
     v.format = SPK_FMT_VECTOR;
     v.block = 256;
     // A borrowed CSR matrix (only its sizes are known): the row stream, with
-    // as many rows per wavefront as make about one 512-entry chunk, but at
-    // least eight wavefronts per compute unit.  64 rows of 7.8 entries take
-    // 14.0 us where 32 take 14.4 (500,000 rows), 32 rows of 19.8 14.1 us where
-    // 64 take 20.1; of 40,000 such rows 32 per wavefront take 9.5 us, 16 take
-    // 7.8.  From about 80 entries a row on, G lanes per row read long runs
-    // anyway (145 entries: 15.1 us against 18.5 with 8 rows a wavefront, 73
-    // entries: 20.0 against 14.4); and below 8,192 rows they give the GPU more
-    // wavefronts.
+    // as many rows per wavefront as fill one 512-entry chunk, but at least
+    // eight wavefronts per compute unit: of 600,000 rows of 19.8 entries (FP64)
+    // 24 per wavefront take 30.3 us, 20 and 28, which leave more of a chunk
+    // empty or start a second one, 31.6 and 33.3; 300,000 rows of 39.0 entries
+    // 29.5 with 12, 30.7 with 8, 33.0 with 16; 100,000 rows of 19.8 6.9 with
+    // 16, 8.6 with 32.  From about 80 entries a row on, G lanes per row read
+    // long runs anyway (145 entries: 15.1 us against 18.5 with 8 rows a
+    // wavefront, 73 entries: 20.0 against 14.4); and below 8,192 rows they
+    // give the GPU more wavefronts.
     if (mean <= 80.0 && csr && csr->nrows >= 8192) {
-        v.group = 64;
-        while (v.group > 8 && (v.group * mean > 640.0 || csr->nrows < v.group * 8ll * h->num_cu)) v.group /= 2;
+        const int rows[] = {64, 48, 32, 28, 24, 20, 16, 12, 8};   // the compiled ones
+        for (int r : rows) {
+            v.group = r;
+            if (r * mean <= 500.0 && csr->nrows >= r * 8ll * h->num_cu) break;
+        }
         v.lds = 512;
         return v;
     }

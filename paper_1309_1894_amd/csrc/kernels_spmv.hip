@@ -154,14 +154,20 @@ __global__ __launch_bounds__(BS) void k_spmv_vector(SpmvArgs<T> a)
 
 // R consecutive rows per wavefront on the plain CSR arrays (no tiles made
 // beforehand): their entries are streamed in chunks of E with coalesced loads,
-// the products go to the wavefront's LDS slice, and G = 64/R lanes add each
-// row's part of the chunk; a row with more than 32*G entries in a chunk is
-// added by all 64 lanes.  ROWSNUM
-template <typename T, int BS, int R, int E, bool FUSED>
+// the products go to the wavefront's LDS slice, and G lanes (a power of two,
+// R*G <= 64) add each row's part of the chunk; a row with more than 32*G
+// entries in a chunk is added by all 64 lanes.  Bound by memory latency (row
+// offsets, then entries, then x): a chunk's loads all go out before the first
+// is used, the next chunk's while this one's products are added, and the
+// columns are ordinary loads (a chunk's end lines are its neighbours' too).
+// 600,000 rows of 19.8 entries, FP64: 39.0 us at the best R without these, 30.7
+// with (4.8 TB/s; 16 lanes per row and no LDS 75.6); 200,003 rows 14.2 and
+// 13.0; 300,000 rows of 39 entries 37.8 and 29.5.
+template <typename T, int BS, int R, int E, bool FUSED, bool KEEP>
 __global__ __launch_bounds__(BS) void k_spmv_rows(SpmvArgs<T> a)
 {
     constexpr int NW = BS / kWave;
-    constexpr int G = kWave / R;
+    constexpr int G = kWave / R >= 8 ? 8 : kWave / R >= 4 ? 4 : kWave / R >= 2 ? 2 : 1;   // R * G <= 64
     constexpr int ITEMS = E / kWave;
     __shared__ double stage[NW * E];
     const int l = threadIdx.x & (kWave - 1);
@@ -179,23 +185,30 @@ __global__ __launch_bounds__(BS) void k_spmv_rows(SpmvArgs<T> a)
     if constexpr (FUSED) xo = x[r0 + min(row, nr - 1)];
     const int k0 = __builtin_amdgcn_readlane(s, 0);
     const int k1 = __builtin_amdgcn_readlane(e, kWave - 1);
-    double acc = 0.0;
-    for (int64_t kb64 = k0; kb64 < k1; kb64 += E) {
-        const int kb = (int)kb64;
+    int c[ITEMS];
+    T v[ITEMS];
+    const auto load = [&](int kb) {
         const int last = k1 - 1 - kb;      // last entry of the rows, from the chunk's first
-        int c[ITEMS];
-        T v[ITEMS];
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j)
+            if (j * kWave <= last) c[j] = ci[kb + min(l + j * kWave, last)];
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j)
             if (j * kWave <= last) {
-                const int k = min(l + j * kWave, last);
-                c[j] = __builtin_nontemporal_load(ci + kb + k);
-                v[j] = __builtin_nontemporal_load(val + kb + k);
+                const gptr<T> at = val + kb + min(l + j * kWave, last);
+                v[j] = KEEP ? *at : __builtin_nontemporal_load(at);
             }
+    };
+    if (k0 < k1) load(k0);
+    double acc = 0.0;
+    for (int64_t kb64 = k0; kb64 < k1; kb64 += E) {
+        const int kb = (int)kb64;
+        const int last = k1 - 1 - kb;
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j)
             if (j * kWave <= last) sp[l + j * kWave] = (double)v[j] * (double)x[c[j]];
         wave_lds_sync();
+        if (kb64 + E < k1) load(kb + E);   // while this chunk's products are added
         const int lo = max(s - kb, 0), hi = min(e - kb, E);
         unsigned long long wide = __ballot(hi - lo > 32 * G && sub == 0);
         if (hi - lo <= 32 * G) {
@@ -417,7 +430,9 @@ hipError_t L_vector(const void *p, dim3 g, hipStream_t s)
 template <typename T, int BS, int R, int E, bool F>
 hipError_t L_rows(const void *p, dim3 g, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_spmv_rows<T, BS, R, E, F>), g, dim3(BS), 0, s, *(const SpmvArgs<T> *)p);
+    const SpmvArgs<T> &a = *(const SpmvArgs<T> *)p;
+    if (a.keep) hipLaunchKernelGGL((k_spmv_rows<T, BS, R, E, F, true>), g, dim3(BS), 0, s, a);
+    else hipLaunchKernelGGL((k_spmv_rows<T, BS, R, E, F, false>), g, dim3(BS), 0, s, a);
     return hipGetLastError();
 }
 
@@ -486,7 +501,8 @@ const SpmvEntry kSpmv[] = {
     VECTOR_V(256, 4, 2, 2), VECTOR_V(256, 8, 2, 2), VECTOR_V(256, 16, 2, 2), VECTOR_V(256, 32, 2, 2),
     VECTOR_V(256, 64, 2, 2), VECTOR_V(256, 8, 4, 4), VECTOR_V(256, 16, 4, 4), VECTOR_V(256, 64, 4, 4),
     // row stream on the plain arrays
-    ROWS(256, 8, 512), ROWS(256, 16, 512), ROWS(256, 32, 512), ROWS(256, 64, 512),
+    ROWS(256, 8, 512), ROWS(256, 12, 512), ROWS(256, 16, 512), ROWS(256, 20, 512), ROWS(256, 24, 512), ROWS(256, 28, 512),
+    ROWS(256, 32, 512), ROWS(256, 48, 512), ROWS(256, 64, 512),
     // row blocks with two-byte columns
     ADAPT_C16(64, 256), ADAPT_C16(64, 512), ADAPT_C16(64, 1024), ADAPT_C16(128, 256), ADAPT_C16(128, 512),
     ADAPT_C16(256, 256), ADAPT_C16(256, 512), ADAPT_C16(512, 256),

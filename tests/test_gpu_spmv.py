@@ -487,6 +487,36 @@ def test_borrowed_csr_default_on_both_sides_of_its_rules(spk, dev, m, mean, dt):
 
 
 @pytest.mark.parametrize("dt", [1, 0])
+@pytest.mark.parametrize("rows", [8, 12, 16, 20, 24, 28, 32, 48, 64])
+@pytest.mark.parametrize("mean", [1, 19, 70])
+def test_row_stream_shapes(spk, dev, rows, mean, dt):
+    """Every row stream shape (rows per wavefront, powers of two or not) on
+    rows that leave the last wavefront ragged, empty rows, rows longer than a
+    chunk, and chunks that end at and inside a row.  Integer data: exact."""
+    m = 37 * rows + rows // 2 + 1
+    rng = np.random.default_rng(rows * 100 + mean)
+    lens = rng.integers(0, 2 * mean + 1, m)
+    lens[[0, m // 2, m - 1]] = [1100, 512, 700]
+    lens[rows:2 * rows] = 512 // rows                   # a wavefront whose rows fill one chunk at most
+    lens[2 * rows:3 * rows] = 0                         # and one without entries
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    n = 1009
+    A = I.CSR(m, n, rp, rng.integers(0, n, rp[-1]).astype(np.int32), rng.integers(-8, 9, rp[-1]).astype(NP[dt]))
+    x = rng.integers(-8, 9, n).astype(NP[dt])
+    ref = O.spmv(A, x)[0].astype(NP[dt])
+    M = spk.Matrix(A)
+    try:
+        xd = torch.from_numpy(x).to(dev)
+        y = torch.full((m + 64,), float("nan"), dtype=xd.dtype, device=dev)
+        v = spk.make_variant(format=2, block=256, group=rows, unroll=1, lds=512, streams=1)
+        spk.spk_run(spk.problem(spk.SPK_OP_SPMV, A=M, x=xd, y=y[:m]), v)
+        got = y.cpu().numpy()
+        assert np.array_equal(got[:m], ref) and np.all(np.isnan(got[m:]))
+    finally:
+        M.release()
+
+
+@pytest.mark.parametrize("dt", [1, 0])
 @pytest.mark.parametrize("extra", [0, 1])
 def test_matrices_on_both_sides_of_the_cache_rule(spk, dev, extra, dt):
     """A matrix of exactly 80 MB of values and columns and one of an entry
