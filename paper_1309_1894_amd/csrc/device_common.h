@@ -176,8 +176,8 @@ struct BatchArgs {
     T *y;
     T *w;              // may be null (SpMV only)
     T alpha;
-    const BatchReq *reqs;            // serving (grid launch): tiles named per request, or null
-    const uint16_t *req_of_tile;     // request of each launch tile (with reqs)
+    const BatchReq *reqs;            // serving (kBatchRequests): tiles and results named per request
+    const uint16_t *req_of_tile;     // request of each launch tile
 };
 
 }  // namespace spk

@@ -213,11 +213,12 @@ using BatchFn = hipError_t (*)(const void *args, dim3 grid, hipStream_t);
 // workgroup of BS threads runs BS/64 consecutive tiles, one per wavefront.
 constexpr int kBatchGrid = 0;        // one workgroup per group of BS/64 tiles
 constexpr int kBatchPersistent = 1;  // persistent grid walking the tile groups in strides
+constexpr int kBatchRequests = 2;    // serving: the grid form, tiles and results named by a request table
 
 struct BatchEntry {
     int block, tile;     // threads per workgroup, LDS products per workgroup
     int xw;              // LDS room for x per wavefront (entries) for mode-1 tiles, 0 = none
-    BatchFn fn[2][2];    // [dtype][launch kind]
+    BatchFn fn[2][3];    // [dtype][launch kind]
     int (*occupancy[2])();  // [dtype] resident workgroups per CU (persistent kernel)
 };
 

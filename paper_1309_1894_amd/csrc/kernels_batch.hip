@@ -45,19 +45,18 @@ __device__ __forceinline__ uint64_t uniform_addr(const void *p)
 // record stays wavefront-uniform: with a request table the 16-bit map entry
 // arrives through a vector load and is made uniform again, and the record is
 // read through the constant address space (scalar loads).
-template <typename T>
+template <typename T, bool REQ>
 __device__ __forceinline__ BatchTile load_tile(const BatchArgs<T> &a, int tile, T **y, T **w)
 {
     const BatchTile *tp = a.tiles + tile;
-    int64_t voff = -1;
-    uint64_t yq = 0, wq = 0;
-    if (a.req_of_tile) {
+    int64_t voff = 0;
+    if constexpr (REQ) {
         const int r = __builtin_amdgcn_readfirstlane((int)a.req_of_tile[tile]);
         const BatchReq *q = a.reqs + r;
         tp = q->tiles + (tile - q->first);
         voff = q->vec_off;
-        yq = uniform_addr(q->y);
-        wq = uniform_addr(q->w);
+        *y = (T *)uniform_addr(q->y);
+        *w = (T *)uniform_addr(q->w);
     }
     const uint64_t tu = uniform_addr(tp);
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -67,10 +66,8 @@ __device__ __forceinline__ BatchTile load_tile(const BatchArgs<T> &a, int tile, 
     for (int i = 0; i < (int)(sizeof(BatchTile) / sizeof(u32x4)); ++i) parts[i] = src[i];
     BatchTile td;
     __builtin_memcpy(&td, parts, sizeof td);
-    if (voff >= 0) {
+    if constexpr (REQ) {
         td.vec_off = voff;
-        *y = (T *)yq;
-        *w = (T *)wq;
     } else {
         *y = a.y + td.vec_off;
         *w = a.w ? a.w + td.vec_off : nullptr;
@@ -78,33 +75,33 @@ __device__ __forceinline__ BatchTile load_tile(const BatchArgs<T> &a, int tile, 
     return td;
 }
 
-template <typename T, int BS, int TILE, int XW>
+template <typename T, int BS, int TILE, int XW, bool REQ>
 __device__ __forceinline__ void run_wave_tile(const BatchArgs<T> &a, int tile, double *sp, int *srp, T *xs)
 {
     T *y, *w;
-    const BatchTile td = load_tile(a, tile, &y, &w);
+    const BatchTile td = load_tile<T, REQ>(a, tile, &y, &w);
     const int32_t *rp = td.rp;
     const int32_t *ci = td.ci;
     const T *val = (const T *)td.val;
     const T *x = a.x + td.vec_off;
     switch (td.mode) {
     case 0:  // entries and rows fit the wavefront's LDS slice (guaranteed by the planner)
-        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, 0, 4, true>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1, td.k0, td.k1,
+        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1, td.k0, td.k1,
                                                       sp, srp);
         break;
     case 1:  // the same, x from the tile's window in LDS when it fits the kernel's room
-        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 4, true>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1,
+        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1,
                                                                  td.k0, td.k1, sp, srp, td.xlo,
                                                                  XW > 0 && td.xn <= XW ? td.xn : 0, xs);
         break;
     case 3:  // mode 1 with compact columns: ci holds each entry's byte offset in the window (which fits)
         if constexpr (XW > 0 && XW <= 256)
-            wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 1, true>(rp, ci, val, x, y, w, a.alpha, td.r0,
+            wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 1>(rp, ci, val, x, y, w, a.alpha, td.r0,
                                                                            td.r1, td.k0, td.k1, sp, srp, td.xlo,
                                                                            td.xn, xs);
         break;
     case 5:  // compact columns of a wider tile: two-byte offsets from xlo, x gathered from memory
-        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 2, true>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1,
+        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 2>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1,
                                                                        td.k0, td.k1, sp, srp, td.xlo, 0, xs);
         break;
     case 2: wave_group_rows<T, 2>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1); break;
@@ -116,7 +113,7 @@ __device__ __forceinline__ void run_wave_tile(const BatchArgs<T> &a, int tile, d
     }
 }
 
-template <typename T, int BS, int TILE, int XW>
+template <typename T, int BS, int TILE, int XW, bool REQ>
 __global__ __launch_bounds__(BS) void k_batch_grid(BatchArgs<T> a)
 {
     using WT = WaveTiles<T, BS, TILE>;
@@ -128,8 +125,8 @@ __global__ __launch_bounds__(BS) void k_batch_grid(BatchArgs<T> a)
     // runs of kXcdRunTiles tiles dealt to the XCDs in turn
     const int tile = xcd_chunk((int)blockIdx.x, ngroups, kXcdRunTiles / WT::NW) * WT::NW + wv;
     if (tile >= a.ntiles) return;
-    run_wave_tile<T, BS, TILE, XW>(a, tile, sp + wv * WT::ENTRIES, srp + wv * (kWaveTileRows + 1),
-                                   xs + wv * (XW > 0 ? XW : 1));
+    run_wave_tile<T, BS, TILE, XW, REQ>(a, tile, sp + wv * WT::ENTRIES, srp + wv * (kWaveTileRows + 1),
+                                        xs + wv * (XW > 0 ? XW : 1));
 }
 
 // Persistent form: a grid of bounded size (the host's persistent_cap), each
@@ -153,8 +150,8 @@ __global__ __launch_bounds__(BS) void k_batch_persistent(BatchArgs<T> a)
     for (int g = (int)blockIdx.x; g < ngroups; g += (int)gridDim.x) {
         const int tile = xcd_chunk(g, ngroups, kXcdRunTiles / WT::NW) * WT::NW + wv;
         if (tile < a.ntiles)
-            run_wave_tile<T, BS, TILE, XW>(a, tile, sp + wv * WT::ENTRIES, srp + wv * (kWaveTileRows + 1),
-                                           xs + wv * (XW > 0 ? XW : 1));
+            run_wave_tile<T, BS, TILE, XW, false>(a, tile, sp + wv * WT::ENTRIES, srp + wv * (kWaveTileRows + 1),
+                                                  xs + wv * (XW > 0 ? XW : 1));
     }
 }
 
@@ -225,17 +222,20 @@ int occ_batch()
 template <typename T, int BS, int TILE, int XW, int KIND>
 hipError_t L_batch(const void *p, dim3 g, hipStream_t s)
 {
-    if constexpr (KIND == 1)
+    if constexpr (KIND == kBatchPersistent)
         hipLaunchKernelGGL((k_batch_persistent<T, BS, TILE, XW>), g, dim3(BS), 0, s, *(const BatchArgs<T> *)p);
     else
-        hipLaunchKernelGGL((k_batch_grid<T, BS, TILE, XW>), g, dim3(BS), 0, s, *(const BatchArgs<T> *)p);
+        hipLaunchKernelGGL((k_batch_grid<T, BS, TILE, XW, KIND == kBatchRequests>), g, dim3(BS), 0, s,
+                           *(const BatchArgs<T> *)p);
     return hipGetLastError();
 }
 
 #define BENTRY(BS, TILE, XW)                                                                 \
     {BS, TILE, XW,                                                                           \
-     {{L_batch<float, BS, TILE, XW, 0>, L_batch<float, BS, TILE, XW, 1>},                    \
-      {L_batch<double, BS, TILE, XW, 0>, L_batch<double, BS, TILE, XW, 1>}},                 \
+     {{L_batch<float, BS, TILE, XW, kBatchGrid>, L_batch<float, BS, TILE, XW, kBatchPersistent>,    \
+       L_batch<float, BS, TILE, XW, kBatchRequests>},                                               \
+      {L_batch<double, BS, TILE, XW, kBatchGrid>, L_batch<double, BS, TILE, XW, kBatchPersistent>,  \
+       L_batch<double, BS, TILE, XW, kBatchRequests>}},                                             \
      {occ_batch<float, BS, TILE, XW>, occ_batch<double, BS, TILE, XW>}}
 
 // (threads per workgroup, LDS products per workgroup, LDS room for x per
