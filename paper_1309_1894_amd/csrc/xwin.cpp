@@ -61,7 +61,7 @@ spk_status build_xwin(spk_handle h, spk_mat *A, int64_t wc, XwinData &d)
         SPK_HIP(hipMemcpy(val.data(), A->val, vs * nnz, hipMemcpyDeviceToHost));
     }
     XwinHost hx;
-    switch (xwin_layout(m, A->ncols, nnz, A->rp_host.data(), ci.data(), val.data(), vs, wc, hx)) {
+    switch (xwin_layout(m, A->ncols, nnz, A->rp_host.data(), ci.data(), val.data(), vs, wc, hx, kXwinMark, kXwinSlack)) {
     case kXwinOk: break;
     case kXwinTooManyPairs: return fail(SPK_ERR_SHAPE, "too many (row, window) pairs for the x-window form");
     case kXwinTooManyWindows:
@@ -79,9 +79,7 @@ spk_status build_xwin(spk_handle h, spk_mat *A, int64_t wc, XwinData &d)
         if (e == hipSuccess && bytes) e = hipMemcpyAsync(*dst, src, bytes, hipMemcpyHostToDevice, h->work);
         return e;
     };
-    // the pairs' starts are marked in the column words; after the last entry,
-    // slack that a tile may read
-    for (int64_t p = 0; p < d.npairs; ++p) hx.ci[hx.ent[p]] |= kXwinMark;
+    // after the last entry, slack that a tile may read
     hx.ci.resize((size_t)(nnz + kXwinSlack), kXwinMark);
     hx.val.resize((size_t)(nnz + kXwinSlack) * vs, 0);
     hipError_t e = up((void **)&d.ci, hx.ci.data(), sizeof(uint16_t) * hx.ci.size());

@@ -52,9 +52,12 @@ struct XwinHost {
 // Regroups the entries of an m x n CSR matrix (values of vs bytes) by
 // windows of wc columns (wc <= 65536): pairs window-major, within a window
 // in row order; a pair's entries keep their order in the row.  Then the
-// row blocks of the second pass and their staging tables.
+// row blocks of the second pass and their staging tables.  A pair's first
+// entry has `start` set in its column word; ci and val keep room for `slack`
+// more entries, so that adding them moves nothing.
 inline XwinLayoutStatus xwin_layout(int64_t m, int64_t n, int64_t nnz, const int32_t *rp, const int32_t *ci,
-                                    const void *val, size_t vs, int64_t wc, XwinHost &d)
+                                    const void *val, size_t vs, int64_t wc, XwinHost &d, uint16_t start = 0,
+                                    int64_t slack = 0)
 {
     d = XwinHost();
     d.wc = wc;
@@ -79,6 +82,8 @@ inline XwinLayoutStatus xwin_layout(int64_t m, int64_t n, int64_t nnz, const int
     d.npairs = d.pair_off[d.nwin];
     if (d.npairs >= (int64_t)kBlkRowMask) return kXwinTooManyPairs;
     if (d.nwin > kXwinMaxWin) return kXwinTooManyWindows;
+    d.ci.reserve((size_t)(nnz + slack));
+    d.val.reserve((size_t)(nnz + slack) * vs);
     d.ci.assign((size_t)nnz, 0);
     d.val.assign((size_t)nnz * vs, 0);
     d.ent.assign((size_t)d.npairs + 1, 0);
@@ -93,15 +98,17 @@ inline XwinLayoutStatus xwin_layout(int64_t m, int64_t n, int64_t nnz, const int
         touched.clear();
         for (int64_t k = rp[i]; k < rp[i + 1]; ++k) {
             const int64_t w = ci[k] / wc;
+            uint16_t head = 0;
             if (mark[w] != i) {
                 mark[w] = i;
+                head = start;
                 const int64_t p = cur_pair[w]++;
                 pair_of[w] = p;
                 d.ent[p] = (int32_t)cur_ent[w];
                 touched.push_back(w);
             }
             const int64_t e = cur_ent[w]++;
-            d.ci[e] = (uint16_t)(ci[k] - w * wc);
+            d.ci[e] = (uint16_t)((ci[k] - w * wc) | head);
             memcpy(&d.val[(size_t)e * vs], vb + (size_t)k * vs, vs);
         }
         std::sort(touched.begin(), touched.end());
