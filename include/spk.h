@@ -153,8 +153,8 @@ typedef struct {
  * apply to an operation must be 0.
  *   format  spk_format (SpMV only)
  *   block   threads per workgroup (64..1024, power of two)
- *   group   SpMV VECTOR: lanes per row (2..64), or rows per wavefront (8..64)
- *           of the row stream (lds > 1); SELL: rows per slice
+ *   group   SpMV VECTOR: lanes per row (2..64), or of the row stream (lds > 1)
+ *           the rows per wavefront divided by `unroll`; SELL: rows per slice
  *   unroll  independent loads in flight per lane (1, 2, 4 or 8)
  *   vec     vector ops: elements per lane load (1, 2 or 4; at most 16 bytes);
  *           SpMV SCALAR/VECTOR: entries per value/index access (0 = one);

@@ -240,9 +240,12 @@ spk_variant default_variant(spk_handle h, const spk_problem &p, const spk_csr *c
     // wavefront, 73 entries: 20.0 against 14.4); and below 8,192 rows they
     // give the GPU more wavefronts.
     if (mean <= 80.0 && csr && csr->nrows >= 8192) {
-        const int rows[] = {64, 48, 32, 28, 24, 20, 16, 12, 8};   // the compiled ones
-        for (int r : rows) {
-            v.group = r;
+        // the compiled shapes: group * unroll = 64, 48, 32, 28, 24, 20, 16, 12, 8 rows
+        const int shapes[][2] = {{64, 1}, {16, 3}, {32, 1}, {4, 7}, {8, 3}, {4, 5}, {16, 1}, {4, 3}, {8, 1}};
+        for (const auto &sh : shapes) {
+            v.group = sh[0];
+            v.unroll = sh[1];
+            const int r = v.group * v.unroll;
             if (r * mean <= 500.0 && csr->nrows >= r * 8ll * h->num_cu) break;
         }
         v.lds = 512;
@@ -475,7 +478,7 @@ spk_status run_spmv(spk_handle h, const SpmvProblem &p, const spk_variant &v, hi
     // row over more than 2^24 rows) is run as consecutive launches.
     const int64_t unit = v.format == SPK_FMT_ADAPTIVE ? v.block / 64
                          : v.format != SPK_FMT_VECTOR ? v.block
-                         : v.lds > 1 ? v.block / 64 * v.group : v.block / v.group;
+                         : v.lds > 1 ? v.block / 64 * v.group * v.unroll : v.block / v.group;
     // (ADAPTIVE launches also hold a workgroup per long row of the range: half
     // the work-items are kept for those.)
     const int64_t span = kMaxLaunchItems / v.block / (v.format == SPK_FMT_ADAPTIVE ? 2 : 1) * unit;

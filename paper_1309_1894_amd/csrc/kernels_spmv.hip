@@ -459,8 +459,8 @@ hipError_t L_adaptive(const void *p, dim3 g, hipStream_t s)
 #define VECTOR(BS, G, U) {2, BS, G, U, 0, FN4(L_vector, BS, G, U, false, 1)}
 #define VECTOR_V(BS, G, U, V) {2, BS, G, U, 0, FN4(L_vector, BS, G, U, false, V), V}
 #define VECTOR_LDS(BS, G) {2, BS, G, 1, 1, FN4(L_vector, BS, G, 1, true, 1)}
-// row stream: `group` rows per wavefront, chunks of `lds` entries
-#define ROWS(BS, R, E) {2, BS, R, 1, E, FN4(L_rows, BS, R, E)}
+// row stream: `group` * `unroll` rows per wavefront, chunks of `lds` entries
+#define ROWS(BS, G, U, E) {2, BS, G, U, E, FN4(L_rows, BS, (G) * (U), E)}
 #define SELL(C, U) {3, 256, C, U, 0, FN4(L_sell, 256, C, U)}
 // lds = row-stream entries per wavefront tile; group = LDS room for x per
 // wavefront (1 = none)
@@ -501,8 +501,8 @@ const SpmvEntry kSpmv[] = {
     VECTOR_V(256, 4, 2, 2), VECTOR_V(256, 8, 2, 2), VECTOR_V(256, 16, 2, 2), VECTOR_V(256, 32, 2, 2),
     VECTOR_V(256, 64, 2, 2), VECTOR_V(256, 8, 4, 4), VECTOR_V(256, 16, 4, 4), VECTOR_V(256, 64, 4, 4),
     // row stream on the plain arrays
-    ROWS(256, 8, 512), ROWS(256, 12, 512), ROWS(256, 16, 512), ROWS(256, 20, 512), ROWS(256, 24, 512), ROWS(256, 28, 512),
-    ROWS(256, 32, 512), ROWS(256, 48, 512), ROWS(256, 64, 512),
+    ROWS(256, 8, 1, 512), ROWS(256, 4, 3, 512), ROWS(256, 16, 1, 512), ROWS(256, 4, 5, 512), ROWS(256, 8, 3, 512),
+    ROWS(256, 4, 7, 512), ROWS(256, 32, 1, 512), ROWS(256, 16, 3, 512), ROWS(256, 64, 1, 512),
     // row blocks with two-byte columns
     ADAPT_C16(64, 256), ADAPT_C16(64, 512), ADAPT_C16(64, 1024), ADAPT_C16(128, 256), ADAPT_C16(128, 512),
     ADAPT_C16(256, 256), ADAPT_C16(256, 512), ADAPT_C16(512, 256),

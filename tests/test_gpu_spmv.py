@@ -487,12 +487,13 @@ def test_borrowed_csr_default_on_both_sides_of_its_rules(spk, dev, m, mean, dt):
 
 
 @pytest.mark.parametrize("dt", [1, 0])
-@pytest.mark.parametrize("rows", [8, 12, 16, 20, 24, 28, 32, 48, 64])
+@pytest.mark.parametrize("group,unroll", [(8, 1), (4, 3), (16, 1), (4, 5), (8, 3), (4, 7), (32, 1), (16, 3), (64, 1)])
 @pytest.mark.parametrize("mean", [1, 19, 70])
-def test_row_stream_shapes(spk, dev, rows, mean, dt):
+def test_row_stream_shapes(spk, dev, group, unroll, mean, dt):
     """Every row stream shape (rows per wavefront, powers of two or not) on
     rows that leave the last wavefront ragged, empty rows, rows longer than a
     chunk, and chunks that end at and inside a row.  Integer data: exact."""
+    rows = group * unroll
     m = 37 * rows + rows // 2 + 1
     rng = np.random.default_rng(rows * 100 + mean)
     lens = rng.integers(0, 2 * mean + 1, m)
@@ -508,7 +509,7 @@ def test_row_stream_shapes(spk, dev, rows, mean, dt):
     try:
         xd = torch.from_numpy(x).to(dev)
         y = torch.full((m + 64,), float("nan"), dtype=xd.dtype, device=dev)
-        v = spk.make_variant(format=2, block=256, group=rows, unroll=1, lds=512, streams=1)
+        v = spk.make_variant(format=2, block=256, group=group, unroll=unroll, lds=512, streams=1)
         spk.spk_run(spk.problem(spk.SPK_OP_SPMV, A=M, x=xd, y=y[:m]), v)
         got = y.cpu().numpy()
         assert np.array_equal(got[:m], ref) and np.all(np.isnan(got[m:]))
