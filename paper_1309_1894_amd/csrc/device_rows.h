@@ -193,77 +193,76 @@ __device__ __forceinline__ double wave_stream(const int32_t *rp_, const int32_t 
     for (int q = 0; q < 3; ++q)
         if (l + q * kWave <= nr) srp[l + q * kWave] = rpv[q];
     wave_lds_sync();
+    double dot = 0.0;
+    const auto put = [&](int q, double sum) {   // the lane's row q
+        const int i = l + q * kWave;
+        const T yt = (T)sum;
+        __builtin_nontemporal_store(yt, y + r0 + i);
+        if (w) __builtin_nontemporal_store(fma_t(alpha, yt, xo[q]), w + r0 + i);
+        if constexpr (DOT) dot = fma_t((double)xo[q], (double)yt, dot);
+    };
     // one lane per row of up to kLaneRowMax entries: four interleaved partial
-    // sums, four LDS reads in flight
-    double sum[2] = {0.0, 0.0};
-    unsigned long long wide[2];
+    // sums, four LDS reads in flight.  (Wider rows wait in a flag: a ballot per
+    // half and the sums kept until after it cost tiles of short rows 5%.)
+    int wide = 0;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const int i = l + q * kWave;
-        int s = 0, e = 0;
         if (i < nr) {
-            s = srp[i];
-            e = srp[i + 1];
-        }
-        wide[q] = __ballot(e - s > kLaneRowMax);
-        if (e - s <= kLaneRowMax) {
-            double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-            int k = s;
-            for (; k + 3 < e; k += 4) {
-                a0 += sp[k];
-                a1 += sp[k + 1];
-                a2 += sp[k + 2];
-                a3 += sp[k + 3];
+            const int s = srp[i], e = srp[i + 1];
+            if (e - s > kLaneRowMax) {
+                wide |= 1 << q;
+            } else {
+                double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+                int k = s;
+                for (; k + 3 < e; k += 4) {
+                    a0 += sp[k];
+                    a1 += sp[k + 1];
+                    a2 += sp[k + 2];
+                    a3 += sp[k + 3];
+                }
+                if (k < e) a0 += sp[k];
+                if (k + 1 < e) a1 += sp[k + 1];
+                if (k + 2 < e) a2 += sp[k + 2];
+                put(q, (a0 + a1) + (a2 + a3));
             }
-            if (k < e) a0 += sp[k];
-            if (k + 1 < e) a1 += sp[k + 1];
-            if (k + 2 < e) a2 += sp[k + 2];
-            sum[q] = (a0 + a1) + (a2 + a3);
         }
     }
     // wider rows: 16 lanes each, four rows at a time; a row's own lane takes
     // the sum
+    if (__builtin_expect(__any(wide != 0), 0)) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        unsigned long long left = wide[q];
-        while (__builtin_expect(left != 0, 0)) {
-            int row[4];
+        for (int q = 0; q < 2; ++q) {
+            unsigned long long left = __ballot((wide >> q) & 1);
+            while (left != 0) {
+                int row[4];
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                row[g] = left ? __builtin_ctzll(left) : row[0];
-                left &= left - 1;
+                for (int g = 0; g < 4; ++g) {
+                    row[g] = left ? __builtin_ctzll(left) : -1;
+                    left &= left - 1;
+                }
+                const int g = l >> 4;
+                const int own = g == 0 ? row[0] : g == 1 ? row[1] : g == 2 ? row[2] : row[3];
+                const int i = q * kWave + (own < 0 ? row[0] : own);
+                const int e = srp[i + 1];
+                int k = srp[i] + (l & 15);
+                double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+                for (; k + 48 < e; k += 64) {
+                    a0 += sp[k];
+                    a1 += sp[k + 16];
+                    a2 += sp[k + 32];
+                    a3 += sp[k + 48];
+                }
+                if (k < e) a0 += sp[k];
+                if (k + 16 < e) a1 += sp[k + 16];
+                if (k + 32 < e) a2 += sp[k + 32];
+                const double t = group_sum<16>((a0 + a1) + (a2 + a3));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double tu = readlane_f64(t, 16 * u);
+                    if (l == row[u]) put(q, tu);
+                }
             }
-            const int g = l >> 4;
-            const int i = q * kWave + (g == 0 ? row[0] : g == 1 ? row[1] : g == 2 ? row[2] : row[3]);
-            const int e = srp[i + 1];
-            int k = srp[i] + (l & 15);
-            double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-            for (; k + 48 < e; k += 64) {
-                a0 += sp[k];
-                a1 += sp[k + 16];
-                a2 += sp[k + 32];
-                a3 += sp[k + 48];
-            }
-            if (k < e) a0 += sp[k];
-            if (k + 16 < e) a1 += sp[k + 16];
-            if (k + 32 < e) a2 += sp[k + 32];
-            const double t = group_sum<16>((a0 + a1) + (a2 + a3));
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const double tu = readlane_f64(t, 16 * u);
-                if (l == row[u]) sum[q] = tu;
-            }
-        }
-    }
-    double dot = 0.0;
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int i = l + q * kWave;
-        if (i < nr) {
-            const T yt = (T)sum[q];
-            __builtin_nontemporal_store(yt, y + r0 + i);
-            if (w) __builtin_nontemporal_store(fma_t(alpha, yt, xo[q]), w + r0 + i);
-            if constexpr (DOT) dot = fma_t((double)xo[q], (double)yt, dot);
         }
     }
     wave_lds_sync();
