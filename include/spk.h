@@ -706,8 +706,9 @@ spk_status spk_serve_add_matrix(spk_server s, const spk_csr *A, int32_t *id);
  * 128 KiB or more whose three buffers (two without w) are each inside one
  * pinned host allocation (hipHostMalloc), aligned to their type, move between
  * those buffers and the device without the server's staging copies: x by a
- * copy kernel and y, w written by the tile kernel, from 512 KiB on by the copy
- * engines. */
+ * copy kernel and y, w written by the tile kernel, from 512 KiB on, or where
+ * the memory is not known to be coherent (flags other than the portable and
+ * mapped ones, without the coherent one), by the copy engines. */
 spk_status spk_serve_submit(spk_server s, int32_t mat_id, const void *x, void *y, void *w,
                             int64_t *req);
 

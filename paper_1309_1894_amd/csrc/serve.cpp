@@ -138,7 +138,7 @@ struct Request {
 struct Flight {
     std::vector<std::pair<int64_t, Request>> reqs;
     std::vector<int64_t> off;   // vector offset of each request
-    std::vector<char> direct;   // its vectors move between the caller's pinned buffers and the device
+    std::vector<char> direct;   // how each request's vectors travel (kStaged, kDirectCopy, kDirect)
     void *dev = nullptr, *pin = nullptr;
     size_t y_off = 0, w_off = 0;
     int64_t vec_bytes = 0;
@@ -330,27 +330,40 @@ constexpr size_t kDirectMin = 128 << 10;
 // and 85.
 constexpr size_t kEngineMin = 512 << 10;
 
-// Whether [p, p + n) lies inside one pinned host allocation of the HIP
-// runtime (hipHostMalloc), at that address for the device too, and aligned to
-// the vector's type (`align` bytes).  Pageable memory, or a pointer the
-// runtime does not know, is not.
-bool pinned_range(const void *p, size_t n, size_t align)
+// How a vector in the caller's memory travels.
+enum : char {
+    kStaged = 0,       // through the staging block
+    kDirectCopy = 1,   // straight, by the copy engines
+    kDirect = 2        // straight, by kernels (long ones by the copy engines)
+};
+
+// The way for [p, p + n): straight when it lies inside one pinned host
+// allocation of the HIP runtime (hipHostMalloc), at that address for the
+// device too, and aligned to the vector's type (`align` bytes); pageable
+// memory, or a pointer the runtime does not know, is staged.  Kernels touch
+// coherent memory only: what they write elsewhere may stay in the GPU's caches
+// past the launch's event, which releases to the device, not to the host (and
+// flags other than the portable and mapped ones do not promise coherence).
+char pinned_range(const void *p, size_t n, size_t align)
 {
-    if ((uintptr_t)p % align != 0) return false;
+    if ((uintptr_t)p % align != 0) return kStaged;
     hipPointerAttribute_t a{};
     if (hipPointerGetAttributes(&a, p) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return kStaged;
     }
-    if (a.type != hipMemoryTypeHost || a.devicePointer != p) return false;
+    if (a.type != hipMemoryTypeHost || a.devicePointer != p) return kStaged;
     hipDeviceptr_t base = nullptr;
     size_t size = 0;
     if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)const_cast<void *>(p)) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return kStaged;
     }
     const uintptr_t b = (uintptr_t)base, q = (uintptr_t)p;
-    return q >= b && q + n <= b + size;
+    if (q < b || q + n > b + size) return kStaged;
+    const bool coherent = (a.allocationFlags & ~(hipHostMallocPortable | hipHostMallocMapped)) == 0 ||
+                          (a.allocationFlags & hipHostMallocCoherent) != 0;
+    return coherent ? kDirect : kDirectCopy;
 }
 
 // One direction of a launch's copies: segments gathered into copy kernels,
@@ -360,10 +373,10 @@ struct SegmentCopy {
     hipStream_t s;
     CopySegs c{};
 
-    spk_status add(void *dst, const void *src, size_t bytes)
+    spk_status add(void *dst, const void *src, size_t bytes, bool engine = false)
     {
         if (bytes == 0) return SPK_OK;
-        if (bytes >= kEngineMin) {
+        if (engine || bytes >= kEngineMin) {
             SPK_HIP(hipMemcpyAsync(dst, src, bytes, in ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost, s));
             return SPK_OK;
         }
@@ -402,14 +415,17 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
         const Request &R = group[k].second;
         const PoolMat &M = S->mats[R.mat];
         const size_t nb = vs * (size_t)M.m;
-        F.direct[k] = nb >= kDirectMin && pinned_range(R.x, nb, vs) && pinned_range(R.y, nb, vs) &&
-                      (!R.w || pinned_range(R.w, nb, vs));
+        if (nb >= kDirectMin) {
+            F.direct[k] = pinned_range(R.x, nb, vs);
+            if (F.direct[k]) F.direct[k] = std::min(F.direct[k], pinned_range(R.y, nb, vs));
+            if (F.direct[k] && R.w) F.direct[k] = std::min(F.direct[k], pinned_range(R.w, nb, vs));
+        }
         if (!F.direct[k]) staged += M.m;
     }
     F.off.assign(group.size(), 0);
     for (int pass = 0; pass < 2; ++pass)
         for (size_t k = 0; k < group.size(); ++k)
-            if ((bool)F.direct[k] == (pass == 1)) {
+            if ((F.direct[k] != kStaged) == (pass == 1)) {
                 F.off[k] = total;
                 total += S->mats[group[k].second.mat].m;
             }
@@ -438,7 +454,7 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
     for (size_t k = 0; batched && k < group.size(); ++k) {
         const Request &R = group[k].second;
         const size_t at = vs * (size_t)F.off[k];
-        engine_out[k] = vs * (size_t)S->mats[R.mat].m >= kEngineMin;
+        engine_out[k] = F.direct[k] == kDirectCopy || vs * (size_t)S->mats[R.mat].m >= kEngineMin;
         char *to_y = F.direct[k] ? (char *)R.y : pin + F.y_off + at;
         char *to_w = F.direct[k] ? (char *)R.w : pin + F.w_off + at;
         rq[k].y = engine_out[k] ? dev + F.y_off + at : to_y;
@@ -489,13 +505,13 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
     for (size_t k = 0; k < group.size(); ++k)
         if (F.direct[k])
             SPK_TRY(to_dev.add(dev + head_b + vs * F.off[k], group[k].second.x,
-                               vs * (size_t)S->mats[group[k].second.mat].n));
+                               vs * (size_t)S->mats[group[k].second.mat].n, F.direct[k] == kDirectCopy));
     SPK_TRY(to_dev.flush());
     F.t_enqueued = now_seconds();
     {
         std::lock_guard<std::mutex> lk(S->mu);
         S->stage_in_s += F.t_enqueued - t_stage;
-        S->direct += (int64_t)std::count(F.direct.begin(), F.direct.end(), (char)1);
+        S->direct += (int64_t)group.size() - (int64_t)std::count(F.direct.begin(), F.direct.end(), (char)kStaged);
     }
     const void *x = dev + head_b;
     void *y = dev + F.y_off;
@@ -520,8 +536,9 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
         if (!engine_out[k]) continue;
         const Request &R = group[k].second;
         const size_t nb = vs * (size_t)S->mats[R.mat].m, at = vs * (size_t)F.off[k];
-        SPK_TRY(to_host.add(F.direct[k] ? (char *)R.y : pin + F.y_off + at, dev + F.y_off + at, nb));
-        if (R.w) SPK_TRY(to_host.add(F.direct[k] ? (char *)R.w : pin + F.w_off + at, dev + F.w_off + at, nb));
+        const bool engine = F.direct[k] == kDirectCopy;
+        SPK_TRY(to_host.add(F.direct[k] ? (char *)R.y : pin + F.y_off + at, dev + F.y_off + at, nb, engine));
+        if (R.w) SPK_TRY(to_host.add(F.direct[k] ? (char *)R.w : pin + F.w_off + at, dev + F.w_off + at, nb, engine));
     }
     SPK_TRY(to_host.flush());
     F.done = take_event(S);

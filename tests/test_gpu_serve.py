@@ -317,3 +317,45 @@ def test_serve_copies_at_their_size_limits(spk, dev, dt, mode):
         if i % 5 == 4:
             ws[i] = O.waxpy(0.5, np.array(ys[i]), np.array(xs[i]))
         _check(pool[m], np.array(xs[i]), np.array(ys[i]), np.array(ws[i]))
+
+
+@pytest.mark.parametrize("flags", [0x0, 0x1, 0x2, 0x4, 0x40000000, 0x80000000],
+                         ids=["default", "portable", "mapped", "write-combined", "coherent", "non-coherent"])
+def test_serve_pinned_buffers_of_every_kind(spk, dev, flags):
+    """Pinned buffers of each kind hipHostMalloc gives, used round after round
+    with new x: non-coherent memory may sit in the GPU's caches after a kernel
+    has touched it, so results and inputs must reach the other side whatever
+    moves them.  Every round against the oracle."""
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so")
+    hip.hipHostMalloc.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_size_t, ctypes.c_uint]
+    hip.hipHostFree.argtypes = [ctypes.c_void_p]
+    sizes = [(128 << 10) // 8, 20001, (512 << 10) // 8 - 1, 70001]
+    pool = [I.banded(m, 1 + i, 1.0, seed_struct=150, seed_val=151 + i) for i, m in enumerate(sizes)]
+    held = []
+
+    def pinned(n):
+        p = ctypes.c_void_p()
+        assert hip.hipHostMalloc(ctypes.byref(p), 8 * n, flags) == 0
+        held.append(p)
+        return np.frombuffer((ctypes.c_char * (8 * n)).from_address(p.value), np.float64)
+
+    say(f"serve pinned flags {flags:#x}")
+    srv = spk.Server(streams=2, max_inflight=16, max_batch=4, mode=0, alpha=0.5)
+    try:
+        ids = [srv.add_matrix(A) for A in pool]
+        bufs = [tuple(pinned(m) for _ in range(3)) for m in sizes]
+        for rnd in range(6):
+            for i, (x, y, w) in enumerate(bufs):
+                x[:] = I.uniform(160 + rnd, i, x.size)
+                y[:], w[:] = np.nan, np.nan
+                srv.submit(ids[i], x, y, w)
+            srv.drain()
+            for i, (x, y, w) in enumerate(bufs):
+                _check(pool[i], np.array(x), np.array(y), np.array(w))
+        assert srv.stats()["completed"] == 6 * len(sizes)
+    finally:
+        srv.close()
+        del bufs
+        for p in held:
+            hip.hipHostFree(p)
