@@ -23,6 +23,8 @@
 //            own tile, with no workgroup barrier.
 // Products are formed and accumulated in FP64 (FP32 operands are widened
 // first, so their products are exact) and each output is rounded once.
+#include <type_traits>
+
 #include "device_common.h"
 #include "device_rows.h"
 #include "kernels.h"
@@ -157,14 +159,20 @@ __global__ __launch_bounds__(BS) void k_spmv_vector(SpmvArgs<T> a)
 // the products go to the wavefront's LDS slice, and G lanes (a power of two,
 // R*G <= 64) add each row's part of the chunk; a row with more than 32*G
 // entries in a chunk is added by all 64 lanes.  Bound by memory latency (row
-// offsets, then entries, then x): a chunk's loads all go out before the first
-// is used, the next chunk's while this one's products are added, and the
-// columns are ordinary loads (a chunk's end lines are its neighbours' too).
-// 600,000 rows of 19.8 entries, FP64: 39.0 us at the best R without these, 30.7
-// with (4.8 TB/s; 16 lanes per row and no LDS 75.6); 200,003 rows 14.2 and
-// 13.0; 300,000 rows of 39 entries 37.8 and 29.5.
+// offsets, then entries, then x): a chunk's columns are loaded while the last
+// one's products are added, its values and then all its x entries go out
+// before the first is used, without branches between them (lanes past the end
+// take the last entry again; a chunk with few entries left runs a shorter
+// form).  With a test per 64 entries each gather was waited for alone, and a
+// run that holds a row of thousands outlived the others: 60,000 rows of
+// truncated-Zipf length (FP64) 57.2 us and 22.6, 300,001 92.8 and 48.9 (32 lanes
+// per row 50.3 and 85.2), 200,003 rows of 19.8 entries 12.9 and 10.4, 600,000
+// 31.2 and 28.5, in FP32 25.8 and 20.6 (16 lanes per row and no LDS 75.8 and
+// 63.6).  The columns are ordinary loads (a chunk's end lines are its
+// neighbours' too).  Seven wavefronts per SIMD: the bound keeps the registers
+// at 68, without it they are 72.
 template <typename T, int BS, int R, int E, bool FUSED, bool KEEP>
-__global__ __launch_bounds__(BS) void k_spmv_rows(SpmvArgs<T> a)
+__global__ __launch_bounds__(BS, 7) void k_spmv_rows(SpmvArgs<T> a)
 {
     constexpr int NW = BS / kWave;
     constexpr int G = kWave / R >= 8 ? 8 : kWave / R >= 4 ? 4 : kWave / R >= 2 ? 2 : 1;   // R * G <= 64
@@ -186,27 +194,40 @@ __global__ __launch_bounds__(BS) void k_spmv_rows(SpmvArgs<T> a)
     const int k0 = __builtin_amdgcn_readlane(s, 0);
     const int k1 = __builtin_amdgcn_readlane(e, kWave - 1);
     int c[ITEMS];
-    T v[ITEMS];
-    const auto load = [&](int kb) {
+    const auto load_columns = [&](int kb, auto n) {
         const int last = k1 - 1 - kb;      // last entry of the rows, from the chunk's first
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j)
-            if (j * kWave <= last) c[j] = ci[kb + min(l + j * kWave, last)];
+        for (int j = 0; j < n.value; ++j) c[j] = ci[kb + min(l + j * kWave, last)];
+    };
+    // (products of entries past the last land where no sum reads)
+    const auto products = [&](int kb, auto n) {
+        const int last = k1 - 1 - kb;
+        T v[n.value], xv[n.value];
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j)
-            if (j * kWave <= last) {
-                const gptr<T> at = val + kb + min(l + j * kWave, last);
-                v[j] = KEEP ? *at : __builtin_nontemporal_load(at);
-            }
+        for (int j = 0; j < n.value; ++j) {
+            const gptr<T> at = val + kb + min(l + j * kWave, last);
+            v[j] = KEEP ? *at : __builtin_nontemporal_load(at);
+        }
+#pragma unroll
+        for (int j = 0; j < n.value; ++j) xv[j] = x[c[j]];
+#pragma unroll
+        for (int j = 0; j < n.value; ++j) sp[l + j * kWave] = (double)v[j] * (double)xv[j];
+    };
+    constexpr std::integral_constant<int, ITEMS> all{};
+    constexpr std::integral_constant<int, ITEMS / 2> few{};
+    constexpr std::integral_constant<int, ITEMS / 4> fewer{};
+    const auto load = [&](int kb) {
+        if (k1 - kb > E / 2) load_columns(kb, all);
+        else if (k1 - kb > E / 4) load_columns(kb, few);
+        else load_columns(kb, fewer);
     };
     if (k0 < k1) load(k0);
     double acc = 0.0;
     for (int64_t kb64 = k0; kb64 < k1; kb64 += E) {
         const int kb = (int)kb64;
-        const int last = k1 - 1 - kb;
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j)
-            if (j * kWave <= last) sp[l + j * kWave] = (double)v[j] * (double)x[c[j]];
+        if (k1 - kb > E / 2) products(kb, all);
+        else if (k1 - kb > E / 4) products(kb, few);
+        else products(kb, fewer);
         wave_lds_sync();
         if (kb64 + E < k1) load(kb + E);   // while this chunk's products are added
         const int lo = max(s - kb, 0), hi = min(e - kb, E);

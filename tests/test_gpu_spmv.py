@@ -547,3 +547,44 @@ def test_matrices_on_both_sides_of_the_cache_rule(spk, dev, extra, dt):
         assert np.array_equal(y.cpu().numpy(), ref.astype(NP[dt]))
     finally:
         M.release()
+
+
+@pytest.mark.parametrize("dt", [1, 0])
+@pytest.mark.parametrize("left", [1, 64, 127, 128, 129, 255, 256, 257, 511, 512, 513, 640, 641, 768, 769, 1025])
+def test_row_stream_chunk_tails(spk, dev, left, dt):
+    """The row stream's chunks have forms for at most 128, at most 256 and more
+    entries: wavefronts whose rows hold `left` entries, as one row among empty
+    ones or spread over all, every shape, plain and fused.  Integer data: sums
+    are exact, so the outputs are compared bit for bit."""
+    rng = np.random.default_rng(left)
+    for rows in (8, 12, 16, 20, 24, 28, 32, 48, 64):
+        runs = []
+        for i in range(40):
+            n = np.zeros(rows, np.int64)
+            if i % 2:
+                n[rng.integers(rows)] = left
+            else:
+                n += np.bincount(rng.integers(0, rows, left), minlength=rows)
+            runs.append(n)
+        lens = np.concatenate(runs)
+        m = lens.size
+        rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        A = I.CSR(m, m, rp, rng.integers(0, m, rp[-1]).astype(np.int32), rng.integers(-8, 9, rp[-1]).astype(NP[dt]))
+        x = rng.integers(-8, 9, m).astype(NP[dt])
+        ref, _ = O.spmv(A, x)
+        say(f"row stream chunk tails left={left} rows={rows} dtype={dt}")
+        M = spk.Matrix(A)
+        xd = torch.from_numpy(x).to(dev)
+        y, w = torch.full_like(xd, float("nan")), torch.full_like(xd, float("nan"))
+        try:
+            g, u = {8: (8, 1), 12: (4, 3), 16: (16, 1), 20: (4, 5), 24: (8, 3), 28: (4, 7), 32: (32, 1), 48: (16, 3),
+                    64: (64, 1)}[rows]
+            v = spk.make_variant(format=spk.SPK_FMT_VECTOR, block=256, group=g, unroll=u, lds=512, streams=1)
+            spk.spk_run(spk.problem(spk.SPK_OP_SPMV, A=M, x=xd, y=y), v)
+            assert np.array_equal(y.cpu().numpy(), ref.astype(NP[dt]))
+            y.fill_(float("nan"))
+            spk.spk_run(spk.problem(spk.SPK_OP_SPMV_WAXPY, A=M, x=xd, y=y, w=w, alpha=0.5), v)
+            assert np.array_equal(y.cpu().numpy(), ref.astype(NP[dt]))
+            assert np.array_equal(w.cpu().numpy(), (0.5 * ref + x).astype(NP[dt]))
+        finally:
+            M.release()
