@@ -588,3 +588,42 @@ def test_row_stream_chunk_tails(spk, dev, left, dt):
             assert np.array_equal(w.cpu().numpy(), (0.5 * ref + x).astype(NP[dt]))
         finally:
             M.release()
+
+
+@pytest.mark.parametrize("length", [8, 16, 20, 39, 60, 79])
+def test_borrowed_csr_is_as_accurate_as_lanes_per_row(spk, dev, length):
+    """FP64 products of a borrowed CSR (the row stream rounds a product before
+    it adds it) have no larger rms error than one lane per entry and a tree
+    (G lanes per row), both against sums in 80-bit floats."""
+    m = 40000
+    rng = np.random.default_rng(length)
+    ci = np.sort(rng.integers(0, m, (m, length)), axis=1).astype(np.int32)
+    val, x = rng.random((m, length)) * 2 - 1, rng.random(m) * 2 - 1
+    # products exactly (Dekker's split), summed in 80 bits
+    def split(v):
+        t = 134217729.0 * v
+        hi = t - (t - v)
+        return hi, v - hi
+    xs = x[ci]
+    (vh, vl), (xh, xl) = split(val), split(xs)
+    p = val * xs
+    e = ((vh * xh - p) + vh * xl + vl * xh) + vl * xl
+    exact = p.astype(np.longdouble).sum(1) + e.astype(np.longdouble).sum(1)
+    A = I.CSR(m, m, (np.arange(m + 1) * length).astype(np.int32), ci.ravel(), val.ravel())
+    say(f"accuracy of the borrowed CSR product, rows of {length}")
+    xd = torch.from_numpy(x).to(dev)
+
+    def rms(y):
+        return float(np.sqrt(np.mean((y.cpu().numpy().astype(np.longdouble) - exact) ** 2)))
+
+    stream = rms(spk.spk_spmv_csr(*spk.to_device_csr(A, dev), xd))
+    M = spk.Matrix(A)
+    try:
+        g = min(64, 1 << (length - 1).bit_length())
+        y = torch.empty_like(xd)
+        v = spk.make_variant(format=spk.SPK_FMT_VECTOR, block=256, group=g, unroll=1, streams=1)
+        spk.spk_run(spk.problem(spk.SPK_OP_SPMV, A=M, x=xd, y=y), v)
+        lanes = rms(y)
+    finally:
+        M.release()
+    assert stream <= lanes, (stream, lanes)
