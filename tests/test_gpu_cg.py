@@ -425,3 +425,52 @@ def test_cg_default_of_a_grid_stencil(spk, dev, name):
         M.release()
     finally:
         H.close()
+
+
+def test_cg_one_workgroup_is_as_accurate_as_three_kernels(spk, dev):
+    """The residual history of the one-workgroup solve is no further from a
+    solve in 80-bit floats than that of the three-kernel form: the ratio of
+    their errors, over five systems and 20 right-hand sides each, has a
+    geometric mean within its sampling error (5%, twice that allowed) of one
+    or below."""
+    L = np.longdouble
+
+    def exact(A, b, iters):
+        v, rp = A.val.astype(L), A.row_ptr
+
+        def mul(p):
+            return np.add.reduceat(v * p[A.col_idx], rp[:-1])   # no row is empty
+        r = b.astype(L)
+        p, rr = r.copy(), [(r * r).sum()]
+        for _ in range(iters):
+            q = mul(p)
+            r = r - rr[-1] / (p * q).sum() * q
+            rr.append((r * r).sum())
+            p = r + rr[-1] / rr[-2] * p
+        return np.array(rr)
+
+    ratios = []
+    for A, iters in ((I.lap2d(40), 40), (I.lap2d(48), 50), (I.lap2d(63), 40), (I.lap3d(14), 25), (I.lap3d(15), 30)):
+        say(f"accuracy of the one-workgroup solve: {A.nrows} rows")
+        one, three = spk.Handle(0), spk.Handle(0)
+        mats = [spk.Matrix(A, handle=h) for h in (one, three)]
+        x = torch.empty(A.nrows, dtype=torch.float64, device=dev)
+        key = spk.spk_class_key(spk.problem(spk.SPK_OP_SPMV, A=mats[1], x=x, y=x), three)
+        spk.spk_plan_put("cg:" + key, spk.make_variant(format=spk.SPK_FMT_ADAPTIVE, block=512, group=1, unroll=1,
+                                                       streams=1, lds=512), three)
+        err = [0.0, 0.0]
+        try:
+            for seed in range(20):
+                b = I.uniform(170, seed, A.nrows)
+                ref = exact(A, b, iters)
+                for k, M in enumerate(mats):
+                    hist = torch.empty(iters + 1, dtype=torch.float64, device=dev)
+                    x.zero_()
+                    spk.spk_cg(M, torch.from_numpy(b).to(dev), x, iters, hist)
+                    err[k] += float(np.sqrt(np.mean(((hist.cpu().numpy() - ref) / ref) ** 2)))
+        finally:
+            for M, h in zip(mats, (one, three)):
+                M.release()
+                h.close()
+        ratios.append(err[0] / err[1])
+    assert np.exp(np.mean(np.log(ratios))) <= 1.1, ratios
