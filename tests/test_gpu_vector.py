@@ -220,3 +220,41 @@ def test_waxpy_default_on_both_sides_of_the_narrow_rule(spk, dev, extra, dt):
             assert torch.equal(got, ref)
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("n", [1_000_003, 50_000_017, 100_000_000])
+def test_dot_rounds_no_more_on_a_long_walk(spk, dev, n):
+    """1 . 0.1, where every rounding can be counted: a pass's four products add
+    up exactly, a lane's passes with their errors kept (one rounding), then
+    the wavefront's six levels, the workgroup's three, and the same nine over
+    the partials: at most 19 units of 2^-53 of the sum, and one for a ragged
+    pass.  (One chain per access rounds once an element: 100 of them end 20 to
+    100 units off.)"""
+    from fractions import Fraction
+    say(f"dot of a constant n={n}")
+    x = torch.ones(n, dtype=torch.float64, device=dev)
+    y = torch.full_like(x, 0.1)
+    d = Fraction(spk.spk_dot(x, y, torch.empty(1, dtype=torch.float64, device=dev)).item())
+    exact = n * Fraction(0.1)
+    assert abs(d - exact) <= 20 * exact / 2 ** 53, float((d - exact) / exact * 2 ** 53)
+
+
+@pytest.mark.parametrize("dt", [1, 0])
+def test_dot_of_values_without_an_error(spk, dev, dt):
+    """Infinities, NaN and sums that overflow give what a plain sum gives, on
+    a lane's first pass and on a later one."""
+    big = 1e308 if dt else 3e38
+    n = 3_000_001
+    for at in (5, n - 1):
+        for v, other, expect in (([np.inf], 1.0, np.inf), ([-np.inf], 1.0, -np.inf), ([np.nan], 1.0, np.nan),
+                                 ([np.inf, -np.inf], 1.0, np.nan), ([big, big], 10.0, np.inf if dt else 6e39),
+                                 ([np.inf], 0.0, np.nan)):
+            say(f"dot special values {v} at {at} dtype={dt}")
+            x = torch.zeros(n, dtype=torch.float64 if dt else torch.float32, device=dev)
+            y = torch.full_like(x, other)
+            for k, q in enumerate(v):
+                x[at - k] = q
+            d = spk.spk_dot(x, y, torch.empty(1, dtype=torch.float64, device=dev)).item()
+            if not dt and np.isfinite(expect):
+                expect = float(x.double().sum().item() * other)
+            assert (np.isnan(d) and np.isnan(expect)) or d == expect, (v, other, d)
