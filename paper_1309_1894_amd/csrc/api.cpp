@@ -479,9 +479,7 @@ spk_status run_spmv(spk_handle h, const SpmvProblem &p, const spk_variant &v, hi
     const int64_t unit = v.format == SPK_FMT_ADAPTIVE ? v.block / 64
                          : v.format != SPK_FMT_VECTOR ? v.block
                          : v.lds > 1 ? v.block / 64 * v.group * v.unroll : v.block / v.group;
-    // (ADAPTIVE launches also hold a workgroup per long row of the range: half
-    // the work-items are kept for those.)
-    const int64_t span = kMaxLaunchItems / v.block / (v.format == SPK_FMT_ADAPTIVE ? 2 : 1) * unit;
+    const int64_t cap = kMaxLaunchItems / v.block;   // workgroups
 
     auto launch_range = [&](int64_t lo, int64_t hi, hipStream_t st) -> spk_status {
         union {
@@ -526,8 +524,11 @@ spk_status run_spmv(spk_handle h, const SpmvProblem &p, const spk_variant &v, hi
         return SPK_OK;
     };
     auto launch_piece = [&](int i, hipStream_t st) -> spk_status {
-        for (int64_t lo = cut[i]; lo < cut[i + 1]; lo += span)
-            SPK_TRY(launch_range(lo, std::min(cut[i + 1], lo + span), st));
+        for (int64_t lo = cut[i], hi; lo < cut[i + 1]; lo = hi) {
+            // (ADAPTIVE launches also hold a workgroup per long row)
+            hi = bd ? row_tile_range(bd->longs, lo, cut[i + 1], unit, cap) : std::min(cut[i + 1], lo + cap * unit);
+            SPK_TRY(launch_range(lo, hi, st));
+        }
         return SPK_OK;
     };
 

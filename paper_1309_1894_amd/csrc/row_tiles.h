@@ -120,4 +120,23 @@ inline void make_row_tiles(const int32_t *rp, int64_t m, int E, int BS, std::vec
     out_k.push_back(rp[m]);
 }
 
+// End of the longest range of tiles from `lo` on that one launch of at most
+// `cap` (two or more) workgroups runs: a workgroup per `unit` tiles, and one
+// for each long tile of the range (`longs`, ascending).
+inline int64_t row_tile_range(const std::vector<int32_t> &longs, int64_t lo, int64_t hi, int64_t unit, int64_t cap)
+{
+    const auto l0 = std::lower_bound(longs.begin(), longs.end(), (int32_t)lo);
+    const auto groups = [&](int64_t end) {
+        return (end - lo + unit - 1) / unit + (std::lower_bound(l0, longs.end(), (int32_t)end) - l0);
+    };
+    if (groups(hi) <= cap) return hi;
+    int64_t fits = lo + 1, over = hi;
+    while (over - fits > 1) {
+        const int64_t mid = fits + (over - fits) / 2;
+        if (groups(mid) <= cap) fits = mid;
+        else over = mid;
+    }
+    return fits;
+}
+
 }  // namespace spk
