@@ -189,6 +189,7 @@ __global__ __launch_bounds__(BS) void k_xwin(XwinArgs a)
     constexpr int NW = BS / kWave;
     constexpr int WC = WB / (int)sizeof(T);
     constexpr int ITEMS = E / kWave;
+    static_assert(WC <= 0x8000, "a column word has 15 bits of column");
     __shared__ T win[WC];
     __shared__ double sp[NW * (E + kWave)];
     // XCD k runs the k-th eighth of the chunks, so that a window's chunks, which

@@ -63,6 +63,7 @@ spk_status build_xwin(spk_handle h, spk_mat *A, int64_t wc, XwinData &d)
     XwinHost hx;
     switch (xwin_layout(m, A->ncols, nnz, A->rp_host.data(), ci.data(), val.data(), vs, wc, hx, kXwinMark, kXwinSlack)) {
     case kXwinOk: break;
+    case kXwinTooWide: return fail(SPK_ERR_ARG, "an x window of %lld columns does not fit the column words", (long long)wc);
     case kXwinTooManyPairs: return fail(SPK_ERR_SHAPE, "too many (row, window) pairs for the x-window form");
     case kXwinTooManyWindows:
         return fail(SPK_ERR_SHAPE, "%lld columns make more than %lld windows", (long long)A->ncols,

@@ -29,7 +29,7 @@ constexpr int64_t kXwinMaxRb = 1024;      // rows per block at most (one per thr
 constexpr int64_t kXwinMaxWin = 1023;     // windows one matrix may have
 constexpr int64_t kXwinMaxTable = (int64_t)1 << 26;   // block table entries
 
-enum XwinLayoutStatus { kXwinOk = 0, kXwinTooManyPairs, kXwinTooManyWindows, kXwinTableTooLarge };
+enum XwinLayoutStatus { kXwinOk = 0, kXwinTooManyPairs, kXwinTooManyWindows, kXwinTableTooLarge, kXwinTooWide };
 
 struct XwinHost {
     int64_t wc = 0;                   // columns per window
@@ -50,16 +50,18 @@ struct XwinHost {
 };
 
 // Regroups the entries of an m x n CSR matrix (values of vs bytes) by
-// windows of wc columns (wc <= 65536): pairs window-major, within a window
-// in row order; a pair's entries keep their order in the row.  Then the
-// row blocks of the second pass and their staging tables.  A pair's first
-// entry has `start` set in its column word; ci and val keep room for `slack`
-// more entries, so that adding them moves nothing.
+// windows of wc columns: pairs window-major, within a window in row order; a
+// pair's entries keep their order in the row.  Then the row blocks of the
+// second pass and their staging tables.  A pair's first entry has `start` (a
+// bit, or 0) set in its column word, so windows have at most `start` columns,
+// or 65,536 without it; ci and val keep room for `slack` more entries, so that
+// adding them moves nothing.
 inline XwinLayoutStatus xwin_layout(int64_t m, int64_t n, int64_t nnz, const int32_t *rp, const int32_t *ci,
                                     const void *val, size_t vs, int64_t wc, XwinHost &d, uint16_t start = 0,
                                     int64_t slack = 0)
 {
     d = XwinHost();
+    if (wc < 1 || wc > (start ? (int64_t)start : 65536)) return kXwinTooWide;
     d.wc = wc;
     d.nwin = n > 0 ? (n + wc - 1) / wc : 0;
     const char *vb = (const char *)val;
