@@ -11,6 +11,7 @@
 #include <mutex>
 #include <set>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "../../include/spk.h"
@@ -73,8 +74,8 @@ struct ColBlockData {
 
 // SPK_FMT_XWIN (see kernels.h, XwinArgs): the entries regrouped by column
 // window, built on first use for one window size; the chunks and wavefront
-// ranges of each (threads, chunks per compute unit); the FP64 partials, one
-// per (row, window) pair, per stream.
+// ranges of each (threads, entries per tile, chunks per compute unit); the FP64
+// partials, one per (row, window) pair, per stream.
 struct XwinPlan {
     int32_t *wave_p = nullptr;      // nchunk * wavefronts + 1: first pair of each wavefront's range
     int32_t *wave_k = nullptr;      // the same: its first entry
@@ -96,7 +97,7 @@ struct XwinData {
     int64_t rb = 0, nblk = 0;       // rows per block of the second pass, blocks
     std::vector<int32_t> ent_host;
     std::vector<int64_t> pair_off;  // nwin + 1: first pair of each window
-    std::map<std::pair<int, int>, XwinPlan> plans;   // by (threads, chunks per compute unit)
+    std::map<std::tuple<int, int, int>, XwinPlan> plans;   // by (threads, entries per tile, chunks per compute unit)
     std::map<hipStream_t, double *> part;
     int64_t bytes = 0;
 };

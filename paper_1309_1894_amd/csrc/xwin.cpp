@@ -101,8 +101,8 @@ spk_status build_xwin(spk_handle h, spk_mat *A, int64_t wc, XwinData &d)
     return SPK_OK;
 }
 
-// Chunks and wavefront ranges of one (wavefronts per workgroup, chunk
-// target), uploaded.
+// Chunks and wavefront ranges of one (entries per tile, wavefronts per
+// workgroup, chunk target), uploaded.
 spk_status build_plan(spk_handle h, const XwinData &d, int E, int nw, int64_t target, XwinPlan &pl)
 {
     XwinHost view;   // the planner reads the pair layout only
@@ -152,7 +152,7 @@ spk_status get_xwin(spk_handle h, spk_mat *A, int kib, int block, int E, int gri
             d = &A->xwin.emplace(kib, std::move(nd)).first->second;
         }
     }
-    const auto key = std::make_pair(block, grid);
+    const auto key = std::make_tuple(block, E, grid);
     XwinPlan *pl = nullptr;
     {
         std::lock_guard<std::mutex> lk(h->mu);

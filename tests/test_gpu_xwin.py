@@ -170,3 +170,27 @@ def test_xwin_rejects_bad_variants(spk, dev):
                 spk.spk_run(p, spk.make_variant(format=spk.SPK_FMT_XWIN, unroll=1, **kw))
     finally:
         M.release()
+
+
+def test_xwin_plans_of_every_kernel_in_any_order(spk, dev):
+    """A plan's chunks are cut by the variant's entries per tile too: on one
+    matrix every kernel gives the same bits whichever ran before it."""
+    A = I.zipf(30000, seed_struct=181, seed_val=182)
+    x = torch.from_numpy(I.uniform(183, 0, A.ncols)).to(dev)
+    shapes = [(512, 128, 256), (1024, 128, 128), (768, 128, 256), (256, 64, 256), (512, 64, 256)]
+    say("x-window plans in any order")
+    outs = []
+    for order in (shapes, shapes[::-1]):
+        M = spk.Matrix(A)
+        y = torch.empty_like(x)
+        got = {}
+        try:
+            for bs, kib, e in order:
+                v = spk.make_variant(format=spk.SPK_FMT_XWIN, block=bs, group=kib, lds=e, grid=2, unroll=1, streams=1)
+                spk.spk_run(spk.problem(spk.SPK_OP_SPMV, A=M, x=x, y=y), v)
+                got[bs, kib, e] = y.clone()
+        finally:
+            M.release()
+        outs.append(got)
+    for s in shapes:
+        assert torch.equal(outs[0][s], outs[1][s]), s
