@@ -545,7 +545,9 @@ typedef struct {
                               * threads with 2048-entry tiles */
     int32_t tile_nnz;        /* target entries per tile of the lane-group
                               * modes (0 -> 1024) */
-    int32_t waves_per_cu;    /* persistent residency (0 -> from occupancy) */
+    int32_t waves_per_cu;    /* wavefronts per compute unit of the persistent
+                              * kind's grid (0 -> eight times those that fit
+                              * at once) */
     int32_t x_window;        /* LDS room for x per wavefront (entries; 0 or 256)
                               * of the kernel used with an explicit block; a
                               * kernel with room runs the tiles of classes
@@ -630,7 +632,8 @@ spk_status spk_batch_tile_modes(spk_handle h, spk_batch b, int64_t *tiles, int64
 /* The launch configuration the batch currently uses (after planning or
  * tuning, Section 3's threads per block and blocks per grid): persistence,
  * graph use and workgroup size; here tile_nnz is the kernel's LDS tile in
- * entries per workgroup and waves_per_cu the persistent kind's residency. */
+ * entries per workgroup and waves_per_cu the persistent kind's grid, as it runs
+ * (given as an option, it gives that grid again). */
 spk_status spk_batch_config(spk_handle h, spk_batch b, spk_batch_opts *out);
 
 /* Frees a batch plan (its tiles, counters and captured graphs).  Library

@@ -875,7 +875,7 @@ spk_status spk_batch_config(spk_handle h, spk_batch b, spk_batch_opts *out)
     out->block = b->entry->block;
     out->tile_nnz = b->entry->tile;
     out->x_window = b->entry->xw;
-    out->waves_per_cu = (int32_t)(b->grid_persistent / std::max(1, b->h->num_cu)) * (b->entry->block / 64);
+    out->waves_per_cu = (int32_t)(persistent_cap(b) / std::max(1, b->h->num_cu)) * (b->entry->block / 64);
     return SPK_OK;
 }
 

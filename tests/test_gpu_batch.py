@@ -505,3 +505,27 @@ def test_batch_persistent_walks_every_tile(spk, dev, count, dt):
             b.free()
         assert np.array_equal(y.cpu().numpy(), ref.astype(dt))
         assert np.array_equal(w.cpu().numpy(), (0.5 * ref + x).astype(dt))
+
+
+def test_batch_config_names_the_grid_that_runs(spk, dev, monkeypatch):
+    """The persistent kind's grid holds several times the wavefronts that fit a
+    compute unit (32) at once; the configuration reports that grid, and its
+    value given as an option reports, and runs, the same."""
+    B = mixed_batch()
+    arrs = _dev_batch(B, dev)
+    say("batch configuration")
+    x = torch.from_numpy(I.batch_vector(B, seed=13)).to(dev)
+    y, w, y2, w2 = (torch.empty_like(x) for _ in range(4))
+    b = spk.Batch(B, arrs)
+    waves = b.config()["waves_per_cu"]
+    b.run(0.5, x, y, w)
+    b.free()
+    assert waves > 32, waves
+    opts = spk.spk_batch_opts
+    monkeypatch.setattr(spk, "spk_batch_opts", lambda p, g, blk, nnz, _, xw: opts(p, g, blk, nnz, waves, xw))
+    b = spk.Batch(B, arrs)
+    monkeypatch.undo()
+    assert b.config()["waves_per_cu"] == waves
+    b.run(0.5, x, y2, w2)
+    b.free()
+    assert torch.equal(y, y2) and torch.equal(w, w2)
