@@ -529,3 +529,78 @@ def test_batch_config_names_the_grid_that_runs(spk, dev, monkeypatch):
     b.run(0.5, x, y2, w2)
     b.free()
     assert torch.equal(y, y2) and torch.equal(w, w2)
+
+
+def _graph_batch(dt=np.float64):
+    """80,001 instances of three rows: more tiles (one each) than are launched
+    directly, so that use_graph replays a captured graph."""
+    count, m = 80_001, 3
+    one = lambda v: np.full(count, v, np.int64)
+    return I.Batch(one(m), one(7), one(1), (m + 1) * np.arange(count), 7 * np.arange(count), m * np.arange(count),
+                   np.tile(np.array([0, 2, 5, 7], np.int32), count),
+                   np.tile(np.array([0, 1, 0, 1, 2, 1, 2], np.int32), count),
+                   ((np.arange(7 * count) * 7) % 13 - 6).astype(dt))
+
+
+@pytest.mark.parametrize("persistent", [1, 0])
+def test_batch_graph_follows_its_operands(spk, dev, persistent):
+    """A captured graph holds x, y, w and alpha: every change of one of them,
+    going back to the first set and eager work in between give the oracle's
+    results (integer data: exact), replays included."""
+    B = _graph_batch()
+    n = 3 * B.count
+    A = I.block_diagonal(B)
+    xs = [((np.arange(n) * k) % 11 - 5).astype(np.float64) for k in (5, 7)]
+    refs = [O.spmv(A, x)[0] for x in xs]
+    xd = [torch.from_numpy(x).to(dev) for x in xs]
+    ys = [torch.empty(n, dtype=torch.float64, device=dev) for _ in range(2)]
+    ws = [torch.empty_like(ys[0]) for _ in range(2)]
+    b = spk.Batch(B, _dev_batch(B, dev), persistent=persistent, use_graph=True)
+    try:
+        assert b.info()["tiles"] > 65536
+        steps = [(0, 0, 0, 0.5), (0, 0, 0, 0.5), (1, 0, 0, 0.5), (1, 1, 0, 0.5), (1, 1, 1, 0.5), (1, 1, 1, 0.25),
+                 (1, 1, None, 0.25), (0, 0, 0, 0.5), (0, 0, 0, 0.5)]
+        for k, (x, y, w, alpha) in enumerate(steps):
+            say(f"batch graph step {k} persistent={persistent}")
+            for t in ys + ws:
+                t.fill_(float("nan"))
+            b.run(alpha, xd[x], ys[y], None if w is None else ws[w])
+            torch.cuda.synchronize()
+            assert np.array_equal(ys[y].cpu().numpy(), refs[x]), k
+            assert bool(torch.isnan(ys[1 - y]).all()), k
+            for i in range(2):
+                if i == w:
+                    assert np.array_equal(ws[i].cpu().numpy(), alpha * refs[x] + xs[x]), k
+                else:
+                    assert bool(torch.isnan(ws[i]).all()), k
+    finally:
+        b.free()
+
+
+@pytest.mark.parametrize("persistent", [1, 0])
+def test_batch_graphs_on_two_streams(spk, dev, persistent):
+    """Each stream has its own captured graph: replays on two streams in turn,
+    with operands and coefficients of their own, queued without waiting."""
+    B = _graph_batch()
+    n = 3 * B.count
+    A = I.block_diagonal(B)
+    xs = [((np.arange(n) * k) % 11 - 5).astype(np.float64) for k in (5, 7)]
+    refs = [O.spmv(A, x)[0] for x in xs]
+    xd = [torch.from_numpy(x).to(dev) for x in xs]
+    ys = [torch.full((n,), float("nan"), dtype=torch.float64, device=dev) for _ in range(2)]
+    ws = [torch.full_like(ys[0], float("nan")) for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    say(f"batch graphs on two streams persistent={persistent}")
+    b = spk.Batch(B, _dev_batch(B, dev), persistent=persistent, use_graph=True)
+    try:
+        assert b.info()["tiles"] > 65536
+        torch.cuda.synchronize()
+        for _ in range(5):
+            for i in range(2):
+                b.run(0.5 + 0.25 * i, xd[i], ys[i], ws[i], stream=streams[i])
+        torch.cuda.synchronize()
+        for i in range(2):
+            assert np.array_equal(ys[i].cpu().numpy(), refs[i]), i
+            assert np.array_equal(ws[i].cpu().numpy(), (0.5 + 0.25 * i) * refs[i] + xs[i]), i
+    finally:
+        b.free()
