@@ -79,18 +79,21 @@ __device__ __forceinline__ gptr_mut<T> as_global_mut(T *p) { return (gptr_mut<T>
 // 4-byte columns.
 // A matrix entry is read once a product, so the values are loaded
 // non-temporal: the caches keep the x entries that neighbouring rows share.
-// With `keep` (a matrix small enough to stay in the last-level cache from one
-// product to the next: keep_matrix) they are ordinary loads.  The columns are ordinary
+// With KEEP (a matrix small enough to stay in the last-level cache from one
+// product to the next: keep_matrix) they are ordinary loads; a form of its own,
+// since a branch here, taken or not, cost the larger matrices 8% (two-byte
+// columns, 256-entry tiles, lap3d(128) FP64 38.3 us and 35.3, FP32 34.3 and
+// 30.9).  The columns are ordinary
 // loads too: a tile's first and last lines are its neighbours' as well, and
 // read non-temporal they came from memory twice (lap3d(128) FP64 42.3 us and
 // 39.6, a band of 600,000 rows of 20 entries 32.9 and 29.5, in FP32 24.1 and
 // 21.2; batches with 4-byte columns: 256 instances 40.9 and 36.7, in FP32 31.0
 // and 27.9, 512 instances 81.1 and 83.4, 4,096 740 and 735; 512 with compact
 // columns 58.0 and 56.2, in FP32 46.9 and 45.3).
-template <typename T, int ITEMS, bool DOT = false, int XW = 0, int CB = 4>
+template <typename T, int ITEMS, bool DOT = false, int XW = 0, int CB = 4, bool KEEP = false>
 __device__ __forceinline__ double wave_stream(const int32_t *rp_, const int32_t *ci_, const T *val_, const T *x_,
                                               T *y_, T *w_, T alpha, int r0, int r1, int k0, int k1, double *sp,
-                                              int *srp, int xlo = 0, int xn = 0, T *xs = nullptr, bool keep = false)
+                                              int *srp, int xlo = 0, int xn = 0, T *xs = nullptr)
 {
     static_assert(CB == 4 || CB == 2 || CB == 1, "columns of 4, 2 or 1 bytes");
     static_assert(CB != 1 || (XW > 0 && XW <= 256), "one-byte columns index a window of at most 256 entries");
@@ -119,12 +122,10 @@ __device__ __forceinline__ double wave_stream(const int32_t *rp_, const int32_t 
         const int glast = (off + klast) & ~(GE - 1);   // start of the last group holding an entry
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) g[s] = *(gptr<int4v>)(cg + IB * min(GE * (l + kWave * s), glast));
-        if (keep) {
 #pragma unroll
-            for (int j = 0; j < ITEMS; ++j) v[j] = val[k0 + min(l + j * kWave, klast)];
-        } else {
-#pragma unroll
-            for (int j = 0; j < ITEMS; ++j) v[j] = __builtin_nontemporal_load(val + k0 + min(l + j * kWave, klast));
+        for (int j = 0; j < ITEMS; ++j) {
+            const gptr<T> at = val + k0 + min(l + j * kWave, klast);
+            v[j] = KEEP ? *at : __builtin_nontemporal_load(at);
         }
     }
     constexpr int XQ = XW > 0 ? XW / kWave : 1;

@@ -329,7 +329,7 @@ __global__ __launch_bounds__(BS) void k_spmv_sell(SpmvArgs<T> a)
 // offsets from the block's first column (which is also its window's first
 // column) instead of the CSR's four-byte columns; the other blocks read
 // the CSR's.
-template <typename T, int BS, int E, int XW, int CB, bool FUSED>
+template <typename T, int BS, int E, int XW, int CB, bool FUSED, bool KEEP>
 __global__ __launch_bounds__(BS) void k_spmv_adaptive(SpmvArgs<T> a)
 {
     constexpr int NW = BS / kWave;
@@ -363,16 +363,16 @@ __global__ __launch_bounds__(BS) void k_spmv_adaptive(SpmvArgs<T> a)
         if constexpr (CB == 2) {
             const int base = a.block_c16[b];
             if (base >= 0) {
-                wave_stream<T, E / kWave, false, XW, 2>(a.rp, reinterpret_cast<const int32_t *>(a.c16), a.val, a.x,
-                                                        a.y, w, a.alpha, r0, r1, a.block_k[b], a.block_k[b + 1],
-                                                        sp + wv * E, srp + wv * (kWaveTileRows + 1), base, xn,
-                                                        xs + wv * (XW > 0 ? XW : 1), a.keep != 0);
+                wave_stream<T, E / kWave, false, XW, 2, KEEP>(
+                    a.rp, reinterpret_cast<const int32_t *>(a.c16), a.val, a.x, a.y, w, a.alpha, r0, r1, a.block_k[b],
+                    a.block_k[b + 1], sp + wv * E, srp + wv * (kWaveTileRows + 1), base, xn,
+                    xs + wv * (XW > 0 ? XW : 1));
                 return;
             }
         }
-        wave_stream<T, E / kWave, false, XW>(a.rp, a.ci, a.val, a.x, a.y, w, a.alpha, r0, r1, a.block_k[b],
-                                             a.block_k[b + 1], sp + wv * E, srp + wv * (kWaveTileRows + 1), xlo, xn,
-                                             xs + wv * (XW > 0 ? XW : 1), a.keep != 0);
+        wave_stream<T, E / kWave, false, XW, 4, KEEP>(a.rp, a.ci, a.val, a.x, a.y, w, a.alpha, r0, r1, a.block_k[b],
+                                                      a.block_k[b + 1], sp + wv * E, srp + wv * (kWaveTileRows + 1),
+                                                      xlo, xn, xs + wv * (XW > 0 ? XW : 1));
     } else if (mode == kBlkWave) {
         // medium rows (a kBlkLong tile's row is a workgroup's)
         wave_rows_mlp<T, 8>(a.rp, a.ci, a.val, a.x, a.y, w, a.alpha, r0, r1);
@@ -492,7 +492,9 @@ hipError_t L_sell(const void *p, dim3 g, hipStream_t s)
 template <typename T, int BS, int E, int XW, int CB, bool F>
 hipError_t L_adaptive(const void *p, dim3 g, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_spmv_adaptive<T, BS, E, XW, CB, F>), g, dim3(BS), 0, s, *(const SpmvArgs<T> *)p);
+    const SpmvArgs<T> &a = *(const SpmvArgs<T> *)p;
+    if (a.keep) hipLaunchKernelGGL((k_spmv_adaptive<T, BS, E, XW, CB, F, true>), g, dim3(BS), 0, s, a);
+    else hipLaunchKernelGGL((k_spmv_adaptive<T, BS, E, XW, CB, F, false>), g, dim3(BS), 0, s, a);
     return hipGetLastError();
 }
 

@@ -627,3 +627,36 @@ def test_borrowed_csr_is_as_accurate_as_lanes_per_row(spk, dev, length):
     finally:
         M.release()
     assert stream <= lanes, (stream, lanes)
+
+
+@pytest.mark.parametrize("dt", [1, 0])
+def test_row_blocks_either_side_of_the_kept_size(spk, dev, dt):
+    """Row blocks have a form whose values may stay in the last-level cache
+    (matrices up to 80 MB of values and columns) and one whose values may not:
+    sizes on both sides of the line, four- and two-byte columns, with and
+    without room for x.  Integer data: bit for bit."""
+    per = 10
+    line = (80 << 20) // (12 if dt else 8) // per      # rows of `per` entries that reach it
+    rng = np.random.default_rng(5)
+    for m in (line, line + 1):
+        start = np.minimum(np.arange(m), m - 20)
+        ci = (start[:, None] + np.arange(0, 20, 2)[None, :]).astype(np.int32)
+        A = I.CSR(m, m, (np.arange(m + 1) * per).astype(np.int32), ci.ravel(),
+                  rng.integers(-8, 9, m * per).astype(NP[dt]))
+        x = rng.integers(-8, 9, m).astype(NP[dt])
+        ref, _ = O.spmv(A, x)
+        M = spk.Matrix(A)
+        xd = torch.from_numpy(x).to(dev)
+        y, w = torch.empty_like(xd), torch.empty_like(xd)
+        try:
+            for group, vec in ((1, 0), (1, 2), (256, 0), (256, 2)):
+                say(f"row blocks m={m} dtype={dt} group={group} vec={vec}")
+                v = spk.make_variant(format=spk.SPK_FMT_ADAPTIVE, block=256, group=group, unroll=1, streams=1, lds=256,
+                                     vec=vec)
+                y.fill_(float("nan"))
+                spk.spk_run(spk.problem(spk.SPK_OP_SPMV, A=M, x=xd, y=y), v)
+                assert np.array_equal(y.cpu().numpy(), ref.astype(NP[dt]))
+                spk.spk_run(spk.problem(spk.SPK_OP_SPMV_WAXPY, A=M, x=xd, y=y, w=w, alpha=0.5), v)
+                assert np.array_equal(w.cpu().numpy(), (0.5 * ref + x).astype(NP[dt]))
+        finally:
+            M.release()
