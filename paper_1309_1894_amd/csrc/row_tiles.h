@@ -64,8 +64,8 @@ inline void make_blocks(const int32_t *rp, int64_t m, int E, std::vector<uint32_
 // capacity, BS = threads per workgroup: runs of short rows (at most
 // min(E, 512) entries each, at most 128 rows, at most E entries); runs of
 // medium rows of up to kMediumRun entries (or one row), 64 lanes per row;
-// rows over long_row_min(BS) entries stand alone, and are named in `longs`
-// (tile indices): a whole workgroup runs each.  The aim is that no wavefront
+// rows over long_row_line entries stand alone, and are named in `longs` (tile
+// indices): a whole workgroup runs each.  The aim is that no wavefront
 // has much more to do than a full row-stream tile: gathers are bound by rate,
 // so a wavefront with four times the entries outlives the others and ends
 // alone, bound by latency.  300,001 rows of truncated-Zipf length (mean 16),
@@ -78,11 +78,39 @@ constexpr int64_t kStreamRowMax = 512;
 constexpr int64_t kMediumRun = 1024;
 inline int64_t long_row_min(int BS) { return BS > 256 ? 1024 : 512; }
 
-inline void make_row_tiles(const int32_t *rp, int64_t m, int E, int BS, std::vector<uint32_t> &out,
+// Where most wavefronts would run such rows, none outlives the others, and a
+// workgroup per row mostly waits (a row of 600 is one pass of its loads): FP64
+// rows over long_row_min get a wavefront each, up to kManyLongRowMax entries,
+// when they are at least kManyLongRows (eight wavefronts per compute unit) and
+// outnumber the other tiles.  One length throughout, FP64, a workgroup and a
+// wavefront per row: 10,000 rows of 520 21.1 us and 14.7, 8,000 of 800 31.9 and
+// 26.7, 5,000 of 1,100 23.2 and 17.9, 3,000 of 2,000 15.4 and 15.5, 1,500 of
+// 700 5.7 and 6.0, 300 of 2,000 5.7 and 7.7; CG's 512 threads, five iterations:
+// 8,000 of 1,100 274 and 172, 3,000 of 3,000 198 and 195.  In FP32 the
+// workgroup is the faster one at all of these (10,000 of 520 16.4 and 19.7,
+// 3,000 of 2,000 11.9 and 29.7).
+constexpr int64_t kManyLongRows = 2048, kManyLongRowMax = 4096;
+inline int64_t long_row_line(const int32_t *rp, int64_t m, int E, int BS, bool f64)
+{
+    const int64_t line = long_row_min(BS);
+    if (!f64) return line;
+    int64_t rows = 0, entries = 0;
+    for (int64_t r = 0; r < m; ++r) {
+        const int64_t l = rp[r + 1] - rp[r];
+        if (l > line) {
+            ++rows;
+            entries += l;
+        }
+    }
+    const int64_t others = (rp[m] - rp[0] - entries) / E + (m - rows) / (2 * 64);   // at least so many tiles
+    return rows >= kManyLongRows && rows > others ? kManyLongRowMax : line;
+}
+
+inline void make_row_tiles(const int32_t *rp, int64_t m, int E, int BS, bool f64, std::vector<uint32_t> &out,
                            std::vector<int32_t> &out_k, std::vector<int32_t> &longs)
 {
     const int64_t short_max = std::min<int64_t>(kStreamRowMax, E);
-    const int64_t long_min = long_row_min(BS);
+    const int64_t long_min = long_row_line(rp, m, E, BS, f64);
     const int64_t row_cap = 2 * 64;
     out.clear();
     out_k.clear();
