@@ -125,6 +125,7 @@ struct PoolMat {
     double last_use = 0.0;
     hipEvent_t uploaded = nullptr;
     std::vector<BatchTile> tiles;   // row ranges of this matrix (pointers set when made resident)
+    bool lanes = false;             // some tile gives G lanes to a row
 };
 
 struct Request {
@@ -330,6 +331,15 @@ constexpr size_t kDirectMin = 128 << 10;
 // and 85.
 constexpr size_t kEngineMin = 512 << 10;
 
+// Results of tiles that give G lanes to a row go back by a copy from this many
+// bytes on: such a tile stores one to eight rows at a time, each a write of its
+// own on the host link, where the row stream stores up to 64.  32 requests over
+// matrices of 2,000 to 8,000 rows of 240 entries: 245 us by the copy kernel, 331
+// written straight, 285 by the engines; in FP32 177, 240 and 218; 16 over 20,000
+// to 40,000 rows of 120 entries 372, 491 and 572.  Shorter ones the copy's own
+// launch costs more: 8 requests over 500 to 1,500 rows 71 and 66.
+constexpr size_t kLanesMin = 8 << 10;
+
 // How a vector in the caller's memory travels.
 enum : char {
     kStaged = 0,       // through the staging block
@@ -448,17 +458,18 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
     SPK_HIP(S->hpool.get(all_b, &F.pin));
     char *pin = (char *)F.pin;
     char *dev = (char *)F.dev;
-    // where each request's results go: host memory, or device memory for what
-    // the copy engines bring back
-    std::vector<char> engine_out(group.size(), batched ? 0 : 1);
+    // where each request's results go: host memory, or device memory for what is
+    // copied back
+    std::vector<char> copied_out(group.size(), batched ? 0 : 1);
     for (size_t k = 0; batched && k < group.size(); ++k) {
         const Request &R = group[k].second;
         const size_t at = vs * (size_t)F.off[k];
-        engine_out[k] = F.direct[k] == kDirectCopy || vs * (size_t)S->mats[R.mat].m >= kEngineMin;
+        const PoolMat &M = S->mats[R.mat];
+        copied_out[k] = F.direct[k] == kDirectCopy || vs * (size_t)M.m >= (M.lanes ? kLanesMin : kEngineMin);
         char *to_y = F.direct[k] ? (char *)R.y : pin + F.y_off + at;
         char *to_w = F.direct[k] ? (char *)R.w : pin + F.w_off + at;
-        rq[k].y = engine_out[k] ? dev + F.y_off + at : to_y;
-        rq[k].w = !R.w ? nullptr : engine_out[k] ? dev + F.w_off + at : to_w;
+        rq[k].y = copied_out[k] ? dev + F.y_off + at : to_y;
+        rq[k].w = !R.w ? nullptr : copied_out[k] ? dev + F.w_off + at : to_w;
     }
     if (batched) {
         memcpy(pin, rq.data(), sizeof(BatchReq) * rq.size());
@@ -533,7 +544,7 @@ spk_status launch_group(Server *S, std::vector<std::pair<int64_t, Request>> &gro
     }
     SegmentCopy to_host{false, s};
     for (size_t k = 0; k < group.size(); ++k) {
-        if (!engine_out[k]) continue;
+        if (!copied_out[k]) continue;
         const Request &R = group[k].second;
         const size_t nb = vs * (size_t)S->mats[R.mat].m, at = vs * (size_t)F.off[k];
         const bool engine = F.direct[k] == kDirectCopy;
@@ -783,6 +794,8 @@ spk_status spk_serve_add_matrix(spk_server S, const spk_csr *A, int32_t *id)
     if (spk_plan_get(S->h, batch_key(A->dtype, cls).c_str(), &v) == SPK_OK) mode = v.group;
     if (mode == 3) mode = 1;   // resident matrices keep 4-byte columns only
     cut_rows(rp, A->nrows, mode, batch_wave_entries(*S->entry), 1024, M.tiles);
+    // (a tile of one row too long for the stream stores that row alone)
+    for (const BatchTile &t : M.tiles) M.lanes = M.lanes || (t.mode != 0 && t.mode != 1 && t.r1 - t.r0 > 1);
     if ((int64_t)M.tiles.size() > kMaxLaunchTiles)
         return fail(SPK_ERR_SHAPE, "the matrix needs %lld tiles, more than one launch takes",
                     (long long)M.tiles.size());

@@ -359,3 +359,42 @@ def test_serve_pinned_buffers_of_every_kind(spk, dev, flags):
         del bufs
         for p in held:
             hip.hipHostFree(p)
+
+
+@pytest.mark.parametrize("dt", [np.float64, np.float32])
+def test_serve_lanes_per_row_results(spk, dev, dt):
+    """Classes over 64 entries a row give G lanes to a row; their results come
+    back by a copy from 8 KiB on and are written straight below it: sizes
+    around that line, around the direct and the engine lines, and a matrix
+    with rows too long for the stream, staged and pinned, with and without w."""
+    item = np.dtype(dt).itemsize
+    sizes = [70, (8 << 10) // item - 1, (8 << 10) // item, (128 << 10) // item, (512 << 10) // item - 1,
+             (512 << 10) // item]
+    pool = [I.banded(m, 66, 1.0, seed_struct=190, seed_val=191 + i, dtype=dt) for i, m in enumerate(sizes)]
+    pool.append(I.zipf(6000, kmax=3000, seed_struct=198, seed_val=199, dtype=dt))
+    import torch
+    nreq = 4 * len(pool)
+    mats = [i % len(pool) for i in range(nreq)]
+    xs, ys, ws = [], [], []
+    for i, m in enumerate(mats):
+        n = pool[m].nrows
+        pinned = i // len(pool) % 2
+        bufs = [torch.full((n * item,), 255, dtype=torch.uint8).pin_memory().numpy().view(dt) if pinned else
+                np.full(n, np.nan, dt) for _ in range(3)]
+        bufs[0][:] = I.uniform(200, i, n, dt)
+        for to, b in zip((xs, ys, ws), bufs):
+            to.append(b)
+    say(f"serve lanes per row {np.dtype(dt).name}")
+    srv = spk.Server(streams=2, max_inflight=nreq, max_batch=8, mode=0, alpha=0.5)
+    try:
+        ids = [srv.add_matrix(A) for A in pool]
+        for i, m in enumerate(mats):
+            srv.submit(ids[m], xs[i], ys[i], *([ws[i]] if i % 3 else []))
+        srv.drain()
+        assert srv.stats()["completed"] == nreq and srv.stats()["rejected"] == 0
+    finally:
+        srv.close()
+    for i, m in enumerate(mats):
+        if i % 3 == 0:
+            ws[i] = O.waxpy(0.5, np.array(ys[i]), np.array(xs[i]))
+        _check(pool[m], np.array(xs[i]), np.array(ys[i]), np.array(ws[i]))
