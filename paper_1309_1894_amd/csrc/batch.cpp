@@ -169,7 +169,9 @@ spk_status launch_tiles(const BatchEntry *e, int dtype, const BatchTile *d_tiles
     const int64_t nw = e->block / 64;
     int64_t g = (ntiles + nw - 1) / nw;   // tile groups, one per workgroup
     if (kind == kBatchPersistent) g = std::min<int64_t>(persistent_grid, g);
-    SPK_HIP(e->fn[dtype][reqs ? kBatchRequests : kind](dtype == SPK_F64 ? (const void *)&a.d : (const void *)&a.f, dim3((unsigned)g), s));
+    const BatchFn fn = e->fn[dtype][reqs ? kBatchRequests : kind];
+    if (!fn) return fail(SPK_ERR_NOT_FOUND, "no request-table kernel of block %d and tile %d", e->block, e->tile);
+    SPK_HIP(fn(dtype == SPK_F64 ? (const void *)&a.d : (const void *)&a.f, dim3((unsigned)g), s));
     return SPK_OK;
 }
 

@@ -230,13 +230,17 @@ hipError_t L_batch(const void *p, dim3 g, hipStream_t s)
     return hipGetLastError();
 }
 
-#define BENTRY(BS, TILE, XW)                                                                 \
-    {BS, TILE, XW,                                                                           \
-     {{L_batch<float, BS, TILE, XW, kBatchGrid>, L_batch<float, BS, TILE, XW, kBatchPersistent>,    \
-       L_batch<float, BS, TILE, XW, kBatchRequests>},                                               \
-      {L_batch<double, BS, TILE, XW, kBatchGrid>, L_batch<double, BS, TILE, XW, kBatchPersistent>,  \
-       L_batch<double, BS, TILE, XW, kBatchRequests>}},                                             \
-     {occ_batch<float, BS, TILE, XW>, occ_batch<double, BS, TILE, XW>}}
+#define BFN(T, BS, TILE, XW, REQ) \
+    {L_batch<T, BS, TILE, XW, kBatchGrid>, L_batch<T, BS, TILE, XW, kBatchPersistent>, REQ}
+#define BOCC(BS, TILE, XW) {occ_batch<float, BS, TILE, XW>, occ_batch<double, BS, TILE, XW>}
+#define BENTRY(BS, TILE, XW) \
+    {BS, TILE, XW, {BFN(float, BS, TILE, XW, nullptr), BFN(double, BS, TILE, XW, nullptr)}, BOCC(BS, TILE, XW)}
+// with the request-table form too (serving's shape)
+#define BENTRY_REQ(BS, TILE, XW)                                                \
+    {BS, TILE, XW,                                                              \
+     {BFN(float, BS, TILE, XW, (L_batch<float, BS, TILE, XW, kBatchRequests>)),   \
+      BFN(double, BS, TILE, XW, (L_batch<double, BS, TILE, XW, kBatchRequests>))}, \
+     BOCC(BS, TILE, XW)}
 
 // (threads per workgroup, LDS products per workgroup, LDS room for x per
 // wavefront): a wavefront's row stream holds TILE/(BS/64) entries: 256
@@ -245,7 +249,7 @@ const BatchEntry kBatch[] = {
     BENTRY(256, 2048, 0), BENTRY(256, 1024, 0), BENTRY(256, 4096, 0),
     BENTRY(128, 1024, 0), BENTRY(128, 2048, 0),
     BENTRY(512, 2048, 0), BENTRY(512, 4096, 0),
-    BENTRY(256, 2048, 256), BENTRY(256, 4096, 256), BENTRY(128, 2048, 256),
+    BENTRY_REQ(256, 2048, 256), BENTRY(256, 4096, 256), BENTRY(128, 2048, 256),
     BENTRY(128, 1024, 256), BENTRY(64, 1024, 256), BENTRY(64, 512, 256), BENTRY(64, 2048, 256),
 };
 
