@@ -46,6 +46,7 @@ struct spk_batch_s {
     uint16_t *c16 = nullptr;              // two-byte compact columns (the same layout), made when needed
     int *d_need16 = nullptr;              // tiles that would take two-byte columns, while c16 is absent
     int64_t grid_persistent = 0;
+    bool ntc = false;                     // the uploaded tiles' columns are read non-temporal
     std::mutex mu;                        // guards `streams`
     std::map<hipStream_t, BatchStream> streams;
 };
@@ -141,7 +142,7 @@ void cut_rows(const int32_t *rp, int64_t m, int mode, int entries, int64_t targe
 
 spk_status launch_tiles(const BatchEntry *e, int dtype, const BatchTile *d_tiles, int64_t ntiles, double alpha,
                         const void *x, void *y, void *w, int kind, int64_t persistent_grid,
-                        hipStream_t s, const BatchReq *reqs, const uint16_t *req_of_tile)
+                        hipStream_t s, const BatchReq *reqs, const uint16_t *req_of_tile, bool ntc)
 {
     if (ntiles == 0) return SPK_OK;
     if (ntiles > kMaxLaunchTiles)
@@ -169,7 +170,7 @@ spk_status launch_tiles(const BatchEntry *e, int dtype, const BatchTile *d_tiles
     const int64_t nw = e->block / 64;
     int64_t g = (ntiles + nw - 1) / nw;   // tile groups, one per workgroup
     if (kind == kBatchPersistent) g = std::min<int64_t>(persistent_grid, g);
-    const BatchFn fn = e->fn[dtype][reqs ? kBatchRequests : kind];
+    const BatchFn fn = e->fn[dtype][ntc][reqs ? kBatchRequests : kind];
     if (!fn) return fail(SPK_ERR_NOT_FOUND, "no request-table kernel of block %d and tile %d", e->block, e->tile);
     SPK_HIP(fn(dtype == SPK_F64 ? (const void *)&a.d : (const void *)&a.f, dim3((unsigned)g), s));
     return SPK_OK;
@@ -223,8 +224,25 @@ void cut_instance(const spk_batch b, int64_t i, int mode, std::vector<BatchTile>
     }
 }
 
+// Whether a launch's columns are too many to stay in cache from one run to the
+// next, so that reading them non-temporal leaves the caches to x and to the
+// results: 96 MB of four-byte columns, 64 MB of compact ones (whatever the tile
+// size).  Banded batches, ordinary loads and non-temporal: four-byte columns,
+// 55 MB 36.3 us and 40.7, 69 MB 45.6 and 49.8, 83 MB 59.7 and 59.4 (FP32 39.5 and
+// 40.8), 116 MB 84.0 and 81.3, 235 MB 168 and 164, 358 MB 252 and 245; compact,
+// 44 MB 82.9 and 85.8, 59 MB 114 and 111 (FP32 71.8 and 73.4), 89 MB 179 and
+// 171, 122 MB 235 and 226; from about 180 MB of compact and 490 MB of four-byte
+// columns on the two are equal.
+bool columns_past_cache(const std::vector<BatchTile> &tiles)
+{
+    double four = 0.0, compact = 0.0;
+    for (const BatchTile &t : tiles) (t.mode == 3 ? compact : four) += t.k1 - t.k0;
+    return 4.0 * four / (96 << 20) + compact / (64 << 20) > 1.0;
+}
+
 spk_status upload_tiles(spk_batch b, const std::vector<BatchTile> &tiles)
 {
+    b->ntc = columns_past_cache(tiles);
     if ((int64_t)tiles.size() > b->d_tiles_cap) {
         if (b->d_tiles) SPK_HIP(hipFree(b->d_tiles));
         b->d_tiles = nullptr;
@@ -310,7 +328,7 @@ constexpr int64_t kDirectTiles = 65536;
 spk_status launch(spk_batch b, int64_t ntiles, double alpha, const void *x, void *y, void *w, hipStream_t s)
 {
     return launch_tiles(b->entry, b->dtype, b->d_tiles, ntiles, alpha, x, y, w, b->opts.persistent,
-                        persistent_cap(b), s);
+                        persistent_cap(b), s, nullptr, nullptr, b->ntc);
 }
 
 spk_status occupancy(spk_batch b)
@@ -461,7 +479,7 @@ spk_status spk_batch_run(spk_handle h, spk_batch b, double alpha, const void *x,
         SPK_HIP(hipStreamSynchronize(h->work));
         SPK_HIP(hipStreamBeginCapture(h->work, hipStreamCaptureModeThreadLocal));
         spk_status ls = launch_tiles(b->entry, b->dtype, b->d_tiles, (int64_t)b->tiles.size(), alpha, x, y, w,
-                                     b->opts.persistent, persistent_cap(b), h->work);
+                                     b->opts.persistent, persistent_cap(b), h->work, nullptr, nullptr, b->ntc);
         hipGraph_t graph = nullptr;
         const hipError_t ce = hipStreamEndCapture(h->work, &graph);
         if (ls != SPK_OK) {

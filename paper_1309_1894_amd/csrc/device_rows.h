@@ -83,14 +83,13 @@ __device__ __forceinline__ gptr_mut<T> as_global_mut(T *p) { return (gptr_mut<T>
 // product to the next: keep_matrix) they are ordinary loads; a form of its own,
 // since a branch here, taken or not, cost the larger matrices 8% (two-byte
 // columns, 256-entry tiles, lap3d(128) FP64 38.3 us and 35.3, FP32 34.3 and
-// 30.9).  The columns are ordinary
-// loads too: a tile's first and last lines are its neighbours' as well, and
-// read non-temporal they came from memory twice (lap3d(128) FP64 42.3 us and
-// 39.6, a band of 600,000 rows of 20 entries 32.9 and 29.5, in FP32 24.1 and
-// 21.2; batches with 4-byte columns: 256 instances 40.9 and 36.7, in FP32 31.0
-// and 27.9, 512 instances 81.1 and 83.4, 4,096 740 and 735; 512 with compact
-// columns 58.0 and 56.2, in FP32 46.9 and 45.3).
-template <typename T, int ITEMS, bool DOT = false, int XW = 0, int CB = 4, bool KEEP = false>
+// 30.9).  The columns are ordinary loads too: a tile's first and last lines are
+// its neighbours' as well, and read non-temporal they came from memory twice
+// (lap3d(128) FP64 42.3 us and 39.6, a band of 600,000 rows of 20 entries 32.9
+// and 29.5, in FP32 24.1 and 21.2).  NTC reads them non-temporal, for batches
+// whose columns are too many to stay in cache (batch.cpp, columns_past_cache).
+template <typename T, int ITEMS, bool DOT = false, int XW = 0, int CB = 4, bool KEEP = false,
+          bool NTC = false>
 __device__ __forceinline__ double wave_stream(const int32_t *rp_, const int32_t *ci_, const T *val_, const T *x_,
                                               T *y_, T *w_, T alpha, int r0, int r1, int k0, int k1, double *sp,
                                               int *srp, int xlo = 0, int xn = 0, T *xs = nullptr)
@@ -121,7 +120,10 @@ __device__ __forceinline__ double wave_stream(const int32_t *rp_, const int32_t 
         const gptr<uint8_t> cg = cb + ((int64_t)k0 - off) * IB;
         const int glast = (off + klast) & ~(GE - 1);   // start of the last group holding an entry
 #pragma unroll
-        for (int s = 0; s < STEPS; ++s) g[s] = *(gptr<int4v>)(cg + IB * min(GE * (l + kWave * s), glast));
+        for (int s = 0; s < STEPS; ++s) {
+            const gptr<int4v> at = (gptr<int4v>)(cg + IB * min(GE * (l + kWave * s), glast));
+            g[s] = NTC ? __builtin_nontemporal_load(at) : *at;
+        }
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
             const gptr<T> at = val + k0 + min(l + j * kWave, klast);

@@ -325,9 +325,10 @@ void cut_rows(const int32_t *rp, int64_t m, int mode, int entries, int64_t targe
 // One launch of the tile kernel of launch kind `kind` (kBatchGrid, or
 // kBatchPersistent with at most persistent_grid workgroups).  With `reqs` (grid launches
 // only) the ntiles launch tiles are named through the request table and
-// `req_of_tile` instead of `d_tiles`.
+// `req_of_tile` instead of `d_tiles`.  `ntc`: columns read non-temporal.
 spk_status launch_tiles(const BatchEntry *e, int dtype, const BatchTile *d_tiles, int64_t ntiles, double alpha,
                         const void *x, void *y, void *w, int kind, int64_t persistent_grid,
-                        hipStream_t s, const BatchReq *reqs = nullptr, const uint16_t *req_of_tile = nullptr);
+                        hipStream_t s, const BatchReq *reqs = nullptr, const uint16_t *req_of_tile = nullptr,
+                        bool ntc = false);
 
 }  // namespace spk

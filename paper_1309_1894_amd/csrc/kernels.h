@@ -218,7 +218,9 @@ constexpr int kBatchRequests = 2;    // serving: the grid form, tiles and result
 struct BatchEntry {
     int block, tile;     // threads per workgroup, LDS products per workgroup
     int xw;              // LDS room for x per wavefront (entries) for mode-1 tiles, 0 = none
-    BatchFn fn[2][3];    // [dtype][launch kind]; kBatchRequests where it is compiled, else null
+    // [dtype][columns read non-temporal][launch kind]; kBatchRequests where it
+    // is compiled, else null
+    BatchFn fn[2][2][3];
     int (*occupancy[2])();  // [dtype] resident workgroups per CU (persistent kernel)
 };
 

@@ -75,7 +75,7 @@ __device__ __forceinline__ BatchTile load_tile(const BatchArgs<T> &a, int tile, 
     return td;
 }
 
-template <typename T, int BS, int TILE, int XW, bool REQ>
+template <typename T, int BS, int TILE, int XW, bool REQ, bool NTC>
 __device__ __forceinline__ void run_wave_tile(const BatchArgs<T> &a, int tile, double *sp, int *srp, T *xs)
 {
     T *y, *w;
@@ -84,25 +84,24 @@ __device__ __forceinline__ void run_wave_tile(const BatchArgs<T> &a, int tile, d
     const int32_t *ci = td.ci;
     const T *val = (const T *)td.val;
     const T *x = a.x + td.vec_off;
+    constexpr int ITEMS = WaveTiles<T, BS, TILE>::ITEMS;
     switch (td.mode) {
     case 0:  // entries and rows fit the wavefront's LDS slice (guaranteed by the planner)
-        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1, td.k0, td.k1,
-                                                      sp, srp);
+        wave_stream<T, ITEMS, false, 0, 4, false, NTC>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1, td.k0, td.k1, sp,
+                                                       srp);
         break;
     case 1:  // the same, x from the tile's window in LDS when it fits the kernel's room
-        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1,
-                                                                 td.k0, td.k1, sp, srp, td.xlo,
-                                                                 XW > 0 && td.xn <= XW ? td.xn : 0, xs);
+        wave_stream<T, ITEMS, false, XW, 4, false, NTC>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1, td.k0, td.k1, sp,
+                                                        srp, td.xlo, XW > 0 && td.xn <= XW ? td.xn : 0, xs);
         break;
     case 3:  // mode 1 with compact columns: ci holds each entry's byte offset in the window (which fits)
         if constexpr (XW > 0 && XW <= 256)
-            wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 1>(rp, ci, val, x, y, w, a.alpha, td.r0,
-                                                                           td.r1, td.k0, td.k1, sp, srp, td.xlo,
-                                                                           td.xn, xs);
+            wave_stream<T, ITEMS, false, XW, 1, false, NTC>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1, td.k0, td.k1,
+                                                            sp, srp, td.xlo, td.xn, xs);
         break;
     case 5:  // compact columns of a wider tile: two-byte offsets from xlo, x gathered from memory
-        wave_stream<T, WaveTiles<T, BS, TILE>::ITEMS, false, XW, 2>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1,
-                                                                       td.k0, td.k1, sp, srp, td.xlo, 0, xs);
+        wave_stream<T, ITEMS, false, XW, 2, false, NTC>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1, td.k0, td.k1, sp,
+                                                        srp, td.xlo, 0, xs);
         break;
     case 2: wave_group_rows<T, 2>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1); break;
     case 4: wave_group_rows<T, 4>(rp, ci, val, x, y, w, a.alpha, td.r0, td.r1); break;
@@ -113,7 +112,7 @@ __device__ __forceinline__ void run_wave_tile(const BatchArgs<T> &a, int tile, d
     }
 }
 
-template <typename T, int BS, int TILE, int XW, bool REQ>
+template <typename T, int BS, int TILE, int XW, bool REQ, bool NTC>
 __global__ __launch_bounds__(BS) void k_batch_grid(BatchArgs<T> a)
 {
     using WT = WaveTiles<T, BS, TILE>;
@@ -125,8 +124,8 @@ __global__ __launch_bounds__(BS) void k_batch_grid(BatchArgs<T> a)
     // runs of kXcdRunTiles tiles dealt to the XCDs in turn
     const int tile = xcd_chunk((int)blockIdx.x, ngroups, kXcdRunTiles / WT::NW) * WT::NW + wv;
     if (tile >= a.ntiles) return;
-    run_wave_tile<T, BS, TILE, XW, REQ>(a, tile, sp + wv * WT::ENTRIES, srp + wv * (kWaveTileRows + 1),
-                                        xs + wv * (XW > 0 ? XW : 1));
+    run_wave_tile<T, BS, TILE, XW, REQ, NTC>(a, tile, sp + wv * WT::ENTRIES, srp + wv * (kWaveTileRows + 1),
+                                             xs + wv * (XW > 0 ? XW : 1));
 }
 
 // Persistent form: a grid of bounded size (the host's persistent_cap), each
@@ -138,7 +137,7 @@ __global__ __launch_bounds__(BS) void k_batch_grid(BatchArgs<T> a)
 // those device-scope atomics on nine addresses set the launch's length.
 // 96 banded FP32 instances (8,390 tiles, 37 MB): 104.3 us with the queues,
 // 12.0 us without.
-template <typename T, int BS, int TILE, int XW>
+template <typename T, int BS, int TILE, int XW, bool NTC>
 __global__ __launch_bounds__(BS) void k_batch_persistent(BatchArgs<T> a)
 {
     using WT = WaveTiles<T, BS, TILE>;
@@ -150,8 +149,8 @@ __global__ __launch_bounds__(BS) void k_batch_persistent(BatchArgs<T> a)
     for (int g = (int)blockIdx.x; g < ngroups; g += (int)gridDim.x) {
         const int tile = xcd_chunk(g, ngroups, kXcdRunTiles / WT::NW) * WT::NW + wv;
         if (tile < a.ntiles)
-            run_wave_tile<T, BS, TILE, XW, false>(a, tile, sp + wv * WT::ENTRIES, srp + wv * (kWaveTileRows + 1),
-                                                  xs + wv * (XW > 0 ? XW : 1));
+            run_wave_tile<T, BS, TILE, XW, false, NTC>(a, tile, sp + wv * WT::ENTRIES, srp + wv * (kWaveTileRows + 1),
+                                                       xs + wv * (XW > 0 ? XW : 1));
     }
 }
 
@@ -213,33 +212,34 @@ template <typename T, int BS, int TILE, int XW>
 int occ_batch()
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(&k_batch_persistent<T, BS, TILE, XW>),
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(&k_batch_persistent<T, BS, TILE, XW, false>),
                                                      BS, 0) != hipSuccess)
         n = 1;
     return n > 0 ? n : 1;
 }
 
-template <typename T, int BS, int TILE, int XW, int KIND>
+template <typename T, int BS, int TILE, int XW, int KIND, bool NTC>
 hipError_t L_batch(const void *p, dim3 g, hipStream_t s)
 {
+    const BatchArgs<T> &a = *(const BatchArgs<T> *)p;
     if constexpr (KIND == kBatchPersistent)
-        hipLaunchKernelGGL((k_batch_persistent<T, BS, TILE, XW>), g, dim3(BS), 0, s, *(const BatchArgs<T> *)p);
+        hipLaunchKernelGGL((k_batch_persistent<T, BS, TILE, XW, NTC>), g, dim3(BS), 0, s, a);
     else
-        hipLaunchKernelGGL((k_batch_grid<T, BS, TILE, XW, KIND == kBatchRequests>), g, dim3(BS), 0, s,
-                           *(const BatchArgs<T> *)p);
+        hipLaunchKernelGGL((k_batch_grid<T, BS, TILE, XW, KIND == kBatchRequests, NTC>), g, dim3(BS), 0, s, a);
     return hipGetLastError();
 }
 
-#define BFN(T, BS, TILE, XW, REQ) \
-    {L_batch<T, BS, TILE, XW, kBatchGrid>, L_batch<T, BS, TILE, XW, kBatchPersistent>, REQ}
+#define BFN(T, BS, TILE, XW, REQ)                                                                        \
+    {{L_batch<T, BS, TILE, XW, kBatchGrid, false>, L_batch<T, BS, TILE, XW, kBatchPersistent, false>, REQ}, \
+     {L_batch<T, BS, TILE, XW, kBatchGrid, true>, L_batch<T, BS, TILE, XW, kBatchPersistent, true>, nullptr}}
 #define BOCC(BS, TILE, XW) {occ_batch<float, BS, TILE, XW>, occ_batch<double, BS, TILE, XW>}
 #define BENTRY(BS, TILE, XW) \
     {BS, TILE, XW, {BFN(float, BS, TILE, XW, nullptr), BFN(double, BS, TILE, XW, nullptr)}, BOCC(BS, TILE, XW)}
 // with the request-table form too (serving's shape)
-#define BENTRY_REQ(BS, TILE, XW)                                                \
-    {BS, TILE, XW,                                                              \
-     {BFN(float, BS, TILE, XW, (L_batch<float, BS, TILE, XW, kBatchRequests>)),   \
-      BFN(double, BS, TILE, XW, (L_batch<double, BS, TILE, XW, kBatchRequests>))}, \
+#define BENTRY_REQ(BS, TILE, XW)                                                       \
+    {BS, TILE, XW,                                                                     \
+     {BFN(float, BS, TILE, XW, (L_batch<float, BS, TILE, XW, kBatchRequests, false>)),   \
+      BFN(double, BS, TILE, XW, (L_batch<double, BS, TILE, XW, kBatchRequests, false>))}, \
      BOCC(BS, TILE, XW)}
 
 // (threads per workgroup, LDS products per workgroup, LDS room for x per

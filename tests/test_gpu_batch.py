@@ -604,3 +604,48 @@ def test_batch_graphs_on_two_streams(spk, dev, persistent):
             assert np.array_equal(ws[i].cpu().numpy(), (0.5 + 0.25 * i) * refs[i] + xs[i]), i
     finally:
         b.free()
+
+
+@pytest.mark.parametrize("dt", [np.float64, np.float32])
+@pytest.mark.parametrize("mode", [0, 1, 3])
+def test_batch_columns_past_the_cache(spk, dev, mode, dt):
+    """Batches whose columns are too many to stay in cache read them
+    non-temporal, a form of the kernel of its own: 1,100 copies of one instance
+    (72 M entries) give every copy the bits of that instance alone, in both
+    launch kinds, and those are the oracle's."""
+    import types
+    copies, m, per = 1100, 4096, 16
+    one = I.banded(m, 20, per / 41, seed_struct=210, seed_val=211, dtype=dt)
+    x = I.uniform(212, 0, m, dt)
+    nnz = int(one.row_ptr[-1])
+    assert nnz * copies > 64 << 20
+    n = np.arange(copies, dtype=np.int64)
+    rp, ci, val = (torch.from_numpy(v).to(dev) for v in (one.row_ptr, one.col_idx, one.val))
+    h = spk.Handle(0)
+    dn = "f64" if dt == np.float64 else "f32"
+    for c in range(21):
+        spk.spk_plan_put(f"batch:{dn}:c{c}", spk.make_variant(group=mode), h)
+    outs = []
+    try:
+        for count in (1, copies):
+            B = types.SimpleNamespace(count=count, m=np.full(count, m), nnz=np.full(count, nnz), rp_off=(m + 1) * n[:count],
+                                      nz_off=nnz * n[:count], vec_off=m * n[:count], row_ptr=np.tile(one.row_ptr, count))
+            arrs = tuple(v.repeat(count) for v in (rp, ci, val))
+            xd = torch.from_numpy(x).to(dev).repeat(count)
+            for persistent in (1, 0):
+                say(f"batch columns mode={mode} {dn} copies={count} persistent={persistent}")
+                y, w = torch.full_like(xd, float("nan")), torch.full_like(xd, float("nan"))
+                b = spk.Batch(B, arrs, persistent=persistent, block=256, x_window=256 if mode else 0, handle=h)
+                try:
+                    b.run(0.5, xd, y, w)
+                    torch.cuda.synchronize()
+                finally:
+                    b.free()
+                outs.append((y.view(count, m), w.view(count, m)))
+    finally:
+        h.close()
+    ref, absum = O.spmv(one, x)
+    bad, worst, at = O.check_rows(outs[0][0][0].cpu().numpy().astype(np.float64), ref, absum, O.tau_for(dt))
+    assert bad == 0, (worst, at)
+    for y, w in outs[1:]:
+        assert bool((y == outs[0][0]).all()) and bool((w == outs[0][1]).all())
