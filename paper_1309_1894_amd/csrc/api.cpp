@@ -606,7 +606,8 @@ spk_status get_blocks(spk_handle h, spk_mat *A, int entries, int block, BlockDat
         return SPK_OK;
     }
     BlockData d;
-    make_row_tiles(A->rp_host.data(), A->nrows, entries, block, A->dtype == SPK_F64, d.host, d.host_k, d.longs);
+    make_row_tiles(A->rp_host.data(), A->nrows, entries, block, A->dtype == SPK_F64, A->max_len, d.host, d.host_k,
+                   d.longs);
     d.nblk = (int32_t)d.host.size() - 1;
     std::vector<int32_t> lrow;
     for (int32_t t : d.longs) lrow.push_back((int32_t)(d.host[t] & kBlkRowMask));

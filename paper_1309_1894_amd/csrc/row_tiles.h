@@ -88,12 +88,13 @@ inline int64_t long_row_min(int BS) { return BS > 256 ? 1024 : 512; }
 // 700 5.7 and 6.0, 300 of 2,000 5.7 and 7.7; CG's 512 threads, five iterations:
 // 8,000 of 1,100 274 and 172, 3,000 of 3,000 198 and 195.  In FP32 the
 // workgroup is the faster one at all of these (10,000 of 520 16.4 and 19.7,
-// 3,000 of 2,000 11.9 and 29.7).
+// 3,000 of 2,000 11.9 and 29.7).  (`max_len`: the longest row, or more; it
+// spares matrices without long rows the count.)
 constexpr int64_t kManyLongRows = 2048, kManyLongRowMax = 4096;
-inline int64_t long_row_line(const int32_t *rp, int64_t m, int E, int BS, bool f64)
+inline int64_t long_row_line(const int32_t *rp, int64_t m, int E, int BS, bool f64, int64_t max_len)
 {
     const int64_t line = long_row_min(BS);
-    if (!f64) return line;
+    if (!f64 || max_len <= line) return line;
     int64_t rows = 0, entries = 0;
     for (int64_t r = 0; r < m; ++r) {
         const int64_t l = rp[r + 1] - rp[r];
@@ -106,11 +107,11 @@ inline int64_t long_row_line(const int32_t *rp, int64_t m, int E, int BS, bool f
     return rows >= kManyLongRows && rows > others ? kManyLongRowMax : line;
 }
 
-inline void make_row_tiles(const int32_t *rp, int64_t m, int E, int BS, bool f64, std::vector<uint32_t> &out,
-                           std::vector<int32_t> &out_k, std::vector<int32_t> &longs)
+inline void make_row_tiles(const int32_t *rp, int64_t m, int E, int BS, bool f64, int64_t max_len,
+                           std::vector<uint32_t> &out, std::vector<int32_t> &out_k, std::vector<int32_t> &longs)
 {
     const int64_t short_max = std::min<int64_t>(kStreamRowMax, E);
-    const int64_t long_min = long_row_line(rp, m, E, BS, f64);
+    const int64_t long_min = long_row_line(rp, m, E, BS, f64, max_len);
     const int64_t row_cap = 2 * 64;
     out.clear();
     out_k.clear();

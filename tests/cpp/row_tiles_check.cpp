@@ -64,10 +64,12 @@ static std::vector<int32_t> check_tiles(const std::vector<int64_t> &len, int E, 
     std::vector<int32_t> rp{0}, k, longs;
     for (int64_t l : len) rp.push_back((int32_t)(rp.back() + l));
     const int64_t m = (int64_t)len.size();
+    const int64_t top = m > 0 ? *std::max_element(len.begin(), len.end()) : 0;
     std::vector<uint32_t> t;
-    CHECK(long_row_line(rp.data(), m, E, BS, f64) == line, "line %lld, not %lld",
-          (long long)long_row_line(rp.data(), m, E, BS, f64), (long long)line);
-    make_row_tiles(rp.data(), m, E, BS, f64, t, k, longs);
+    for (int64_t max_len : {top, (int64_t)INT32_MAX})
+        CHECK(long_row_line(rp.data(), m, E, BS, f64, max_len) == line, "line %lld, not %lld",
+              (long long)long_row_line(rp.data(), m, E, BS, f64, max_len), (long long)line);
+    make_row_tiles(rp.data(), m, E, BS, f64, top, t, k, longs);
     const int64_t short_max = E < 512 ? E : 512;
     std::vector<int32_t> found;
     CHECK(t.size() == k.size() && (t.back() & kBlkRowMask) == (uint32_t)m && (t[0] & kBlkRowMask) == 0, "ends");
@@ -119,7 +121,7 @@ static void tiles(std::mt19937_64 &g)
         for (int E : {256, 512, 1024})
             for (int BS : {64, 256, 512})
                 for (bool f64 : {false, true})
-                    check_tiles(len, E, BS, f64, long_row_line(rp.data(), (int64_t)len.size(), E, BS, f64));
+                    check_tiles(len, E, BS, f64, long_row_line(rp.data(), (int64_t)len.size(), E, BS, f64, INT32_MAX));
     }
 }
 
