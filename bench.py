@@ -6,8 +6,8 @@ Headline (``value``): achieved HBM GB/s of one Krylov-style step
 CSR instances (row counts log-uniform in [64, 16384), half-bandwidth 1..32,
 60% fill inside the band), all instances in one hipGraph-replayed launch of
 the tile kernel, autotuned per shape class (the tuner picks the launch kind:
-one workgroup per tile group, or a persistent grid pulling tiles from
-per-XCD queues; and per class the tile kernel, compact one-byte columns
+one workgroup per tile group, or a persistent grid walking them in strides;
+and per class the tile kernel, compact one-byte columns
 among them).  Bytes are the algorithmic ones of the CSR statement: every
 array once (values, 4-byte column indices, row pointers, x, y, w), no
 re-reads, no padding; the bytes the tuned plan's own form moves (fewer,

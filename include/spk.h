@@ -155,7 +155,8 @@ typedef struct {
  *   block   threads per workgroup (64..1024, power of two)
  *   group   SpMV VECTOR: lanes per row (2..64), or of the row stream (lds > 1)
  *           the rows per wavefront divided by `unroll`; SELL: rows per slice
- *   unroll  independent loads in flight per lane (1, 2, 4 or 8)
+ *   unroll  independent loads in flight per lane (1, 2, 4 or 8); the row
+ *           stream's factor of its rows per wavefront (1, 3, 5 or 7)
  *   vec     vector ops: elements per lane load (1, 2 or 4; at most 16 bytes);
  *           SpMV SCALAR/VECTOR: entries per value/index access (0 = one);
  *           ADAPTIVE: 2 = two-byte columns (each row-stream block whose
@@ -636,7 +637,7 @@ spk_status spk_batch_tile_modes(spk_handle h, spk_batch b, int64_t *tiles, int64
  * (given as an option, it gives that grid again). */
 spk_status spk_batch_config(spk_handle h, spk_batch b, spk_batch_opts *out);
 
-/* Frees a batch plan (its tiles, counters and captured graphs).  Library
+/* Frees a batch plan (its tiles, compact columns and captured graphs).  Library
  * plumbing, not in the paper. */
 spk_status spk_batch_free(spk_handle h, spk_batch b);
 

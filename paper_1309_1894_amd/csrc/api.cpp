@@ -173,8 +173,10 @@ spk_variant default_variant(spk_handle h, const spk_problem &p, const spk_csr *c
         // 20,000,003 FP64 (6.74 TB/s), 36.9 in FP32 (6.5), 461 and 232 at 2^27,
         // where 256 threads with two 16-byte accesses each take 75.6, 38.0, 525
         // and 264 (wavefronts that wait for more reads before they write hold
-        // their slots longer).  Below 40 MB the two agree within 2%, and at n =
-        // 1e6 the wide form is the faster (6.3 us against 7.0).
+        // their slots longer).  AXPY, wide and narrow: 76.5 us and 71.2 at n =
+        // 20,000,003 FP64, 193 and 174 at 5e7, in FP32 37.5 and 36.6, 93.6 and
+        // 87.8.  Below 40 MB the two agree within 2%, and at n = 1e6 the wide form
+        // is the faster (6.3 us against 7.0).
         if (p.n >= kWaxpyNarrowBytes / (int64_t)dtype_size(p.dtype)) {
             v.block = 64;
             v.vec = 1;
@@ -232,13 +234,15 @@ spk_variant default_variant(spk_handle h, const spk_problem &p, const spk_csr *c
     // A borrowed CSR matrix (only its sizes are known): the row stream, with
     // as many rows per wavefront as fill one 512-entry chunk, but at least
     // eight wavefronts per compute unit: of 600,000 rows of 19.8 entries (FP64)
-    // 24 per wavefront take 30.3 us, 20 and 28, which leave more of a chunk
-    // empty or start a second one, 31.6 and 33.3; 300,000 rows of 39.0 entries
-    // 29.5 with 12, 30.7 with 8, 33.0 with 16; 100,000 rows of 19.8 6.9 with
-    // 16, 8.6 with 32.  From about 80 entries a row on, G lanes per row read
-    // long runs anyway (145 entries: 15.1 us against 18.5 with 8 rows a
-    // wavefront, 73 entries: 20.0 against 14.4); and below 8,192 rows they
-    // give the GPU more wavefronts.
+    // 24 per wavefront take 27.6 us, 20 and 28, which leave more of a chunk
+    // empty or start a second one, 30.3 and 30.3; 300,000 rows of 39.0 entries
+    // 28.4 with 12, 33.4 with 8, 28.5 with 16; 100,000 rows of 19.8 7.3 with
+    // 16, 7.9 with 32.  Up to 80 entries a row its error is shown to be no
+    // larger than that of G lanes per row (in time it leads past that line too:
+    // 100,000 rows of 74 entries 20.4 us against 24.6 with the best G, 50,000 of
+    // 146 20.8 and 22.3).  Below 8,192 rows both are bound by the launch (3,000
+    // and 9,000 rows of 19.8: 5.2 to 5.7 us every way), and G lanes per row give
+    // the GPU more wavefronts.
     if (mean <= 80.0 && csr && csr->nrows >= 8192) {
         // the compiled shapes: group * unroll = 64, 48, 32, 28, 24, 20, 16, 12, 8 rows
         const int shapes[][2] = {{64, 1}, {16, 3}, {32, 1}, {4, 7}, {8, 3}, {4, 5}, {16, 1}, {4, 3}, {8, 1}};

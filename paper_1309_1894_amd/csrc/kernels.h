@@ -100,11 +100,10 @@ const SpmvEntry *spmv_table(int *count);
 // SPK_FMT_XWIN: the entries regrouped by column window (window w holds the
 // columns [w*WC, (w+1)*WC), WC = window bytes / sizeof(T)) into (row,
 // window) pairs, window-major and, inside a window, in row order; a pair's
-// entries keep their order in the row.  Pair p has entries [ent[p],
-// ent[p+1]) of ci (column inside the window) and val.  Wavefront tiles over
-// the pairs never cross a window (start pair | mode << 30, as the row
-// blocks of the LDS-staged kernel, and their first entries); chunk c is the
-// tiles [chunk_t[c], chunk_t[c+1]) of window chunk_w[c], one workgroup each.
+// entries keep their order in the row, and its first one is marked in the top
+// bit of its column word.  Chunk c is a run of pairs of window chunk_w[c], one
+// workgroup; its wavefront v runs the pairs [wave_p[i], wave_p[i+1]), i =
+// c*wavefronts + v, whose entries start at wave_k[i].
 struct XwinArgs {
     const int32_t *wave_p;     // nchunk * wavefronts + 1: first pair of each wavefront's range
     const int32_t *wave_k;     // the same: its first entry

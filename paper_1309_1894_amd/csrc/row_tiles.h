@@ -1,5 +1,5 @@
-// row_tiles.h -- wavefront tiles over the rows of a CSR matrix (host
-// planning, shared by the LDS-staged row-block kernel and the x-window
+// row_tiles.h -- tiles over the rows of a CSR matrix (host planning of the
+// row-block and CG kernels, and, over (row, window) pairs, of the x-window
 // form; plain C++, no GPU headers).
 #pragma once
 
@@ -13,14 +13,13 @@ namespace spk {
 // A tile is recorded as its start row | mode << 30 and its first entry.
 constexpr uint32_t kBlkRowMask = 0x3FFFFFFFu;
 constexpr uint32_t kBlkStream = 0u;     // short rows streamed through the wavefront's LDS slice
-constexpr int kStreamRowsPerThread = 2; // a workgroup row stream holds at most 2*BS rows
 constexpr uint32_t kBlkWave = 1u;       // medium rows, one after another, 64 lanes per row
-constexpr uint32_t kBlkLong = 2u;       // one long row, 64 lanes
+constexpr uint32_t kBlkLong = 2u;       // one long row, a workgroup
 
-// Wavefront tiles for the LDS-staged kernels, E = row-stream capacity:
-// runs of short rows (at most 96 entries each) whose entries fit E and that
-// number at most 128; runs of medium rows, up to 4E entries in all, one
-// wavefront with 64 lanes per row; single long rows (over 8E entries).
+// Tiles of the x-window form's pairs, of which only the cuts are used (chunks
+// end at them): runs of short rows (at most 96 entries each) whose entries fit
+// E and that number at most 128; runs of medium rows, up to 4E entries in all;
+// single long rows (over 8E entries).
 inline void make_blocks(const int32_t *rp, int64_t m, int E, std::vector<uint32_t> &out, std::vector<int32_t> &out_k)
 {
     const int64_t kShort = std::min<int64_t>(96, E);
