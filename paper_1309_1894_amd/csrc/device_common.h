@@ -107,6 +107,19 @@ __device__ __forceinline__ double block_sum(double v, double *red)
     }
 }
 
+// A sum with the rounding errors of its additions kept (Knuth's two-sum).
+struct KeptSum {
+    double sum = 0.0, err = 0.0;
+    __device__ __forceinline__ void add(double v)
+    {
+        const double next = sum + v, part = next - sum;
+        err += (sum - (next - part)) + (v - part);
+        sum = next;
+    }
+    // (an overflow, an infinity or a NaN leaves the errors no numbers)
+    __device__ __forceinline__ double value() const { return err - err == 0.0 ? sum + err : sum; }
+};
+
 // Workgroups are dispatched to the 8 XCDs round-robin (workgroup b runs on
 // XCD b % 8), each XCD with its own L2.
 constexpr int kXcds = 8;

@@ -154,24 +154,18 @@ __global__ __launch_bounds__(BS) void k_spmv_vector(SpmvArgs<T> a)
 
 // --------------------------------------------------- VECTOR, row stream --
 
-// a + b + c + d in FP64, rounded twice: the rounding errors of the first two
-// additions (Knuth's two-sum) are added at the end, unless an overflow, an
-// infinity or a NaN left them no numbers.  The row stream rounds a product as
+// a + b + c + d with the errors of the additions kept.  The row stream rounds a product as
 // it goes to LDS, where G lanes per row round a lane's first one only; with
 // its last additions kept so, rows of 2 to 79 random entries end with 0.78 to
 // 1.00 of the rms error of G lanes per row, without it with up to 1.04.
 __device__ __forceinline__ double sum4(double a, double b, double c, double d)
 {
-    double sum = a, err = 0.0;
-    const auto add = [&](double p) {
-        const double s = sum + p, t = s - sum;
-        err += (sum - (s - t)) + (p - t);
-        sum = s;
-    };
-    add(b);
-    add(c);
-    add(d);
-    return err - err == 0.0 ? sum + err : sum;
+    KeptSum s;
+    s.sum = a;
+    s.add(b);
+    s.add(c);
+    s.add(d);
+    return s.value();
 }
 
 // R consecutive rows per wavefront on the plain CSR arrays (no tiles made

@@ -100,19 +100,6 @@ __global__ __launch_bounds__(BS) void k_waxpy(int64_t n, T alpha, const T *x, co
     }
 }
 
-// A sum with the rounding errors of its additions kept (Knuth's two-sum).
-struct KeptSum {
-    double sum = 0.0, err = 0.0;
-    __device__ __forceinline__ void add(double v)
-    {
-        const double next = sum + v, part = next - sum;
-        err += (sum - (next - part)) + (v - part);
-        sum = next;
-    }
-    // (an overflow, an infinity or a NaN leaves the errors no numbers)
-    __device__ __forceinline__ double value() const { return err - err == 0.0 ? sum + err : sum; }
-};
-
 // block_sum with the wavefronts' sums added as a tree, in every wavefront.
 template <int BS>
 __device__ __forceinline__ double block_sum_tree(double v, double *red)

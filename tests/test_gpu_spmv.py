@@ -629,6 +629,44 @@ def test_borrowed_csr_is_as_accurate_as_lanes_per_row(spk, dev, length):
     assert stream <= lanes, (stream, lanes)
 
 
+@pytest.mark.parametrize("length,rows", [(300, 12000), (512, 8000)])
+def test_wide_rows_are_as_accurate_as_lanes_per_row(spk, dev, length, rows):
+    """FP64 row blocks (a product is rounded on its way through LDS) have no
+    larger rms error than a wavefront per row with four sums to a lane, both
+    against sums in 80-bit floats; the rows of one length, signs mixed."""
+    rng = np.random.default_rng(length)
+    n = 8000
+    ci = rng.integers(0, n, (rows, length)).astype(np.int32)
+    val = rng.random((rows, length)) * 2 - 1
+    A = I.CSR(rows, n, (np.arange(rows + 1) * length).astype(np.int32), ci.ravel(), val.ravel())
+    say(f"accuracy of rows of {length}")
+
+    def split(v):                       # Dekker's: exact products
+        t = 134217729.0 * v
+        hi = t - (t - v)
+        return hi, v - hi
+
+    M = spk.Matrix(A)
+    square = {None: 0.0, 64: 0.0}
+    try:
+        for _ in range(max(1, 12000 // rows)):
+            x = rng.random(n) * 2 - 1
+            xs = x[ci]
+            (vh, vl), (xh, xl) = split(val), split(xs)
+            p = val * xs
+            e = ((vh * xh - p) + vh * xl + vl * xh) + vl * xl
+            exact = p.astype(np.longdouble).sum(1) + e.astype(np.longdouble).sum(1)
+            xd = torch.from_numpy(x).to(dev)
+            for g in square:
+                y = torch.empty(rows, dtype=torch.float64, device=dev)
+                v = g and spk.make_variant(format=spk.SPK_FMT_VECTOR, block=256, group=g, unroll=4, streams=1)
+                spk.spk_run(spk.problem(spk.SPK_OP_SPMV, A=M, x=xd, y=y), v)
+                square[g] += float(np.sum((y.cpu().numpy().astype(np.longdouble) - exact) ** 2))
+    finally:
+        M.release()
+    assert square[None] <= square[64], (square[None] / square[64]) ** 0.5
+
+
 @pytest.mark.parametrize("dt", [1, 0])
 def test_row_blocks_either_side_of_the_kept_size(spk, dev, dt):
     """Row blocks have a form whose values may stay in the last-level cache
