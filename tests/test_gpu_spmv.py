@@ -629,7 +629,7 @@ def test_borrowed_csr_is_as_accurate_as_lanes_per_row(spk, dev, length):
     assert stream <= lanes, (stream, lanes)
 
 
-@pytest.mark.parametrize("length,rows", [(300, 12000), (512, 8000)])
+@pytest.mark.parametrize("length,rows", [(300, 12000), (512, 8000), (800, 1500), (1100, 1500)])
 def test_wide_rows_are_as_accurate_as_lanes_per_row(spk, dev, length, rows):
     """FP64 row blocks (a product is rounded on its way through LDS) have no
     larger rms error than a wavefront per row with four sums to a lane, both
