@@ -403,27 +403,26 @@ __device__ __forceinline__ double block_row(const int32_t *ci_, const T *val_, c
             acc[j] = base + (int)threadIdx.x + j * BS < e ? t : acc[j];
         }
     }
-    if constexpr (sizeof(T) == 8) {
-        // the lane's sums and the wavefronts' with the errors of their additions
-        // kept: with fewer products to a lane than a wavefront per row has, fewer of
-        // them are fused into a sum that is no longer zero.  1,500 rows of 800 and
-        // 1,100: 0.93 and 0.91 of a wavefront's rms error, 1.01 and 1.03 with plain
-        // additions (FP32 products are exact here)
-        KeptSum lane, sum;
 #pragma unroll
-        for (int j = 0; j < UNR; ++j) lane.add(acc[j]);
-        const double t = group_sum<kWave>(lane.value());
+    for (int d = 1; d < UNR; d *= 2)
+#pragma unroll
+        for (int j = 0; j + d < UNR; j += 2 * d) acc[j] += acc[j + d];
+    if constexpr (sizeof(T) == 8) {
+        // the wavefronts' sums with the errors of their additions kept: with fewer
+        // products to a lane than a wavefront per row has, fewer of them are fused
+        // into a sum that is no longer zero.  1,500 rows of 800 and 1,100: 0.97
+        // and 0.96 of a wavefront's rms error, 1.01 and 1.03 with plain additions
+        // (FP32 products are exact here)
+        const double t = group_sum<kWave>(acc[0]);
         if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = t;
         __syncthreads();
         if (threadIdx.x >= kWave) return 0.0;
+        KeptSum sum;
+        sum.sum = red[0];
 #pragma unroll
-        for (int i = 0; i < BS / kWave; ++i) sum.add(red[i]);
+        for (int i = 1; i < BS / kWave; ++i) sum.add(red[i]);
         return sum.value();
     } else {
-#pragma unroll
-        for (int d = 1; d < UNR; d *= 2)
-#pragma unroll
-            for (int j = 0; j + d < UNR; j += 2 * d) acc[j] += acc[j + d];
         return block_sum<BS>(acc[0], red);
     }
 }
